@@ -12,7 +12,7 @@
 
 namespace ccuba {
 
-constexpr int kDivBlock = 128;  // two wavefronts: the maximum's search and the minimum's
+constexpr int kDivBlock = 128;  // threads of one region's search sample
 
 struct DRegions {
   double *lo, *hi;          // [R][d] bounds

@@ -5,13 +5,13 @@
 //   split   per selected region, one wavefront: d probes f(xmax with
 //           x_j := xmin_j); the cut goes through the midpoint of the
 //           dimension of largest loss fmax - f_j; the two children
-//   search  per child, one workgroup of two wavefronts: both evaluate the
-//           nsearch Philox points of the child and reduce to the largest and
-//           smallest value (ties to the lower index); then wave 0 climbs to
-//           the maximum and wave 1 descends to the minimum by compass search,
-//           lane c < 2d evaluating candidate c (x +- h_j e_j, clipped) each
-//           iteration; a move is taken when the best candidate (ties to the
-//           lower c) beats the current value, else every step halves
+//   search  per child: two wavefronts evaluate its nsearch Philox points and
+//           reduce to the largest and smallest value (ties to the lower
+//           index); then one group of lanes climbs to the maximum and one
+//           descends to the minimum by compass search, lane c < 2d of a group
+//           evaluating candidate c (x +- h_j e_j, clipped) each iteration; a
+//           move is taken when the best candidate (ties to the lower c) beats
+//           the current value, else every step halves
 //   totals  the largest and the total spread over all regions (fixed order)
 // The host reads the totals after each step and sizes the next.
 #include "divonne.h"
@@ -78,152 +78,190 @@ __global__ void __launch_bounds__(64) div_root_kernel(DivArgs A) {
   }
 }
 
-// a double of lane l (l wave-uniform) to every lane
-__device__ __forceinline__ double readlane_d(double v, int l) {
+namespace {
+
+// the lane values a row rotation by CTRL - 0x120 lanes brings (rows of 16)
+template <int CTRL>
+__device__ __forceinline__ double row_ror(double v) {
   const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// D = 4 NB coordinates in registers (d <= D): the point and the steps of the
-// compass search live in every lane, and a move is broadcast from the
-// winning lane, so an iteration needs no LDS and no barrier.
+// the largest value of each group of GL = 16 or 32 lanes, in all its lanes
+// (NaNs lose)
+template <int GL>
+__device__ __forceinline__ double group_max(double v) {
+  v = fmax(v, row_ror<0x128>(v));
+  v = fmax(v, row_ror<0x124>(v));
+  v = fmax(v, row_ror<0x122>(v));
+  v = fmax(v, row_ror<0x121>(v));
+  if constexpr (GL == 32) v = fmax(v, __shfl_xor(v, 16, 64));
+  return v;
+}
+
+}  // namespace
+
+// A search has 2d candidates an iteration, so it takes a group of 16 lanes
+// (d <= 8) or 32, and one wavefront climbs for two regions' maxima and minima
+// at once, or one's: a wavefront per search leaves 3/4 of its lanes idle at
+// d = 8.  The search sample has a block's two wavefronts per region.
+template <int NB>
+struct DivShape {
+  static constexpr int kGroup = NB <= 2 ? 16 : 32;       // lanes of one search
+  static constexpr int kRegions = 64 / (2 * kGroup);     // regions of a block
+  static constexpr int kThreads = kDivBlock * kRegions;  // two wavefronts a region
+};
+
+// What bounds it: the chain of niter dependent iterations of a region (small
+// launches), instruction issue with about one wavefront per SIMD (large
+// ones).  D = 4 NB coordinates in registers (d <= D): the point lives in every
+// lane of a group; a lane's own coordinate, its step and its bounds are held
+// apart, so that an iteration selects nothing by a lane-varying index.  The
+// best candidate is a row-rotation maximum and a ballot; ties go to the lower
+// candidate.  Gaussian d = 8, 1024 search points and 64 iterations, launches of
+// 1 to 2048 regions on the way to 8192: 42.2 us a launch on average, 90.9 with a
+// wavefront per search, lane-varying selects and a six-step (value, index)
+// reduction.
 template <int FAM, int NB>
-__global__ void __launch_bounds__(kDivBlock) div_search_kernel(DivArgs A) {
-  constexpr int D = 4 * NB;
-  __shared__ double sLo[kMaxDim], sW[kMaxDim], sP0[kMaxDim], sP1[kMaxDim];
-  __shared__ double sv[2][2], sF[2];
-  __shared__ int si[2][2];
-  const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int pos = A.chpos[c], q = A.chser[c], d = A.d;
-  if (tid < d) {
-    const double lo = A.R.lo[(size_t)pos * d + tid];
-    sLo[tid] = lo;
-    sW[tid] = A.R.hi[(size_t)pos * d + tid] - lo;
-    sP0[tid] = A.p64[tid];
-    sP1[tid] = A.p64[kParamRow + tid];
+__global__ void __launch_bounds__(DivShape<NB>::kThreads) div_search_kernel(DivArgs A,
+                                                                            int nchild) {
+  constexpr int D = 4 * NB, GL = DivShape<NB>::kGroup, RB = DivShape<NB>::kRegions;
+  __shared__ double sLo[RB][kMaxDim], sW[RB][kMaxDim];
+  __shared__ double sv[2 * RB][2];
+  __shared__ int si[2 * RB][2];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, d = A.d;
+  const int first = blockIdx.x * RB;
+  // (an odd launch's last block searches its one region twice and writes once)
+  if (tid < RB * kMaxDim && tid % kMaxDim < d) {
+    const int r = tid / kMaxDim, j = tid % kMaxDim;
+    const int pos = A.chpos[min(first + r, nchild - 1)];
+    const double lo = A.R.lo[(size_t)pos * d + j];
+    sLo[r][j] = lo;
+    sW[r][j] = A.R.hi[(size_t)pos * d + j] - lo;
   }
   __syncthreads();
-  double p0[D], p1[D], lo[D], wd[D];
+  // Coordinates from d to D are 0 with constants that leave every family's
+  // running value as it is (a factor 0 of a sum's term, a factor 1 of the
+  // product peak), so that no step tests j < d.
+  double p0[D], p1[D];  // (the rows are zero-padded)
 #pragma unroll
   for (int j = 0; j < D; ++j) {
-    p0[j] = j < d ? sP0[j] : 0.0;
-    p1[j] = j < d ? sP1[j] : 0.0;
-    lo[j] = j < d ? sLo[j] : 0.0;
-    wd[j] = j < d ? sW[j] : 0.0;
+    p0[j] = FAM == PRODUCT_PEAK && j >= d ? 1.0 : A.p64[j];
+    p1[j] = A.p64[kParamRow + j];
   }
-  // the point of search-sample index i
-  auto point = [&](int i, double (&x)[D]) {
+  // the point of search-sample index i of the region with search serial q
+  auto point = [&](int i, int q, const double *lo, const double *wd, double (&x)[D]) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const U4 W = philox4x32_10(U4{(uint32_t)i, ((uint32_t)q << 8) | (uint32_t)b, A.sid, 0u},
                                  A.key0, A.key1);
       const uint32_t r[4] = {W.x, W.y, W.z, W.w};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) x[4 * b + k] = fma((double)r[k] * 0x1p-32 + 0x1p-33,
-                                                      wd[4 * b + k], lo[4 * b + k]);
+      for (int k = 0; k < 4; ++k) {
+        const int j = 4 * b + k;
+        x[j] = j < d ? fma((double)r[k] * 0x1p-32 + 0x1p-33, wd[j], lo[j]) : 0.0;
+      }
     }
   };
-  auto value = [&](const double (&x)[D]) {
-    double acc = Genz<double, FAM>::init(p1[0]);
+  // the search sample: wavefronts 2r and 2r + 1 take region r's points
+  {
+    const int r = w >> 1, t = tid & (kDivBlock - 1);
+    const int q = A.chser[min(first + r, nchild - 1)];
+    double lo[D], wd[D];
 #pragma unroll
-    for (int j = 0; j < D; ++j)
-      if (j < d) acc = Genz<double, FAM>::step(acc, x[j], p0[j], p1[j]);
-    return Genz<double, FAM>::finish(acc, d);
-  };
-  // the search sample
-  double bmax = -INFINITY, bmin = INFINITY;
-  int imax = 0x7fffffff, imin = 0x7fffffff;
-  for (int i = tid; i < A.nsearch; i += kDivBlock) {
-    double x[D];
-    point(i, x);
-    const double f = value(x);
-    if (f > bmax) {  // i grows, so a tie keeps the lower index
-      bmax = f;
-      imax = i;
+    for (int j = 0; j < D; ++j) {
+      lo[j] = j < d ? sLo[r][j] : 0.0;
+      wd[j] = j < d ? sW[r][j] : 0.0;
     }
-    if (f < bmin) {
-      bmin = f;
-      imin = i;
+    double bmax = -INFINITY, bmin = INFINITY;
+    int imax = 0x7fffffff, imin = 0x7fffffff;
+    for (int i = t; i < A.nsearch; i += kDivBlock) {
+      double x[D];
+      point(i, q, lo, wd, x);
+      double acc = Genz<double, FAM>::init(p1[0]);
+#pragma unroll
+      for (int j = 0; j < D; ++j) acc = Genz<double, FAM>::step(acc, x[j], p0[j], p1[j]);
+      const double f = Genz<double, FAM>::finish(acc, d);
+      if (f > bmax) {  // i grows, so a tie keeps the lower index
+        bmax = f;
+        imax = i;
+      }
+      if (f < bmin) {
+        bmin = f;
+        imin = i;
+      }
     }
-  }
-  wave_best(bmax, imax, 1.0);
-  wave_best(bmin, imin, -1.0);
-  if (lane == 0) {
-    sv[w][0] = bmax;
-    si[w][0] = imax;
-    sv[w][1] = bmin;
-    si[w][1] = imin;
+    wave_best(bmax, imax, 1.0);
+    wave_best(bmin, imin, -1.0);
+    if (lane == 0) {
+      sv[w][0] = bmax;
+      si[w][0] = imax;
+      sv[w][1] = bmin;
+      si[w][1] = imin;
+    }
   }
   __syncthreads();
-  // wave 0 searches the maximum, wave 1 the minimum, from the sample's best
-  const int k = w;
+  if (w != 0) return;
+  // one wavefront from here: group g searches region g / 2's maximum (even g)
+  // or minimum (odd g), from the sample's best
+  const int g = lane / GL, c = lane & (GL - 1), base = lane & ~(GL - 1);
+  const int r = g >> 1, k = g & 1;
+  const bool write = first + r < nchild;
+  const int child = min(first + r, nchild - 1);
+  const int pos = A.chpos[child];
   const double sign = k == 0 ? 1.0 : -1.0;
-  double fx;
+  double sfx;  // sign * (the value held)
   int i0;
   {
-    const double v0 = sv[0][k], v1 = sv[1][k];
-    const int j0 = si[0][k], j1 = si[1][k];
-    const bool second = sign * v1 > sign * v0 || (v1 == v0 && j1 < j0);
-    fx = second ? v1 : v0;
-    i0 = __builtin_amdgcn_readfirstlane(second ? j1 : j0);
+    const double v0 = sign * sv[2 * r][k], v1 = sign * sv[2 * r + 1][k];
+    const int j0 = si[2 * r][k], j1 = si[2 * r + 1][k];
+    const bool second = v1 > v0 || (v1 == v0 && j1 < j0);
+    sfx = second ? v1 : v0;
+    i0 = second ? j1 : j0;
   }
-  double x[D], h[D];
-  point(i0, x);
-#pragma unroll
-  for (int j = 0; j < D; ++j) h[j] = wd[j] / 4.0;
+  double x[D];
+  point(i0, A.chser[child], sLo[r], sW[r], x);
   // lane c < 2d owns candidate c: coordinate jc = c/2, + for even c
-  const int jc = lane >> 1;
-  const bool plus = (lane & 1) == 0, live = lane < 2 * d;
-  double loj = 0.0, hij = 0.0;
+  const int jc = c >> 1;
+  const bool plus = (c & 1) == 0, live = c < 2 * d;
+  const double loj = live ? sLo[r][jc] : 0.0, wj = live ? sW[r][jc] : 0.0;
+  const double hij = loj + wj;
+  double hj = wj / 4.0, xj = 0.0;
 #pragma unroll
   for (int j = 0; j < D; ++j)
-    if (j == jc) {
-      loj = lo[j];
-      hij = lo[j] + wd[j];
-    }
+    if (j == jc) xj = x[j];
   for (int t = 0; t < A.niter; ++t) {
-    double xj = 0.0, hj = 0.0;
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-      if (j == jc) {
-        xj = x[j];
-        hj = h[j];
-      }
     const double zc = fmin(fmax(plus ? xj + hj : xj - hj, loj), hij);
     double acc = Genz<double, FAM>::init(p1[0]);
 #pragma unroll
     for (int j = 0; j < D; ++j)
-      if (j < d) acc = Genz<double, FAM>::step(acc, j == jc ? zc : x[j], p0[j], p1[j]);
-    double bv = live ? Genz<double, FAM>::finish(acc, d) : sign * -INFINITY;
-    int bi = live ? lane : 0x7fffffff;
-    wave_best(bv, bi, sign);
-    if (sign * bv > sign * fx) {
-      const int win = __builtin_amdgcn_readfirstlane(bi);
-      const double znew = readlane_d(zc, win);
-      const int jw = win >> 1;
-      fx = bv;
+      acc = Genz<double, FAM>::step(acc, j == jc ? zc : x[j], p0[j], p1[j]);
+    const double sf = live ? sign * Genz<double, FAM>::finish(acc, d) : -INFINITY;
+    const double best = group_max<GL>(sf);
+    const uint32_t eq = (uint32_t)(__ballot(live && sf == best) >> base) &
+                        (uint32_t)((1ull << GL) - 1ull);
+    const int win = __ffs((int)eq) - 1;  // (-1 when every candidate is NaN: no move then)
+    const double znew = __shfl(zc, base + max(win, 0), 64);
+    const bool move = best > sfx;
+    const int jw = move ? win >> 1 : -1;
+    sfx = move ? best : sfx;
+    xj = jc == jw ? znew : xj;
+    hj = move ? hj : hj * 0.5;
 #pragma unroll
-      for (int j = 0; j < D; ++j) x[j] = j == jw ? znew : x[j];
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) h[j] *= 0.5;
-    }
+    for (int j = 0; j < D; ++j) x[j] = j == jw ? znew : x[j];
   }
-  double* xo = (k == 0 ? A.R.xmax : A.R.xmin) + (size_t)pos * d;
-#pragma unroll
-  for (int j = 0; j < D; ++j)
-    if (j < d && lane == j) xo[j] = x[j];
-  if (lane == 0) {
+  const double fx = sign * sfx, other = __shfl_xor(fx, GL, 64);
+  if (!write) return;
+  if (live && plus) (k == 0 ? A.R.xmax : A.R.xmin)[(size_t)pos * d + jc] = xj;
+  if (c == 0) {
     (k == 0 ? A.R.fmax : A.R.fmin)[pos] = fx;
-    sF[k] = fx;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double V = 1.0;
-    for (int j = 0; j < d; ++j) V *= sW[j];
-    A.R.spread[pos] = 0.5 * V * (sF[0] - sF[1]);
+    if (k == 0) {
+      double V = 1.0;
+      for (int j = 0; j < d; ++j) V *= sW[r][j];
+      A.R.spread[pos] = 0.5 * V * (fx - other);
+    }
   }
 }
 
@@ -331,24 +369,23 @@ hipError_t launch_div_root(const DivArgs &A, hipStream_t s) {
 
 template <int NB>
 static void launch_search_nb(const DivArgs &A, int nchild, hipStream_t s) {
+  constexpr int RB = DivShape<NB>::kRegions;
+  const dim3 grid((nchild + RB - 1) / RB), block(DivShape<NB>::kThreads);
   switch (A.family) {
     case GAUSSIAN:
-      hipLaunchKernelGGL((div_search_kernel<GAUSSIAN, NB>), dim3(nchild), dim3(kDivBlock), 0, s, A);
+      hipLaunchKernelGGL((div_search_kernel<GAUSSIAN, NB>), grid, block, 0, s, A, nchild);
       break;
     case OSCILLATORY:
-      hipLaunchKernelGGL((div_search_kernel<OSCILLATORY, NB>), dim3(nchild), dim3(kDivBlock), 0, s,
-                         A);
+      hipLaunchKernelGGL((div_search_kernel<OSCILLATORY, NB>), grid, block, 0, s, A, nchild);
       break;
     case PRODUCT_PEAK:
-      hipLaunchKernelGGL((div_search_kernel<PRODUCT_PEAK, NB>), dim3(nchild), dim3(kDivBlock), 0, s,
-                         A);
+      hipLaunchKernelGGL((div_search_kernel<PRODUCT_PEAK, NB>), grid, block, 0, s, A, nchild);
       break;
     case CORNER_PEAK:
-      hipLaunchKernelGGL((div_search_kernel<CORNER_PEAK, NB>), dim3(nchild), dim3(kDivBlock), 0, s,
-                         A);
+      hipLaunchKernelGGL((div_search_kernel<CORNER_PEAK, NB>), grid, block, 0, s, A, nchild);
       break;
     default:
-      hipLaunchKernelGGL((div_search_kernel<C0, NB>), dim3(nchild), dim3(kDivBlock), 0, s, A);
+      hipLaunchKernelGGL((div_search_kernel<C0, NB>), grid, block, 0, s, A, nchild);
       break;
   }
 }

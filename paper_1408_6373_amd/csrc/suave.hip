@@ -86,45 +86,91 @@ __global__ void __launch_bounds__(256) suave_root_kernel(SuaveArgs A) {
   }
 }
 
-constexpr int kKeyBatch = 8;  // key loads issued together by the selection
+constexpr int kKeyRegs = 8;     // keys a thread of the selection holds in registers
+constexpr int kTopGroup = 64;   // boundary keys ranked directly
 
 // The K largest of R non-negative keys, ties to the lower position, in that
 // order (the regions of largest variance here, of largest spread in the
-// Divonne partition).
+// Divonne partition): 8-bit digits from the highest bit in which any two keys
+// differ, until at most 64 keys share the boundary digits (they rank
+// themselves) or all that do are taken; then a bitonic sort of the K winners.
+// One workgroup: latency.  Up to 8192 keys stay in registers over the passes.
+// 1024 of up to 8192 keys: 18.9 us on average, 24.3 with eight passes that
+// read the keys from memory each time; 64 of up to 1000: 10.8 from 14.8.
 __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, int K, int *sel) {
-  __shared__ unsigned hist[256];
+  __shared__ unsigned hist[2][256];
+  __shared__ unsigned long long wmax[16], wmin[16];
+  __shared__ unsigned long long s_prefix;
+  __shared__ int s_krem, s_group, s_take, s_ng;
   __shared__ int red[16];
-  __shared__ unsigned long long s_prefix, s_mask;
-  __shared__ int s_krem;
+  __shared__ unsigned long long gkey[kTopGroup];
+  __shared__ int gpos[kTopGroup];
   __shared__ unsigned long long skey[kSuaveMaxSplit];
   __shared__ int spos[kSuaveMaxSplit];
-  const int tid = threadIdx.x;
-  const int chunk = (R + 1023) / 1024;
-  const int b0 = min(tid * chunk, R), b1 = min(b0 + chunk, R);
-  if (tid == 0) {
-    s_prefix = 0;
-    s_mask = 0;
-    s_krem = K;
-  }
-  // radix select of the K-th largest key, 8 bits at a time from the top
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    const unsigned long long pre = s_prefix, mask = s_mask;
-    for (int i0 = b0; i0 < b1; i0 += kKeyBatch) {  // a batch of loads in flight
-      unsigned long long kk[kKeyBatch];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const bool inreg = R <= kKeyRegs * 1024;
+  unsigned long long kr[kKeyRegs];
 #pragma unroll
-      for (int q = 0; q < kKeyBatch; ++q) kk[q] = i0 + q < b1 ? var_key(key[i0 + q]) : 0;
+  for (int q = 0; q < kKeyRegs; ++q)
+    kr[q] = inreg && tid + 1024 * q < R ? var_key(key[tid + 1024 * q]) : 0;
+  // f(key, position) over the thread's keys
+  auto each = [&](auto f) {
+    if (inreg) {
 #pragma unroll
-      for (int q = 0; q < kKeyBatch; ++q)
-        if (i0 + q < b1 && (kk[q] & mask) == pre) atomicAdd(&hist[(kk[q] >> shift) & 255], 1u);
+      for (int q = 0; q < kKeyRegs; ++q)
+        if (tid + 1024 * q < R) f(kr[q], tid + 1024 * q);
+    } else {
+      for (int i0 = tid; i0 < R; i0 += 1024 * kKeyRegs) {
+        unsigned long long kk[kKeyRegs];
+#pragma unroll
+        for (int q = 0; q < kKeyRegs; ++q)
+          kk[q] = i0 + 1024 * q < R ? var_key(key[i0 + 1024 * q]) : 0;
+#pragma unroll
+        for (int q = 0; q < kKeyRegs; ++q)
+          if (i0 + 1024 * q < R) f(kk[q], i0 + 1024 * q);
+      }
     }
+  };
+  // the bits that all keys share need no pass
+  unsigned long long mx = 0, mn = ~0ull;
+  each([&](unsigned long long k, int) {
+    mx = max(mx, k);
+    mn = min(mn, k);
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    mx = max(mx, (unsigned long long)__shfl_xor((long long)mx, o, 64));
+    mn = min(mn, (unsigned long long)__shfl_xor((long long)mn, o, 64));
+  }
+  if (lane == 0) {
+    wmax[w] = mx;
+    wmin[w] = mn;
+  }
+  if (tid < 512) hist[tid >> 8][tid & 255] = 0;
+  if (tid == 0) {
+    s_take = 0;
+    s_ng = 0;
+  }
+  __syncthreads();
+  for (int q = 0; q < 16; ++q) {
+    mx = max(mx, wmax[q]);
+    mn = min(mn, wmin[q]);
+  }
+  const int top = mx == mn ? 0 : 64 - __clzll((long long)(mx ^ mn));  // bits that differ
+  int shift = max(0, (top + 7) / 8 * 8);
+  unsigned long long mask = shift >= 64 ? 0 : ~0ull << shift, pre = mx & mask;
+  int krem = K, group = R, par = 0;
+  while (shift > 0 && group > kTopGroup && group != krem) {
+    shift -= 8;
+    each([&](unsigned long long k, int) {
+      if ((k & mask) == pre) atomicAdd(&hist[par][(k >> shift) & 255], 1u);
+    });
     __syncthreads();
     if (tid < 64) {  // one wavefront: lane l owns digits 4l .. 4l+3
-      const int lane = tid;
-      const unsigned h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2],
-                     h3 = hist[4 * lane + 3];
-      const unsigned mine = h0 + h1 + h2 + h3;
+      unsigned hh[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) hh[q] = hist[par][4 * lane + q];
+      const unsigned mine = hh[0] + hh[1] + hh[2] + hh[3];
       // count of keys with a larger digit: the lanes above, inclusive scan downwards
       unsigned above = mine;
 #pragma unroll
@@ -132,63 +178,71 @@ __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, in
         const unsigned t = __shfl_down(above, o, 64);
         if (lane + o < 64) above += t;
       }
-      above -= mine;
-      const int krem = s_krem;
-      const unsigned hh[4] = {h0, h1, h2, h3};
-      unsigned cum = above;
+      unsigned cum = above - mine;
       for (int q = 3; q >= 0; --q) {
         if (cum < (unsigned)krem && (unsigned)krem <= cum + hh[q]) {
           s_krem = krem - (int)cum;
+          s_group = (int)hh[q];
           s_prefix = pre | ((unsigned long long)(4 * lane + q) << shift);
-          s_mask = mask | (255ull << shift);
         }
         cum += hh[q];
       }
+    } else if (tid >= 256 && tid < 512) {
+      hist[par ^ 1][tid - 256] = 0;  // (read last before the barrier above)
     }
     __syncthreads();
+    pre = s_prefix;
+    krem = s_krem;
+    group = s_group;
+    mask |= 255ull << shift;
+    par ^= 1;
   }
-  const unsigned long long T = s_prefix;
-  const int take_eq = s_krem;  // keys equal to T taken, the lowest positions first
-  int ngt = 0, neq = 0;
-  for (int i0 = b0; i0 < b1; i0 += kKeyBatch) {
-    unsigned long long kk[kKeyBatch];
-#pragma unroll
-    for (int q = 0; q < kKeyBatch; ++q) kk[q] = i0 + q < b1 ? var_key(key[i0 + q]) : 0;
-#pragma unroll
-    for (int q = 0; q < kKeyBatch; ++q)
-      if (i0 + q < b1) {
-        ngt += kk[q] > T;
-        neq += kk[q] == T;
-      }
-  }
-  int tot;
-  int gbase = block_scan_excl(ngt, red, &tot);
-  int ebase = block_scan_excl(neq, red, &tot);
-  for (int i0 = b0; i0 < b1; i0 += kKeyBatch) {
-    unsigned long long kk[kKeyBatch];
-#pragma unroll
-    for (int q = 0; q < kKeyBatch; ++q) kk[q] = i0 + q < b1 ? var_key(key[i0 + q]) : 0;
-    for (int q = 0; q < kKeyBatch && i0 + q < b1; ++q) {
-      const unsigned long long k = kk[q];
-      const int i = i0 + q;
-      if (k > T) {
-        skey[gbase] = k;
-        spos[gbase] = i;
-        ++gbase;
-      } else if (k == T) {
-        if (ebase < take_eq) {
-          skey[K - take_eq + ebase] = k;
-          spos[K - take_eq + ebase] = i;
-        }
-        ++ebase;
-      }
+  // above the boundary digits: all taken; within them: krem of the group
+  const bool all = group == krem;
+  each([&](unsigned long long k, int i) {
+    const unsigned long long b = k & mask;
+    if (b > pre || (all && b == pre)) {
+      const int o = atomicAdd(&s_take, 1);
+      skey[o] = k;
+      spos[o] = i;
+    } else if (b == pre && group <= kTopGroup) {
+      const int o = atomicAdd(&s_ng, 1);
+      gkey[o] = k;
+      gpos[o] = i;
     }
-  }
+  });
   int P = 1;
   while (P < K) P <<= 1;
   for (int i = K + tid; i < P; i += 1024) {
     skey[i] = 0;
     spos[i] = 0x7fffffff;
+  }
+  __syncthreads();
+  if (!all && group <= kTopGroup) {
+    if (tid < group) {
+      const unsigned long long mk = gkey[tid];
+      const int mp = gpos[tid];
+      int r = 0;
+      for (int q = 0; q < group; ++q) r += gkey[q] > mk || (gkey[q] == mk && gpos[q] < mp);
+      if (r < krem) {
+        skey[K - krem + r] = mk;
+        spos[K - krem + r] = mp;
+      }
+    }
+  } else if (!all) {  // every bit is fixed: equal keys, the lowest positions first
+    int base = 0;
+    for (int i0 = 0; i0 < R && base < krem; i0 += 1024) {
+      const int i = i0 + tid;
+      const unsigned long long k = i < R ? var_key(key[i]) : 0;
+      const int eq = i < R && (k & mask) == pre;
+      int tot;
+      const int o = base + block_scan_excl(eq, red, &tot);
+      if (eq && o < krem) {
+        skey[K - krem + o] = k;
+        spos[K - krem + o] = i;
+      }
+      base += tot;
+    }
   }
   __syncthreads();
   // bitonic sort: larger key first, then lower position
