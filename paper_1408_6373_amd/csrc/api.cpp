@@ -149,6 +149,21 @@ int pinned_block(ccuba_ctx *ctx, double **host, double **dev) {
   *dev = ctx->pinned_dev;
   return CCUBA_OK;
 }
+
+int poll_outcome(double *slot, unsigned long long seq, hipStream_t s) {
+  const volatile unsigned long long *word = host_word(slot);
+  const auto t0 = std::chrono::steady_clock::now();
+  for (unsigned spin = 0;; ++spin) {
+    const unsigned long long w = *word;
+    if ((w >> 8) == seq) return (int)(w & 0xFFull);
+    if ((spin & 4095u) == 4095u &&
+        std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
+      CCUBA_HIP(hipStreamSynchronize(s));
+      const unsigned long long w2 = *word;
+      return (w2 >> 8) == seq ? (int)(w2 & 0xFFull) : CCUBA_EHIP;
+    }
+  }
+}
 }  // namespace ccuba
 
 namespace {
@@ -235,7 +250,6 @@ int ccuba_init(ccuba_ctx **ctx, int device, size_t hbm_budget) {
   if (set_kernel_limits() != hipSuccess) return CCUBA_EHIP;
   // the allocation-free entry point's scratch: its address on this device
   if (noalloc_init(device) != CCUBA_OK) return CCUBA_EHIP;
-  if (suave_set_kernel_limits() != hipSuccess) return CCUBA_EHIP;
   if (cuhre_set_kernel_limits() != hipSuccess) return CCUBA_EHIP;
   for (int p = 0; p < 2; ++p) {
     c->tune[p].block = (int)env_ll("CCUBA_BLOCK", 256);

@@ -76,6 +76,18 @@ void pool_release(ccuba_ctx *ctx);
 // CCUBA_OK or CCUBA_EHIP.
 int pinned_block(ccuba_ctx *ctx, double **host, double **dev);
 
+// The word a kernel writes its outcome to, seq << 8 | code, in mapped pinned
+// memory (a slot of doubles).
+inline volatile unsigned long long *host_word(double *slot) {
+  return (volatile unsigned long long *)slot;
+}
+// Wait for state seq's outcome in the word at `slot': its code, or a negative
+// status.  Polled: a blocking wait adds a wake-up of ~10 us to every step,
+// longer than a small step's work, and an event recorded per step costs the
+// device ~5 us (a system-scope release).  If the word does not come within a
+// second, the stream is drained and it is read once more.
+int poll_outcome(double *slot, unsigned long long seq, hipStream_t s);
+
 // A typed device buffer that returns its bytes to the context on release.
 template <typename T>
 struct DevBuf {

@@ -11,7 +11,6 @@
 #include "cuhre_engine.h"
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <vector>
 
@@ -401,28 +400,10 @@ int CuhreRun::run(hipStream_t s) {
     dev_slots = (double *)d;
   }
   auto slot = [&](int t) { return 4 * (t % kSlots); };
-  auto word = [&](int t) {
-    return (volatile unsigned long long *)(host_slots + slot(t) + 2);
-  };
-  for (int q = 0; q < kSlots; ++q) *word(q) = ~0ull;  // no state's word
-  // the outcome of state t: 0 go on, 1 converged, 2 not finite.  Polled: a
-  // blocking wait adds a wake-up of ~10 us to every step, longer than a
-  // small step's work, and an event recorded per step costs the device ~5 us
-  // (a system-scope release).  If the word does not come within a second,
-  // the stream is drained and it is read once more.
-  auto outcome = [&](int t) -> int {
-    const unsigned long long want = (unsigned long long)t;
-    auto t0 = std::chrono::steady_clock::now();
-    for (unsigned spin = 0;; ++spin) {
-      const unsigned long long w = *word(t);
-      if ((w >> 8) == want) return (int)(w & 0xFFull);
-      if ((spin & 4095u) == 4095u &&
-          std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
-        CCUBA_HIP(hipStreamSynchronize(s));
-        const unsigned long long w2 = *word(t);
-        return (w2 >> 8) == want ? (int)(w2 & 0xFFull) : CCUBA_EHIP;
-      }
-    }
+  for (int q = 0; q < kSlots; ++q) *host_word(host_slots + slot(q) + 2) = ~0ull;  // no state's
+  // the outcome of state t: 0 go on, 1 converged, 2 not finite
+  auto outcome = [&](int t) {
+    return poll_outcome(host_slots + slot(t) + 2, (unsigned long long)t, s);
   };
   // finish with state q, whose outcome (code) ended the run
   auto finish = [&](const Plan &p, int q, int code) -> int {

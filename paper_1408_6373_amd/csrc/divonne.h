@@ -34,12 +34,20 @@ struct DivArgs {
   int *sel;               // [K] selected positions
   int *chpos, *chser;     // [2K] children's positions and search serials
   int *cut;               // [splits] dimension of every split, in order
+};
+
+// The stop rule of one state: its totals go to `state', the outcome to `word'
+// (both mapped host memory).
+struct DStop {
+  double spread_tol;
+  unsigned long long seq;
   DState *state;
+  unsigned long long *word;
 };
 
 hipError_t launch_div_root(const DivArgs &A, hipStream_t s);
 hipError_t launch_div_search(const DivArgs &A, int nchild, hipStream_t s);
 hipError_t launch_div_split(const DivArgs &A, int R, long long Q, int K, hipStream_t s);
-hipError_t launch_div_totals(const DivArgs &A, int R, hipStream_t s);
+hipError_t launch_div_totals(const DivArgs &A, int R, const DStop &stop, hipStream_t s);
 
 }  // namespace ccuba

@@ -13,7 +13,8 @@
 //           move is taken when the best candidate (ties to the lower c) beats
 //           the current value, else every step halves
 //   totals  the largest and the total spread over all regions (fixed order)
-// The host reads the totals after each step and sizes the next.
+// The selection changes no region, so the host learns a step's outcome while
+// the next one's runs.
 #include "divonne.h"
 #include "genz.h"
 #include "philox.h"
@@ -308,8 +309,10 @@ __global__ void __launch_bounds__(64) div_split_kernel(DivArgs A, int R, long lo
   }
 }
 
-// The largest and the total spread over the R regions (fixed order).
-__global__ void __launch_bounds__(1024) div_totals_kernel(DivArgs A, int R) {
+// The largest and the total spread over the R regions (fixed order), and the
+// stop rule's outcome as one word, seq << 8 | code, that the host polls (code
+// 0: go on, 1: every spread within spread_tol, 2: not finite).
+__global__ void __launch_bounds__(1024) div_totals_kernel(DivArgs A, int R, DStop stop) {
   __shared__ double rs[16], rm[16];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int chunk = (R + 1023) / 1024;
@@ -336,8 +339,11 @@ __global__ void __launch_bounds__(1024) div_totals_kernel(DivArgs A, int R) {
       S += rs[q];
       M = fmax(M, rm[q]);
     }
-    A.state->max_spread = M;
-    A.state->total_spread = S;
+    stop.state->max_spread = M;
+    stop.state->total_spread = S;
+    const unsigned long long code = !isfinite(S) ? 2u : M <= stop.spread_tol ? 1u : 0u;
+    __hip_atomic_store(stop.word, (stop.seq << 8) | code, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -415,8 +421,8 @@ hipError_t launch_div_split(const DivArgs &A, int R, long long Q, int K, hipStre
 
 #undef CCUBA_DIV_FAMILY_SWITCH
 
-hipError_t launch_div_totals(const DivArgs &A, int R, hipStream_t s) {
-  hipLaunchKernelGGL(div_totals_kernel, dim3(1), dim3(1024), 0, s, A, R);
+hipError_t launch_div_totals(const DivArgs &A, int R, const DStop &stop, hipStream_t s) {
+  hipLaunchKernelGGL(div_totals_kernel, dim3(1), dim3(1024), 0, s, A, R, stop);
   return hipGetLastError();
 }
 

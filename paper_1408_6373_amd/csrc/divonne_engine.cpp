@@ -1,8 +1,9 @@
 // divonne_engine.cpp -- host driver of Divonne's partitioning phase (Sect. 2.2;
 // the steps are those listed in divonne.hip).  The regions, their extrema and
-// spreads stay on the device; after each step the host reads the largest and
-// the total spread (16 bytes) and sizes the next step:
-// K = min(nsplit, regions, maxregions - regions).
+// spreads stay on the device.  A step's size is K = min(nsplit, regions,
+// maxregions - regions); only the end of the phase depends on the spreads, and
+// the next step's selection, which changes no region, is queued before the
+// host has learned that the phase goes on.
 #include "divonne_engine.h"
 
 #include <algorithm>
@@ -70,37 +71,43 @@ int run_partition(ccuba_ctx *ctx, const PartitionSpec &sp, PartitionResult &res,
   A.chpos = chpos.p;
   A.chser = chser.p;
   A.cut = cut.p;
-  A.state = (DState *)pin_dev;
   const long long per_search = sp.nsearch + 4ll * d * sp.niter;
 
+  // state t's totals and outcome go to slot t % 2 of the pinned block
+  constexpr int kSlot = 4, kWord = 2;  // doubles of a slot; its word's place
+  for (int q = 0; q < 2; ++q) *host_word(pin_host + kSlot * q + kWord) = ~0ull;
+  long long R = 1, Q = 0, neval = per_search;
+  auto totals = [&](long long t) {
+    double *slot = pin_dev + kSlot * (t % 2);
+    return launch_div_totals(A, (int)R,
+                             DStop{sp.spread_tol, (unsigned long long)t, (DState *)slot,
+                                   (unsigned long long *)(slot + kWord)},
+                             s);
+  };
   CCUBA_HIP(launch_div_root(A, s));
   CCUBA_HIP(launch_div_search(A, 1, s));
-  CCUBA_HIP(launch_div_totals(A, 1, s));
-  long long R = 1, Q = 0, neval = per_search;
-  DState st{};
+  CCUBA_HIP(totals(0));
   int fail = 1;
-  for (;;) {
-    CCUBA_HIP(hipStreamSynchronize(s));
-    std::memcpy(&st, pin_host, sizeof(st));
-    if (!std::isfinite(st.total_spread)) {  // a non-finite integrand value
-      fail = -4;
-      st = DState{};
-      break;
-    }
-    if (st.max_spread <= sp.spread_tol) {
-      fail = 0;
-      break;
-    }
+  long long t = 0;
+  for (;; ++t) {
     const long long K = std::min<long long>({(long long)sp.nsplit, R, Rmax - R});
-    if (K <= 0) break;
-    CCUBA_HIP(launch_topk(spread.p, (int)R, (int)K, sel.p, s));
+    if (K > 0) CCUBA_HIP(launch_topk(spread.p, (int)R, (int)K, sel.p, s));
+    const int code = poll_outcome(pin_host + kSlot * (t % 2) + kWord, (unsigned long long)t, s);
+    if (code < 0) return code;
+    if (code || K <= 0) {
+      fail = code == 2 ? -4 : code == 1 ? 0 : 1;
+      break;
+    }
     CCUBA_HIP(launch_div_split(A, (int)R, Q, (int)K, s));
     CCUBA_HIP(launch_div_search(A, (int)(2 * K), s));
     R += K;
     Q += K;
     neval += K * (2 * per_search + d);
-    CCUBA_HIP(launch_div_totals(A, (int)R, s));
+    CCUBA_HIP(totals(t + 1));
   }
+  CCUBA_HIP(hipStreamSynchronize(s));
+  DState st{};
+  if (fail != -4) std::memcpy(&st, pin_host + kSlot * (t % 2), sizeof(st));
   res.nregions = (int)R;
   res.fail = fail;
   res.neval = neval;

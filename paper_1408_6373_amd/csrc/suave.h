@@ -16,8 +16,9 @@ namespace ccuba {
 
 constexpr int kSuaveMaxSplit = 1024;  // regions split per step at most
 constexpr int kSuaveBlock = 256;      // threads of the sampling workgroups
-constexpr int kSuaveTile = 4096;      // points per sampling workgroup
-constexpr int kSuaveChunk = 4096;     // sample points per split-statistics workgroup
+
+// Sample points per sampling workgroup (tile) and per split-statistics
+// workgroup (chunk).
 
 // The regions of one integral in position order (device arrays).
 struct SRegions {
@@ -41,8 +42,8 @@ struct SuaveArgs {
   int d, N, family, flags;
   long long nnew;
   uint32_t key0, key1, sid;
-  int ntiles;             // sampling tiles per child
-  int nchunks;            // split-statistics chunks per region
+  int tile, ntiles;       // points of a sampling tile; tiles per child
+  int chunk, nchunks;     // points of a split-statistics chunk; chunks per region
   double flatness;
   int ipow;               // flatness when it is a whole number in [1, 4096], else 0
   int pad;
@@ -55,12 +56,20 @@ struct SuaveArgs {
   double *tsum;           // [2K][ntiles][2] tile sums
   double *thist;          // [2K][ntiles][d N] tile histograms
   int *cut;               // [splits] dimension of every split, in order
+};
+
+// The stop rule of one state: its totals go to `state', the outcome to `word'
+// (both mapped host memory); `last': no step can follow this state.
+struct SStop {
+  double epsrel, epsabs;
+  long long mineval, neval;
+  unsigned long long seq;
   SState *state;
+  unsigned long long *word;
+  int last, pad;
 };
 
 size_t suave_sample_lds(int d, int N);
-size_t suave_fold_lds(int d, int N);
-hipError_t suave_set_kernel_limits();
 // the root region [0,1]^d with the uniform grid, to be sampled as child 0
 hipError_t launch_suave_root(const SuaveArgs &A, hipStream_t s);
 hipError_t launch_suave_select(const SuaveArgs &A, int R, int K, hipStream_t s);
@@ -71,6 +80,6 @@ hipError_t launch_suave_fluct(const SuaveArgs &A, int K, hipStream_t s);
 hipError_t launch_suave_split(const SuaveArgs &A, int R, long long Q, int K, hipStream_t s);
 hipError_t launch_suave_sample(const SuaveArgs &A, int nchild, hipStream_t s);
 hipError_t launch_suave_fold(const SuaveArgs &A, int nchild, hipStream_t s);
-hipError_t launch_suave_totals(const SuaveArgs &A, int R, hipStream_t s);
+hipError_t launch_suave_totals(const SuaveArgs &A, int R, const SStop &stop, hipStream_t s);
 
 }  // namespace ccuba

@@ -15,11 +15,13 @@
 //   sample  DoSample of every child: nnew Philox points through the child's
 //           grid (cells staged in LDS), the integrand, v = w V f, the stored
 //           (v, side bits) and per-tile sums and v^2 histograms
-//   fold    per child: tile sums in tile order, the child's own estimate, its
-//           inverse-variance combination with the inherited one, and the
-//           refinement of the child's grid (one wavefront per dimension)
-//   totals  sums over all regions and the chi^2 probability; one workgroup
-// The host reads the totals after each step and sizes the next one.
+//   fold    per (child, dimension): the refinement of that dimension of the
+//           child's grid; once per child the tile sums in tile order, its own
+//           estimate and the inverse-variance combination with the inherited one
+//   totals  sums over all regions, the stop rule and, at the end, the chi^2
+//           probability; one workgroup
+// Steps are queued ahead of their totals: select and fluct change no region,
+// so the host learns a step's outcome while the next step's run.
 #include "engine.h"
 #include "genz.h"
 #include "philox.h"
@@ -269,225 +271,315 @@ __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, in
 }
 
 // Split statistics in two passes over each selected region's sample, both
-// spread over chunks of kSuaveChunk points (grid: chunk x dimension group x
-// region):
+// spread over chunks of A.chunk points (grid: chunk x region):
 //   pass 1, per (dimension, half): count, S1 = sum v, S2 = sum v^2, min v and
 //           max v; the largest deviation from the half's mean m_h is then
 //           exactly M_h = max(vmax - m_h, m_h - vmin);
 //   pass 2, per (dimension, half): sum (|v - m_h| / M_h)^p.
-// Chunk partials are reduced in chunk order wherever they are needed.
-constexpr int kP1 = 9;       // per (chunk, dimension): cnt1, S1_0, S2_0, S1_1, S2_1, min0, max0, min1, max1
+// Chunk partials are reduced in a fixed order wherever they are needed.
+//
+// Both passes are bound by VALU issue (14 and 17 instructions per point and
+// dimension at p = 25).  A thread keeps the partial sums of kFlDims dimensions
+// in registers and reads its points from memory, so no point passes through
+// LDS; a workgroup's dimension groups read the same points at about the same
+// time.  The half of a point enters as a bit mask: factors 0.0 and 1.0 of
+// fused multiply-adds, and quiet NaNs, which minimum and maximum pass over.
+// 64 regions of 2^17 points, d = 8, p = 25: 30 and 45 us a launch, against 59 and
+// 66 (and 7 for a reduction launch between them) with the chunks staged in LDS
+// and a thread per (dimension, point).
+constexpr int kP1 = 9;         // per (chunk, dimension): cnt1, S1_0, S2_0, S1_1, S2_1, min0, max0, min1, max1
+constexpr int kHs = 10;        // per (region, dimension): cnt, S1, S2, m, M of each half
+constexpr int kFlDims = 4;     // dimensions of a thread
+constexpr int kFlThreads = 128;  // threads that share a dimension group
+constexpr int kFlGroups = kMaxDim / kFlDims;
+constexpr int kFlItems = kFlDims * kP1;  // pass-1 values of a dimension group
 
-// Both passes stage their chunk in LDS once; then G threads per dimension
-// (G = kFlBlock over d rounded up to a power of two, at most 64) accumulate over
-// it, two points at a time into independent partial sums, and reduce with
-// shuffles within their G-lane group.
-constexpr int kFlBlock = 512;  // threads of the split-statistics workgroups
-static_assert(kSuaveChunk % kFlBlock == 0, "a chunk stages evenly over the workgroup");
+namespace {
 
-__device__ __forceinline__ int lanes_per_dim(int d) {
-  int dp = 1;
-  while (dp < d) dp <<= 1;
-  return min(64, kFlBlock / dp);
+// a double made of a high word (0.0 and 1.0 have a zero low word)
+__device__ __forceinline__ double hi_double(uint32_t hi) {
+  return __longlong_as_double((long long)((unsigned long long)hi << 32));
 }
 
-__device__ __forceinline__ int stage_chunk(const double *vall, const uint16_t *sall, int pos,
-                                           long long n, int ch, double *sv, uint16_t *sb) {
-  const long long i0 = (long long)ch * kSuaveChunk;
-  const int cnt = (int)min((long long)kSuaveChunk, n - i0);
-  const double *v = vall + (size_t)pos * n + i0;
-  const uint16_t *sd = sall + (size_t)pos * n + i0;
-  // all of a thread's loads in flight at once (kSuaveChunk / kFlBlock each)
-  constexpr int kPer = kSuaveChunk / kFlBlock;
-  double tv[kPer];
-  uint16_t tb[kPer];
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int i = threadIdx.x + kFlBlock * k;
-    tv[k] = i < cnt ? v[i] : 0.0;
-    tb[k] = i < cnt ? sd[i] : (uint16_t)0;
-  }
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    sv[threadIdx.x + kFlBlock * k] = tv[k];
-    sb[threadIdx.x + kFlBlock * k] = tb[k];
-  }
-  __syncthreads();
-  return cnt;
+// v_min_f64 / v_max_f64 as they are: of a number and a quiet NaN, the number
+__device__ __forceinline__ double min_num(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double max_num(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
 }
 
-// pass-1 partial sums: cnt1, S1_0, S2_0, S1_1, S2_1, min0, max0, min1, max1
-__device__ __forceinline__ void p1_init(double (&a)[kP1]) {
-#pragma unroll
-  for (int q = 0; q < 5; ++q) a[q] = 0.0;
-  a[5] = a[7] = INFINITY;
-  a[6] = a[8] = -INFINITY;
+// A reduction over the wavefront by DPP, its result in lane 63: the row
+// shifts leave each row's result in its lane 15, the row broadcasts carry it
+// on.  A lane without a source takes the identity.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or(double v, double identity) {
+  const long long b = __double_as_longlong(v), z = __double_as_longlong(identity);
+  const int lo = __builtin_amdgcn_update_dpp((int)z, (int)b, CTRL, ROWS, 0xf, false);
+  const int hi =
+      __builtin_amdgcn_update_dpp((int)(z >> 32), (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
-__device__ __forceinline__ void p1_add(double (&a)[kP1], double x, bool up) {
-  // branch-free (a branch here sends both partials to scratch); adding 0.0
-  // to the other half's sums leaves them unchanged
-  const double xu = up ? x : 0.0, xl = up ? 0.0 : x;
-  a[0] += up ? 1.0 : 0.0;
-  a[1] += xl;
-  a[2] += xl * xl;
-  a[3] += xu;
-  a[4] += xu * xu;
-  a[5] = up ? a[5] : fmin(a[5], x);
-  a[6] = up ? a[6] : fmax(a[6], x);
-  a[7] = up ? fmin(a[7], x) : a[7];
-  a[8] = up ? fmax(a[8], x) : a[8];
+template <typename OP>
+__device__ __forceinline__ double wave_reduce63(double v, double identity, OP op) {
+  v = op(v, dpp_or<0x111, 0xf>(v, identity));  // row_shr:1
+  v = op(v, dpp_or<0x112, 0xf>(v, identity));  // row_shr:2
+  v = op(v, dpp_or<0x114, 0xf>(v, identity));  // row_shr:4
+  v = op(v, dpp_or<0x118, 0xf>(v, identity));  // row_shr:8
+  v = op(v, dpp_or<0x142, 0xa>(v, identity));  // row_bcast:15 into rows 1 and 3
+  v = op(v, dpp_or<0x143, 0xc>(v, identity));  // row_bcast:31 into rows 2 and 3
+  return v;
 }
+__device__ __forceinline__ double wave_reduce63_sum(double v) {
+  return wave_reduce63(v, 0.0, [](double a, double b) { return a + b; });
+}
+
 __device__ __forceinline__ double p1_merge(int q, double x, double y) {
   return (q == 5 || q == 7) ? fmin(x, y) : (q == 6 || q == 8) ? fmax(x, y) : x + y;
 }
+__device__ __forceinline__ double p1_identity(int q) {
+  return (q == 5 || q == 7) ? INFINITY : (q == 6 || q == 8) ? -INFINITY : 0.0;
+}
+
+// U points (stride kFlThreads) of a thread at a time, f(x, bits of its
+// dimension group) for each of its points
+template <int U, typename F>
+__device__ __forceinline__ void each_points(const double *v, const uint16_t *sd, int cnt, int g,
+                                            F f) {
+  int i = threadIdx.x & (kFlThreads - 1);
+  for (; i + (U - 1) * kFlThreads < cnt; i += U * kFlThreads) {
+    double x[U];
+    uint32_t b[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      x[q] = v[i + q * kFlThreads];
+      b[q] = (uint32_t)sd[i + q * kFlThreads] >> (kFlDims * g);
+    }
+    f(x, b);
+  }
+  for (; i < cnt; i += kFlThreads) {  // (x and bits of a missing point: see the callers)
+    double x[U];
+    uint32_t b[U];
+    x[0] = v[i];
+    b[0] = (uint32_t)sd[i] >> (kFlDims * g);
+    f(x, b, 1);
+  }
+}
+
+// -1 if bit q of b is set, else 0
+__device__ __forceinline__ uint32_t bit_mask(uint32_t b, int q) {
+  return (uint32_t)((int)(b << (31 - q)) >> 31);
+}
+
+}  // namespace
 
 // Pass 1 over one chunk: grid (chunk, selected region).
-__global__ void __launch_bounds__(kFlBlock) suave_fluct1_kernel(SuaveArgs A) {
-  __shared__ double sv[kSuaveChunk];
-  __shared__ uint16_t sb[kSuaveChunk];
+__global__ void __launch_bounds__(kFlThreads *kFlGroups) suave_fluct1_kernel(SuaveArgs A) {
+  __shared__ double red[kFlGroups][2][kFlItems];
   const int ch = blockIdx.x, s = blockIdx.y, tid = threadIdx.x, d = A.d;
-  const int cnt = stage_chunk(A.R.v, A.R.side, A.sel[s], A.nnew, ch, sv, sb);
-  const int G = lanes_per_dim(d);
-  const int j = tid / G, sub = tid % G;
-  if (j >= d) return;
-  double x0[kP1], x1[kP1];
-  p1_init(x0);
-  p1_init(x1);
-  int i = sub;
-  for (; i + G < cnt; i += 2 * G) {
-    p1_add(x0, sv[i], (sb[i] >> j) & 1u);
-    p1_add(x1, sv[i + G], (sb[i + G] >> j) & 1u);
-  }
-  if (i < cnt) p1_add(x0, sv[i], (sb[i] >> j) & 1u);
+  const int g = __builtin_amdgcn_readfirstlane(tid / kFlThreads), t = tid % kFlThreads;
+  const long long i0 = (long long)ch * A.chunk;
+  const int cnt = (int)min((long long)A.chunk, A.nnew - i0);
+  const size_t at = (size_t)A.sel[s] * A.nnew + i0;
+  double s1l[kFlDims], s2l[kFlDims], s1u[kFlDims], s2u[kFlDims];
+  double mnl[kFlDims], mxl[kFlDims], mnu[kFlDims], mxu[kFlDims];
+  uint32_t cu[kFlDims];
 #pragma unroll
-  for (int q = 0; q < kP1; ++q) {
-    double r = p1_merge(q, x0[q], x1[q]);
-    for (int o = G >> 1; o > 0; o >>= 1) r = p1_merge(q, r, __shfl_xor(r, o, G));
-    x0[q] = r;
+  for (int q = 0; q < kFlDims; ++q) {
+    s1l[q] = s2l[q] = s1u[q] = s2u[q] = 0.0;
+    mnl[q] = mnu[q] = INFINITY;
+    mxl[q] = mxu[q] = -INFINITY;
+    cu[q] = 0;
   }
-  if (sub == 0) {
-    double *r = A.fl1 + (((size_t)s * A.nchunks + ch) * d + j) * kP1;
+  constexpr int U = 4;
+  each_points<U>(A.R.v + at, A.R.side + at, cnt, g,
+                 [&](const double (&x)[U], const uint32_t (&b)[U], int m = U) {
 #pragma unroll
-    for (int q = 0; q < kP1; ++q) r[q] = x0[q];
-  }
-}
-
-namespace {
-
-// pass 1 of (region s, dimension j) over all chunks, in chunk order
-struct HalfStats {
-  double cnt[2], S1[2], S2[2], m[2], M[2];
-};
-__device__ HalfStats half_stats(const SuaveArgs &A, int s, int j) {
-  double c1 = 0.0, a0 = 0.0, q0 = 0.0, a1 = 0.0, q1 = 0.0;
-  double mn0 = INFINITY, mx0 = -INFINITY, mn1 = INFINITY, mx1 = -INFINITY;
-#pragma unroll 8
-  for (int ch = 0; ch < A.nchunks; ++ch) {
-    const double *r = A.fl1 + (((size_t)s * A.nchunks + ch) * A.d + j) * kP1;
-    c1 += r[0];
-    a0 += r[1];
-    q0 += r[2];
-    a1 += r[3];
-    q1 += r[4];
-    mn0 = fmin(mn0, r[5]);
-    mx0 = fmax(mx0, r[6]);
-    mn1 = fmin(mn1, r[7]);
-    mx1 = fmax(mx1, r[8]);
-  }
-  HalfStats h;
-  h.cnt[0] = (double)A.nnew - c1;
-  h.cnt[1] = c1;
-  h.S1[0] = a0;
-  h.S2[0] = q0;
-  h.S1[1] = a1;
-  h.S2[1] = q1;
-  h.m[0] = h.cnt[0] > 0.0 ? a0 / h.cnt[0] : 0.0;
-  h.m[1] = c1 > 0.0 ? a1 / c1 : 0.0;
-  h.M[0] = h.cnt[0] > 0.0 ? fmax(mx0 - h.m[0], h.m[0] - mn0) : 0.0;
-  h.M[1] = c1 > 0.0 ? fmax(mx1 - h.m[1], h.m[1] - mn1) : 0.0;
-  return h;
-}
-
-}  // namespace
-
-namespace {
-
-// r^p for r in [0, 1] (0^p = 0): by squaring for a whole p
-__device__ __forceinline__ double pow01(double r, double p, int ip) {
-  if (ip > 0) {
-    double t = 1.0, b = r;
-    for (int e = ip; e; e >>= 1) {
-      if (e & 1) t *= b;
-      b *= b;
+    for (int p = 0; p < U; ++p) {
+      if (p >= m) break;
+      const double xx = x[p] * x[p];
+      const unsigned long long xb = (unsigned long long)__double_as_longlong(x[p]);
+      const uint32_t xh = (uint32_t)(xb >> 32);
+#pragma unroll
+      for (int q = 0; q < kFlDims; ++q) {
+        const uint32_t up = bit_mask(b[p], q);
+        const double fu = hi_double(up & 0x3FF00000u), fl = hi_double(~up & 0x3FF00000u);
+        s1l[q] = fma(fl, x[p], s1l[q]);
+        s2l[q] = fma(fl, xx, s2l[q]);
+        s1u[q] = fma(fu, x[p], s1u[q]);
+        s2u[q] = fma(fu, xx, s2u[q]);
+        cu[q] -= up;
+        const unsigned long long lo = xb & 0xFFFFFFFFull;
+        const double xl = __longlong_as_double(
+            (long long)(((unsigned long long)(xh | (up & 0x7FF80000u)) << 32) | lo));
+        const double xu = __longlong_as_double(
+            (long long)(((unsigned long long)(xh | (~up & 0x7FF80000u)) << 32) | lo));
+        mnl[q] = min_num(mnl[q], xl);
+        mxl[q] = max_num(mxl[q], xl);
+        mnu[q] = min_num(mnu[q], xu);
+        mxu[q] = max_num(mxu[q], xu);
+      }
     }
-    return t;
+  });
+  auto mn = [](double a, double b) { return min_num(a, b); };
+  auto mx = [](double a, double b) { return max_num(a, b); };
+  const int w = (tid >> 6) & 1;
+#pragma unroll
+  for (int q = 0; q < kFlDims; ++q) {
+    const double r[kP1] = {wave_reduce63_sum((double)cu[q]), wave_reduce63_sum(s1l[q]),
+                           wave_reduce63_sum(s2l[q]),        wave_reduce63_sum(s1u[q]),
+                           wave_reduce63_sum(s2u[q]),        wave_reduce63(mnl[q], INFINITY, mn),
+                           wave_reduce63(mxl[q], -INFINITY, mx),
+                           wave_reduce63(mnu[q], INFINITY, mn),
+                           wave_reduce63(mxu[q], -INFINITY, mx)};
+    if ((tid & 63) == 63)
+#pragma unroll
+      for (int k = 0; k < kP1; ++k) red[g][w][q * kP1 + k] = r[k];
   }
-  return r > 0.0 ? exp2(p * log2(r)) : 0.0;
+  __syncthreads();
+  const int j = kFlDims * g + t / kP1;
+  if (t < kFlItems && j < d)
+    A.fl1[(((size_t)s * A.nchunks + ch) * d + j) * kP1 + t % kP1] =
+        p1_merge(t % kP1, red[g][0][t], red[g][1][t]);
 }
 
-}  // namespace
+// Pass 2 over one chunk: grid (chunk, selected region).  Each workgroup first
+// reduces pass 1 over the chunks (kFlSegs threads a value); chunk 0's writes
+// the halves' statistics for the split.
+constexpr int kFlSegs = kFlThreads / kFlItems;
 
-// Pass 1 reduced over the chunks, once per (selected region, dimension):
-// grid (selected region), lane j < d.
-constexpr int kHs = 10;  // per (region, dimension): cnt, S1, S2, m, M of each half
-__global__ void __launch_bounds__(64) suave_fluct_reduce_kernel(SuaveArgs A) {
-  const int s = blockIdx.x, j = threadIdx.x;
-  if (j >= A.d) return;
-  const HalfStats h = half_stats(A, s, j);
-  double *o = A.hs + ((size_t)s * A.d + j) * kHs;
-  for (int k = 0; k < 2; ++k) {
-    o[5 * k + 0] = h.cnt[k];
-    o[5 * k + 1] = h.S1[k];
-    o[5 * k + 2] = h.S2[k];
-    o[5 * k + 3] = h.m[k];
-    o[5 * k + 4] = h.M[k];
-  }
-}
-
-// Pass 2 over one chunk: grid (chunk, selected region).
-__global__ void __launch_bounds__(kFlBlock) suave_fluct2_kernel(SuaveArgs A) {
-  __shared__ double sv[kSuaveChunk];
-  __shared__ uint16_t sb[kSuaveChunk];
+__global__ void __launch_bounds__(kFlThreads *kFlGroups) suave_fluct2_kernel(SuaveArgs A) {
+  __shared__ double part[kFlGroups][kFlSegs][kFlItems];
   __shared__ double sm[kMaxDim][2], sinv[kMaxDim][2];
+  __shared__ double red[kFlGroups][2][2 * kFlDims];
   const int ch = blockIdx.x, s = blockIdx.y, tid = threadIdx.x, d = A.d;
-  if (tid < d) {
-    const double *h = A.hs + ((size_t)s * d + tid) * kHs;
-    for (int k = 0; k < 2; ++k) {
-      sm[tid][k] = h[5 * k + 3];
-      sinv[tid][k] = h[5 * k + 4] > 0.0 ? 1.0 / h[5 * k + 4] : 0.0;
+  const int g = __builtin_amdgcn_readfirstlane(tid / kFlThreads), t = tid % kFlThreads;
+  {
+    const int seg = t / kFlItems, item = t - seg * kFlItems;
+    const int j = kFlDims * g + item / kP1, q = item % kP1;
+    if (seg < kFlSegs && j < d) {
+      double a = p1_identity(q);
+      const double *r = A.fl1 + ((size_t)s * A.nchunks * d + j) * kP1 + q;
+#pragma unroll 8
+      for (int c = seg; c < A.nchunks; c += kFlSegs) a = p1_merge(q, a, r[(size_t)c * d * kP1]);
+      part[g][seg][item] = a;
     }
   }
-  const int cnt = stage_chunk(A.R.v, A.R.side, A.sel[s], A.nnew, ch, sv, sb);
-  const int G = lanes_per_dim(d);
-  const int j = tid / G, sub = tid % G;
-  if (j >= d) return;
+  __syncthreads();
+  if (t < kFlDims && kFlDims * g + t < d) {
+    const int j = kFlDims * g + t;
+    double x[kP1];
+#pragma unroll
+    for (int q = 0; q < kP1; ++q) {
+      x[q] = part[g][0][t * kP1 + q];
+#pragma unroll
+      for (int k = 1; k < kFlSegs; ++k) x[q] = p1_merge(q, x[q], part[g][k][t * kP1 + q]);
+    }
+    const double cnt[2] = {(double)A.nnew - x[0], x[0]};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const double S1 = x[1 + 2 * k], mn = x[5 + 2 * k], mx = x[6 + 2 * k];
+      const double m = cnt[k] > 0.0 ? S1 / cnt[k] : 0.0;
+      const double M = cnt[k] > 0.0 ? fmax(mx - m, m - mn) : 0.0;
+      sm[j][k] = m;
+      sinv[j][k] = M > 0.0 ? 1.0 / M : 0.0;
+      if (ch == 0) {
+        double *o = A.hs + ((size_t)s * d + j) * kHs + 5 * k;
+        o[0] = cnt[k];
+        o[1] = S1;
+        o[2] = x[2 + 2 * k];
+        o[3] = m;
+        o[4] = M;
+      }
+    }
+  }
+  __syncthreads();
+  double m0[kFlDims], m1[kFlDims], i0v[kFlDims], i1v[kFlDims], ql[kFlDims], qu[kFlDims];
+#pragma unroll
+  for (int q = 0; q < kFlDims; ++q) {
+    const int j = kFlDims * g + q;
+    m0[q] = j < d ? sm[j][0] : 0.0;
+    m1[q] = j < d ? sm[j][1] : 0.0;
+    i0v[q] = j < d ? sinv[j][0] : 0.0;
+    i1v[q] = j < d ? sinv[j][1] : 0.0;
+    ql[q] = qu[q] = 0.0;
+  }
   const double p = A.flatness;
   const int ip = A.ipow;
-  const double m0 = sm[j][0], m1 = sm[j][1], i0v = sinv[j][0], i1v = sinv[j][1];
-  double q00 = 0.0, q01 = 0.0, q10 = 0.0, q11 = 0.0;  // [partial][half]
-  int i = sub;
-  for (; i + G < cnt; i += 2 * G) {
-    const bool ua = (sb[i] >> j) & 1u, ub = (sb[i + G] >> j) & 1u;
-    const double ta = pow01(fabs(sv[i] - (ua ? m1 : m0)) * (ua ? i1v : i0v), p, ip);
-    const double tb = pow01(fabs(sv[i + G] - (ub ? m1 : m0)) * (ub ? i1v : i0v), p, ip);
-    if (ua) q01 += ta; else q00 += ta;
-    if (ub) q11 += tb; else q10 += tb;
+  const long long i0 = (long long)ch * A.chunk;
+  const int cnt = (int)min((long long)A.chunk, A.nnew - i0);
+  const size_t at = (size_t)A.sel[s] * A.nnew + i0;
+  constexpr int U = 4;
+  each_points<U>(A.R.v + at, A.R.side + at, cnt, g,
+                 [&](const double (&x)[U], const uint32_t (&b)[U], int m = U) {
+    double r[U][kFlDims], y[U][kFlDims];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (k < m)
+#pragma unroll
+        for (int q = 0; q < kFlDims; ++q) {
+          const bool up = (b[k] >> q) & 1u;
+          r[k][q] = fabs(x[k] - (up ? m1[q] : m0[q])) * (up ? i1v[q] : i0v[q]);
+        }
+      else
+#pragma unroll
+        for (int q = 0; q < kFlDims; ++q) r[k][q] = 0.0;
+    if (ip > 0) {  // r^p by squaring, from the lowest bit of p; every value together
+      int e = ip;
+      for (; !(e & 1); e >>= 1)
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int q = 0; q < kFlDims; ++q) r[k][q] *= r[k][q];
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int q = 0; q < kFlDims; ++q) y[k][q] = r[k][q];
+      for (e >>= 1; e; e >>= 1) {
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int q = 0; q < kFlDims; ++q) r[k][q] *= r[k][q];
+        if (e & 1)
+#pragma unroll
+          for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int q = 0; q < kFlDims; ++q) y[k][q] *= r[k][q];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int q = 0; q < kFlDims; ++q)
+          y[k][q] = r[k][q] > 0.0 ? exp2(p * log2(r[k][q])) : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (k < m)
+#pragma unroll
+        for (int q = 0; q < kFlDims; ++q) {
+          const uint32_t up = bit_mask(b[k], q);
+          ql[q] = fma(hi_double(~up & 0x3FF00000u), y[k][q], ql[q]);
+          qu[q] = fma(hi_double(up & 0x3FF00000u), y[k][q], qu[q]);
+        }
+  });
+  const int w = (tid >> 6) & 1;
+#pragma unroll
+  for (int q = 0; q < kFlDims; ++q) {
+    const double a = wave_reduce63_sum(ql[q]), c = wave_reduce63_sum(qu[q]);
+    if ((tid & 63) == 63) {
+      red[g][w][2 * q] = a;
+      red[g][w][2 * q + 1] = c;
+    }
   }
-  if (i < cnt) {
-    const bool ua = (sb[i] >> j) & 1u;
-    const double ta = pow01(fabs(sv[i] - (ua ? m1 : m0)) * (ua ? i1v : i0v), p, ip);
-    if (ua) q01 += ta; else q00 += ta;
-  }
-  double q0 = q00 + q10, q1 = q01 + q11;
-  for (int o = G >> 1; o > 0; o >>= 1) {
-    q0 += __shfl_xor(q0, o, G);
-    q1 += __shfl_xor(q1, o, G);
-  }
-  if (sub == 0) {
-    double *r = A.fl2 + (((size_t)s * A.nchunks + ch) * d + j) * 2;
-    r[0] = q0;
-    r[1] = q1;
-  }
+  __syncthreads();
+  const int j = kFlDims * g + (t >> 1);
+  if (t < 2 * kFlDims && j < d)
+    A.fl2[(((size_t)s * A.nchunks + ch) * d + j) * 2 + (t & 1)] = red[g][0][t] + red[g][1][t];
 }
 
 namespace {
@@ -530,25 +622,31 @@ __global__ void __launch_bounds__(256) suave_split_kernel(SuaveArgs A, int R, lo
   const int s = blockIdx.x, tid = threadIdx.x;
   const int d = A.d, N = A.N, row = N + 1;
   const int pos = A.sel[s], up = R + s;
-  __shared__ double s_score[kMaxDim], s_S[kMaxDim][4];
-  if (tid < d) {  // F_0 + F_1 of a cut along dimension tid
-    const double *h = A.hs + ((size_t)s * d + tid) * kHs;
-    const double nd = (double)A.nnew, p = A.flatness;
-    double score = 0.0;
-    for (int k = 0; k < 2; ++k) {
-      double q = 0.0;
+  constexpr int kItems = 2 * kMaxDim, kSegs = 256 / kItems;
+  __shared__ double s_part[kSegs][kItems], s_term[kItems], s_score[kMaxDim], s_S[kMaxDim][4];
+  {  // pass 2 over the chunks: item 2j + k in kSegs interleaved runs
+    const int seg = tid / kItems, item = tid % kItems;
+    double q = 0.0;
+    if (item < 2 * d) {
+      const double *r = A.fl2 + (size_t)s * A.nchunks * d * 2 + item;
 #pragma unroll 8
-      for (int ch = 0; ch < A.nchunks; ++ch)
-        q += A.fl2[(((size_t)s * A.nchunks + ch) * d + tid) * 2 + k];
-      const double cnt = h[5 * k], M = h[5 * k + 4];
-      if (cnt > 0.0 && M > 0.0) score += (cnt / nd) * M * pow(q / cnt, 1.0 / p);
+      for (int ch = seg; ch < A.nchunks; ch += kSegs) q += r[(size_t)ch * d * 2];
     }
-    s_score[tid] = score;
-    s_S[tid][0] = h[1];
-    s_S[tid][1] = h[2];
-    s_S[tid][2] = h[6];
-    s_S[tid][3] = h[7];
+    s_part[seg][item] = q;
   }
+  __syncthreads();
+  if (tid < 2 * d) {  // one half's term of a cut along dimension tid / 2
+    const double *h = A.hs + ((size_t)s * d + (tid >> 1)) * kHs + 5 * (tid & 1);
+    const double nd = (double)A.nnew, p = A.flatness;
+    double q = s_part[0][tid];
+    for (int k = 1; k < kSegs; ++k) q += s_part[k][tid];
+    const double cnt = h[0], M = h[4];
+    s_term[tid] = cnt > 0.0 && M > 0.0 ? (cnt / nd) * M * pow(q / cnt, 1.0 / p) : 0.0;
+    s_S[tid >> 1][2 * (tid & 1)] = h[1];
+    s_S[tid >> 1][2 * (tid & 1) + 1] = h[2];
+  }
+  __syncthreads();
+  if (tid < d) s_score[tid] = s_term[2 * tid] + s_term[2 * tid + 1];
   __syncthreads();
   if (tid == 0) {
     int best = 0;
@@ -616,74 +714,99 @@ __global__ void __launch_bounds__(256) suave_split_kernel(SuaveArgs A, int R, lo
   }
 }
 
-// DoSample of every child: one workgroup per (tile of kSuaveTile points, child).
-template <int FAM, int NB>
+namespace {
+
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ double uniform(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)b);
+  const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+}  // namespace
+
+// DoSample of every child: one workgroup per (tile of A.tile points, child).
+// Bound by VALU issue, with the LDS (a cell read and an FP64 add per
+// coordinate) close behind.  All of a point's cells are read before the first
+// is used; POW2 and FULL (d = 4 NB) as in the Vegas DoSample kernel: a
+// power-of-two bin count's fraction is formed from the word's bits, and only
+// the last Philox block's coordinates can be missing.
+// 128 children of 2^17 points, d = 8, 128 bins, Gaussian: 116 us (145 G points/s),
+// 136 with the constants in vector registers, a branch per coordinate and tiles
+// of 4096 points.
+template <int FAM, int NB, bool POW2, bool FULL>
 __global__ void __launch_bounds__(kSuaveBlock) suave_sample_kernel(SuaveArgs A) {
-  extern __shared__ double lds[];
-  __shared__ double sBlo[kMaxDim], sBw[kMaxDim], sP0[kMaxDim], sP1[kMaxDim];
+  extern __shared__ __align__(16) double lds[];
   __shared__ double red[kSuaveBlock / 64];
   const int c = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x;
   const int pos = A.chpos[c], serial = A.chser[c];
   const int d = A.d, N = A.N, dN = d * N;
-  double *sLo = lds, *sSp = lds + dN, *sH = lds + 2 * dN;
+  Cell<double> *sC = (Cell<double> *)lds;
+  double *sH = lds + 2 * dN;
   const double *G = A.R.grid + (size_t)pos * d * (N + 1);
-  for (int e = tid; e < dN; e += kSuaveBlock) {
-    const int j = e / N, k = e - j * N;
-    const double l = G[j * (N + 1) + k], h = G[j * (N + 1) + k + 1];
-    sLo[e] = l;
-    sSp[e] = h - l;
-    sH[e] = 0.0;
-  }
-  if (tid < d) {
-    const double lo = A.R.lo[(size_t)pos * d + tid];
-    sBlo[tid] = lo;
-    sBw[tid] = A.R.hi[(size_t)pos * d + tid] - lo;
-    sP0[tid] = A.p64[tid];
-    sP1[tid] = A.p64[kParamRow + tid];
+  stage_cells<double, POW2>(G, d, N, sC);
+  for (int e = tid; e < dN; e += kSuaveBlock) sH[e] = 0.0;
+  // the child's box and the integrand's constants, the same for the whole
+  // workgroup: in scalar registers (in vector registers they take 64 at d = 8
+  // and cost the fourth wavefront of a SIMD)
+  constexpr int D = 4 * NB;
+  double blo[D], bw[D], p0[D], p1[D], V = 1.0;
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const size_t at = (size_t)pos * d + (j < d ? j : 0);
+    blo[j] = uniform(A.R.lo[at]);
+    bw[j] = uniform(A.R.hi[at] - A.R.lo[at]);
+    p0[j] = uniform(A.p64[j]);
+    p1[j] = uniform(A.p64[kParamRow + j]);
+    if (j < d) V *= bw[j];
   }
   __syncthreads();
-  double V = 1.0;
-  for (int j = 0; j < d; ++j) V *= sBw[j];
-  const double phase0 = sP1[0];
+  const double phase0 = p1[0];
   const double Nd = (double)N;
+  const int L = POW2 ? 31 - __clz(N) : 0;
+  const double scale = pow2_scale<double>(L);
   const long long n = A.nnew;
-  const long long i0 = (long long)tile * kSuaveTile;
-  const long long i1 = min(i0 + (long long)kSuaveTile, n);
+  const long long i0 = (long long)tile * A.tile;
+  const long long i1 = min(i0 + (long long)A.tile, n);
   double *vout = A.R.v + (size_t)pos * n;
   uint16_t *sout = A.R.side + (size_t)pos * n;
   double S1 = 0.0, S2 = 0.0;
   for (long long i = i0 + tid; i < i1; i += kSuaveBlock) {
-    double w = 1.0;
-    double acc = Genz<double, FAM>::init(phase0);
-    uint32_t bits = 0;
-    int cell[4 * NB];
+    int idx[D];
+    double fr[D], lo[D], sp[D];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      {
-        const U4 W = philox4x32_10(
-            U4{(uint32_t)i, ((uint32_t)serial << 8) | (uint32_t)b, A.sid, 0u}, A.key0, A.key1);
-        const uint32_t wd[4] = {W.x, W.y, W.z, W.w};
+      const U4 W = philox4x32_10(
+          U4{(uint32_t)i, ((uint32_t)serial << 8) | (uint32_t)b, A.sid, 0u}, A.key0, A.key1);
+      const uint32_t wd[4] = {W.x, W.y, W.z, W.w};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = 4 * b + q;
-          cell[j] = 0;
-          if (j < d) {
-            const double y = (double)wd[q] * 0x1p-32 + 0x1p-33;
-            const double z = y * Nd;
-            int k = (int)z;
-            if (k > N - 1) k = N - 1;
-            const double fr = z - (double)k;
-            const int e = j * N + k;
-            const double sp = sSp[e];
-            const double xr = fma(fr, sp, sLo[e]);
-            w = w * (Nd * sp);
-            acc = Genz<double, FAM>::step(acc, fma(xr, sBw[j], sBlo[j]), sP0[j], sP1[j]);
-            if (xr >= 0.5) bits |= 1u << j;
-            cell[j] = e;
-          }
+      for (int q = 0; q < 4; ++q) {
+        const int j = 4 * b + q;
+        if (FULL || b < NB - 1 || j < d) {
+          int k;
+          if (POW2)
+            bin_frac_pow2(wd[q], L, scale, fr[j], k);
+          else
+            bin_frac_any(wd[q], N, Nd, fr[j], k);
+          idx[j] = j * N + k;
+          const Cell<double> cell = sC[j * N + k];
+          lo[j] = cell.lo;
+          sp[j] = cell.span;
         }
       }
     }
+    double w = 1.0;
+    double acc = Genz<double, FAM>::init(phase0);
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+      if (FULL || j < 4 * (NB - 1) || j < d) {
+        const double xr = fma(fr[j], sp[j], lo[j]);
+        w = POW2 ? w * sp[j] : w * (Nd * sp[j]);
+        acc = Genz<double, FAM>::step(acc, fma(xr, bw[j], blo[j]), p0[j], p1[j]);
+        if (xr >= 0.5) bits |= 1u << j;
+      }
     const double v = (w * V) * Genz<double, FAM>::finish(acc, d);
     vout[i] = v;
     sout[i] = (uint16_t)bits;
@@ -691,8 +814,8 @@ __global__ void __launch_bounds__(kSuaveBlock) suave_sample_kernel(SuaveArgs A) 
     S1 += v;
     S2 += v2;
 #pragma unroll
-    for (int j = 0; j < 4 * NB; ++j)
-      if (j < d) atomicAdd(&sH[cell[j]], v2);
+    for (int j = 0; j < D; ++j)
+      if (FULL || j < 4 * (NB - 1) || j < d) unsafeAtomicAdd(&sH[idx[j]], v2);
   }
   S1 = block_sum(S1, red);
   S2 = block_sum(S2, red);
@@ -705,121 +828,127 @@ __global__ void __launch_bounds__(kSuaveBlock) suave_sample_kernel(SuaveArgs A) 
   for (int e = tid; e < dN; e += kSuaveBlock) A.thist[t * dN + e] = sH[e];
 }
 
-// Per child: its own estimate, the combination, and the refined grid.
-__global__ void __launch_bounds__(1024) suave_fold_kernel(SuaveArgs A) {
-  extern __shared__ double lds[];
-  __shared__ double red[16];
-  const int c = blockIdx.x, tid = threadIdx.x;
+// One workgroup per (child, dimension): the refined grid of the dimension;
+// dimension 0's also takes the child's own estimate and the combination.
+// Latency: the tile rows of N bins in one trip, then the refinement's chain.
+// 128 children, d = 8, 128 bins: 10.9 us, 14.7 with one workgroup per child.
+constexpr int kSuaveFold = 256;  // threads (and at most kMaxBins = 256 bins)
+
+__global__ void __launch_bounds__(kSuaveFold) suave_fold_kernel(SuaveArgs A) {
+  __shared__ double H[kMaxBins], D[kMaxBins], E[kMaxBins + 1];
+  __shared__ double red[kSuaveFold / 64];
+  const int c = blockIdx.x, j = blockIdx.y, tid = threadIdx.x;
   const int pos = A.chpos[c];
   const int d = A.d, N = A.N, dN = d * N, row = N + 1, nt = A.ntiles;
-  double *H = lds, *D = lds + dN, *E = lds + 2 * dN;
-  double S1 = 0.0, S2 = 0.0;
-  for (int t = tid; t < nt; t += 1024) {
-    S1 += A.tsum[2 * ((size_t)c * nt + t)];
-    S2 += A.tsum[2 * ((size_t)c * nt + t) + 1];
-  }
-  S1 = block_sum(S1, red);
-  S2 = block_sum(S2, red);
-  const double *th = A.thist + (size_t)c * nt * dN;
-  for (int e = tid; e < dN; e += 1024) {
-    double h = 0.0;
-#pragma unroll 8
-    for (int t = 0; t < nt; ++t) h += th[(size_t)t * dN + e];
-    H[e] = h;
-  }
-  double *G = A.R.grid + (size_t)pos * d * row;
-  for (int e = tid; e < d * row; e += 1024) E[e] = G[e];
-  if (tid == 0) {
-    const double n = (double)A.nnew;
-    const double I = S1 / n;
-    const double var = fmax(0.0, S2 / n - I * I) / (n - 1.0);
-    const double iI = A.R.inh_I[pos], iv = A.R.inh_var[pos];
-    const bool inh = iv > 0.0;
-    const double Ik[2] = {iI, I}, Vk[2] = {iv, var};
-    const int k0 = inh ? 0 : 1;
-    int nzero = 0;
-    double zsum = 0.0;
-    for (int k = k0; k < 2; ++k)
-      if (Vk[k] == 0.0) {
-        ++nzero;
-        zsum += Ik[k];
-      }
-    double Ir, Vr, chi2 = 0.0;
-    if (nzero > 0) {
-      Ir = zsum / nzero;
-      Vr = 0.0;
-    } else {
-      double ws = 0.0, wi = 0.0;
-      for (int k = k0; k < 2; ++k) {
-        ws += 1.0 / Vk[k];
-        wi += Ik[k] / Vk[k];
-      }
-      Ir = wi / ws;
-      Vr = 1.0 / ws;
-      for (int k = k0; k < 2; ++k) chi2 += (Ik[k] - Ir) * (Ik[k] - Ir) / Vk[k];
+  const bool refine = !(A.flags & FLAG_FREEZE_GRID);
+  double *G = A.R.grid + ((size_t)pos * d + j) * row;
+  if (refine) {
+    const double *th = A.thist + (size_t)c * nt * dN + (size_t)j * N + tid;
+    if (tid < N) {
+      double h = 0.0;
+#pragma unroll 16
+      for (int t = 0; t < nt; ++t) h += th[(size_t)t * dN];
+      H[tid] = h;
     }
-    A.R.I[pos] = Ir;
-    A.R.var[pos] = Vr;
-    A.R.chi2[pos] = chi2;
-    A.R.dof[pos] = inh ? 1 : 0;
+    for (int e = tid; e < row; e += kSuaveFold) E[e] = G[e];
+  }
+  if (j == 0) {
+    double S1 = 0.0, S2 = 0.0;
+    for (int t = tid; t < nt; t += kSuaveFold) {
+      S1 += A.tsum[2 * ((size_t)c * nt + t)];
+      S2 += A.tsum[2 * ((size_t)c * nt + t) + 1];
+    }
+    S1 = block_sum(S1, red);
+    S2 = block_sum(S2, red);
+    if (tid == kSuaveFold - 1) {  // (not the wavefront that refines)
+      const double n = (double)A.nnew;
+      const double I = S1 / n;
+      const double var = fmax(0.0, S2 / n - I * I) / (n - 1.0);
+      const double iI = A.R.inh_I[pos], iv = A.R.inh_var[pos];
+      const bool inh = iv > 0.0;
+      const double Ik[2] = {iI, I}, Vk[2] = {iv, var};
+      const int k0 = inh ? 0 : 1;
+      int nzero = 0;
+      double zsum = 0.0;
+      for (int k = k0; k < 2; ++k)
+        if (Vk[k] == 0.0) {
+          ++nzero;
+          zsum += Ik[k];
+        }
+      double Ir, Vr, chi2 = 0.0;
+      if (nzero > 0) {
+        Ir = zsum / nzero;
+        Vr = 0.0;
+      } else {
+        double ws = 0.0, wi = 0.0;
+        for (int k = k0; k < 2; ++k) {
+          ws += 1.0 / Vk[k];
+          wi += Ik[k] / Vk[k];
+        }
+        Ir = wi / ws;
+        Vr = 1.0 / ws;
+        for (int k = k0; k < 2; ++k) chi2 += (Ik[k] - Ir) * (Ik[k] - Ir) / Vk[k];
+      }
+      A.R.I[pos] = Ir;
+      A.R.var[pos] = Vr;
+      A.R.chi2[pos] = chi2;
+      A.R.dof[pos] = inh ? 1 : 0;
+    }
   }
   __syncthreads();
-  if (A.flags & FLAG_FREEZE_GRID) return;
-  const int w = tid >> 6, lane = tid & 63;
-  if (w < d) rebin_dimension(H + w * N, D + w * N, E + w * row, G + w * row, N, lane);
+  if (refine && tid < 64) rebin_dimension(H, D, E, G, N, tid);
 }
 
-// Totals over the R regions (fixed order) and the chi^2 probability.
-__global__ void __launch_bounds__(1024) suave_totals_kernel(SuaveArgs A, int R) {
-  __shared__ double red[16];
+// Totals over the R regions (fixed order), the stop rule's outcome and, once
+// the run ends with them, the chi^2 probability.  The outcome goes to the
+// host as one word, seq << 8 | code, that it polls (code 0: go on, 1:
+// accuracy reached, 2: not finite); the totals beside it are read after the
+// stream has drained.
+__global__ void __launch_bounds__(1024) suave_totals_kernel(SuaveArgs A, int R, SStop stop) {
+  __shared__ double red[4][16];
   const int tid = threadIdx.x;
   const int chunk = (R + 1023) / 1024;
   const int b0 = min(tid * chunk, R), b1 = min(b0 + chunk, R);
-  double I = 0.0, V = 0.0, X = 0.0, F = 0.0;
+  double x[4] = {0.0, 0.0, 0.0, 0.0};
   for (int i = b0; i < b1; ++i) {
-    I += A.R.I[i];
-    V += A.R.var[i];
-    X += A.R.chi2[i];
-    F += (double)A.R.dof[i];
+    x[0] += A.R.I[i];
+    x[1] += A.R.var[i];
+    x[2] += A.R.chi2[i];
+    x[3] += (double)A.R.dof[i];
   }
-  I = block_sum(I, red);
-  V = block_sum(V, red);
-  X = block_sum(X, red);
-  F = block_sum(F, red);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    x[k] = wave_sum(x[k]);
+    if ((tid & 63) == 0) red[k][tid >> 6] = x[k];
+  }
+  __syncthreads();
   if (tid == 0) {
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      for (int q = 0; q < 16; ++q) t[k] += red[k][q];
     SState st;
-    st.I = I;
-    st.var = V;
-    st.chi2 = X;
-    st.dof = (int)F;
+    st.I = t[0];
+    st.var = t[1];
+    st.chi2 = t[2];
+    st.dof = (int)t[3];
     st.pad = 0;
-    st.prob = st.dof > 0 ? gamma_p(0.5 * st.dof, 0.5 * X) : 0.0;
-    *A.state = st;
+    int code = 0;
+    if (!isfinite(st.I) || !isfinite(st.var))
+      code = 2;
+    else if (stop.neval >= stop.mineval &&
+             sqrt(st.var) <= fmax(stop.epsabs, stop.epsrel * fabs(st.I)))
+      code = 1;
+    st.prob = (code || stop.last) && st.dof > 0 ? gamma_p(0.5 * st.dof, 0.5 * st.chi2) : 0.0;
+    *stop.state = st;
+    __hip_atomic_store(stop.word, ((unsigned long long)stop.seq << 8) | (unsigned long long)code,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
 // ---- launchers ---------------------------------------------------------------
 
 size_t suave_sample_lds(int d, int N) { return (size_t)3 * d * N * sizeof(double); }
-size_t suave_fold_lds(int d, int N) {
-  return ((size_t)2 * d * N + (size_t)d * (N + 1)) * sizeof(double);
-}
-
-hipError_t suave_set_kernel_limits() {
-  const int big = 160 * 1024;
-  const void *fns[] = {(const void *)suave_fold_kernel,
-#define CCUBA_SUAVE_FNS(F)                                                            \
-  (const void *)suave_sample_kernel<F, 1>, (const void *)suave_sample_kernel<F, 2>, \
-      (const void *)suave_sample_kernel<F, 3>, (const void *)suave_sample_kernel<F, 4>
-                       CCUBA_SUAVE_FNS(GAUSSIAN), CCUBA_SUAVE_FNS(OSCILLATORY),
-                       CCUBA_SUAVE_FNS(PRODUCT_PEAK), CCUBA_SUAVE_FNS(CORNER_PEAK),
-                       CCUBA_SUAVE_FNS(C0)};
-#undef CCUBA_SUAVE_FNS
-  for (const void *f : fns)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, big) != hipSuccess)
-      (void)hipGetLastError();
-  return hipSuccess;
-}
 
 hipError_t launch_suave_root(const SuaveArgs &A, hipStream_t s) {
   hipLaunchKernelGGL(suave_root_kernel, dim3(1), dim3(256), 0, s, A);
@@ -836,9 +965,9 @@ hipError_t launch_suave_select(const SuaveArgs &A, int R, int K, hipStream_t s) 
 }
 
 hipError_t launch_suave_fluct(const SuaveArgs &A, int K, hipStream_t s) {
-  hipLaunchKernelGGL(suave_fluct1_kernel, dim3(A.nchunks, K), dim3(kFlBlock), 0, s, A);
-  hipLaunchKernelGGL(suave_fluct_reduce_kernel, dim3(K), dim3(64), 0, s, A);
-  hipLaunchKernelGGL(suave_fluct2_kernel, dim3(A.nchunks, K), dim3(kFlBlock), 0, s, A);
+  const dim3 grid(A.nchunks, K), block(kFlThreads * ((A.d + kFlDims - 1) / kFlDims));
+  hipLaunchKernelGGL(suave_fluct1_kernel, grid, block, 0, s, A);
+  hipLaunchKernelGGL(suave_fluct2_kernel, grid, block, 0, s, A);
   return hipGetLastError();
 }
 
@@ -849,21 +978,29 @@ hipError_t launch_suave_split(const SuaveArgs &A, int R, long long Q, int K, hip
 
 namespace {
 
+template <int FAM, int NB>
+void launch_sample_nb(const SuaveArgs &A, dim3 grid, size_t lds, hipStream_t s) {
+  const bool pow2 = (A.N & (A.N - 1)) == 0, full = A.d == 4 * NB;
+  const auto kernel = pow2 ? (full ? suave_sample_kernel<FAM, NB, true, true>
+                                   : suave_sample_kernel<FAM, NB, true, false>)
+                           : (full ? suave_sample_kernel<FAM, NB, false, true>
+                                   : suave_sample_kernel<FAM, NB, false, false>);
+  // more LDS than a launch gets by default (up to d = 16 with 256 bins); a
+  // runtime that refuses keeps its limit, and the launch reports an error
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          160 * 1024) != hipSuccess)
+    (void)hipGetLastError();
+  hipLaunchKernelGGL(kernel, grid, dim3(kSuaveBlock), lds, s, A);
+}
+
 template <int FAM>
 void launch_sample_fam(const SuaveArgs &A, dim3 grid, size_t lds, hipStream_t s) {
   switch ((A.d + 3) / 4) {
-    case 1:
-      hipLaunchKernelGGL((suave_sample_kernel<FAM, 1>), grid, dim3(kSuaveBlock), lds, s, A);
-      break;
-    case 2:
-      hipLaunchKernelGGL((suave_sample_kernel<FAM, 2>), grid, dim3(kSuaveBlock), lds, s, A);
-      break;
-    case 3:
-      hipLaunchKernelGGL((suave_sample_kernel<FAM, 3>), grid, dim3(kSuaveBlock), lds, s, A);
-      break;
-    default:
-      hipLaunchKernelGGL((suave_sample_kernel<FAM, 4>), grid, dim3(kSuaveBlock), lds, s, A);
-      break;
+    case 1: launch_sample_nb<FAM, 1>(A, grid, lds, s); break;
+    case 2: launch_sample_nb<FAM, 2>(A, grid, lds, s); break;
+    case 3: launch_sample_nb<FAM, 3>(A, grid, lds, s); break;
+    default: launch_sample_nb<FAM, 4>(A, grid, lds, s); break;
   }
 }
 
@@ -893,12 +1030,13 @@ hipError_t launch_suave_sample(const SuaveArgs &A, int nchild, hipStream_t s) {
 }
 
 hipError_t launch_suave_fold(const SuaveArgs &A, int nchild, hipStream_t s) {
-  hipLaunchKernelGGL(suave_fold_kernel, dim3(nchild), dim3(1024), suave_fold_lds(A.d, A.N), s, A);
+  const int dims = A.flags & FLAG_FREEZE_GRID ? 1 : A.d;
+  hipLaunchKernelGGL(suave_fold_kernel, dim3(nchild, dims), dim3(kSuaveFold), 0, s, A);
   return hipGetLastError();
 }
 
-hipError_t launch_suave_totals(const SuaveArgs &A, int R, hipStream_t s) {
-  hipLaunchKernelGGL(suave_totals_kernel, dim3(1), dim3(1024), 0, s, A, R);
+hipError_t launch_suave_totals(const SuaveArgs &A, int R, const SStop &stop, hipStream_t s) {
+  hipLaunchKernelGGL(suave_totals_kernel, dim3(1), dim3(1024), 0, s, A, R, stop);
   return hipGetLastError();
 }
 

@@ -39,3 +39,33 @@ def test_partition_ties_and_group_sizes(cc, ctx, d, maxregions, nsplit):
         assert np.array_equal(g[k], o[k]), k
     for k in ("fmin", "fmax", "spread"):
         assert np.allclose(g[k], o[k], rtol=1e-12, atol=0), k
+
+
+def _suave_both(cc, ctx, fam, d, **kw):
+    a, u = W.genz_params(fam, d, d + 40)
+    g = cc.suave(fam, a, u, ctx=ctx, trace=True, **kw)
+    o = O.suave(O.genz(fam, a, u), d, **kw)
+    assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert np.array_equal(g["cut"], o["cut"]) and np.array_equal(g["lo"], o["lo"])
+    for k, tol in (("integral", 1e-12), ("error", 1e-10)):
+        assert abs(g[k] - o[k]) <= tol * abs(o[k]), k
+    assert np.allclose(g["grid"], o["grid"], rtol=0, atol=1e-12)
+    assert abs(g["prob"] - o["prob"]) < 1e-9
+
+
+@pytest.mark.parametrize("d,nbins,nnew,nsplit,flatness", [
+    (4, 64, 1023, 3, 25.0),     # one tile, a ragged chunk
+    (5, 100, 1025, 1, 3.0),     # one more than the smallest piece
+    (8, 256, 12289, 7, 50.0),   # several pieces, d = 4 nb
+    (9, 128, 5000, 5, 2.5),     # the third dimension group, a fractional power
+    (16, 256, 2500, 2, 64.0),   # LDS beyond the default limit
+    (1, 3, 300000, 2, 1.0)])    # the most chunks, one dimension
+def test_suave_pieces_match_oracle(cc, ctx, d, nbins, nnew, nsplit, flatness):
+    _suave_both(cc, ctx, W.C0 if d % 2 else W.PRODUCT_PEAK, d, seed=d, nnew=nnew, nbins=nbins,
+                nsplit=nsplit, flatness=flatness, maxeval=11 * nnew)
+
+
+def test_suave_converging_run_matches_oracle(cc, ctx):
+    # the run ends on its accuracy while the next step's statistics are queued
+    _suave_both(cc, ctx, W.PRODUCT_PEAK, 3, seed=3, nnew=2000, nbins=32, nsplit=4, flatness=5.0,
+                epsrel=2e-3, maxeval=10**6)
