@@ -864,7 +864,7 @@ int ccuba_cuhre(ccuba_ctx **ctxp, int ndim, int ncomp, const ccuba_integrand *f,
   double *ph = nullptr, *pd = nullptr;
   if ((rc = pinned_block(ctx, &ph, &pd))) return rc;
   run.set_mapped_totals(ph, pd);
-  if ((rc = run.start(sp, ctx->stream)) || (rc = run.run(ctx->stream))) return rc;
+  if ((rc = run.start(sp, ctx->stream, false)) || (rc = run.run(ctx->stream))) return rc;
   *nregions = (int)std::min<long long>(run.nregions(), 0x7fffffff);
   *neval = run.neval();
   *fail = run.fail();

@@ -65,6 +65,11 @@ struct CRows {
   CStop stop;
 };
 
+// The rule's generators.
+struct RuleLambdas {
+  double l2, l3, l4, l5;
+};
+
 struct RuleArgs {
   const CSeg *segs;          // device table (nseg > 1)
   int nseg;
@@ -72,10 +77,32 @@ struct RuleArgs {
   long long total;
   CSeg one;                  // the segment itself when nseg == 1 (no table)
   const double *w7, *w5;     // [ndim][5] rule weights (rows 0..16)
-  double l2, l3, l4, l5;
+  RuleLambdas lam;
   int *done;                 // a run's stop flag (null: none): set, the launch does nothing
   CRows rows;                // step opening and rows of the next state (zero: neither)
 };
+
+// The first states of a run in one launch (cuhre_grow_kernel): the root and
+// `doublings' doublings.  The outcome of the last state but one, or of the
+// state that ended the run, goes to slot as in CRows (its sequence number
+// says which); the totals of the last state are one row.  Clears the stop
+// flag first.
+constexpr int kGrowRegions = 32;
+constexpr int kGrowMaxDim = 8;
+struct GrowArgs {
+  CRegions R;
+  int d, doublings;
+  const double *params;    // [2][kParamRow]
+  const double *w7, *w5;   // as in RuleArgs
+  RuleLambdas lam;
+  long long np;            // rule points of a region
+  CStop stop;              // (neval is the state's own)
+  double *row;
+  long long stride;
+  double *slot;
+  int *done;
+};
+hipError_t launch_grow(const GrowArgs &A, int family, hipStream_t s);
 
 // Per-integral scratch for selection, splitting and totals.
 struct CScratch {

@@ -1,7 +1,8 @@
 // cuhre.hip -- Cuhre on gfx950: the degree-7 Genz-Malik rule over batches of
 // subregions, top-K selection, bisection and compaction of the region heap.
 //
-// a8 (the DoSample of Cuhre): one wavefront per region.  The lanes walk the
+// a8 (the DoSample of Cuhre): one wavefront per region (one workgroup in
+//    small launches, one lane at small d in large ones).  The lanes walk the
 //    2^d + 2d^2 + 2d + 1 rule points (Genz & Malik 1980) of their region,
 //    decoding each point index to its generator class and axes, evaluate the
 //    Genz integrand in FP64, and keep five class sums; the class-2 and
@@ -31,6 +32,7 @@
 
 #include "cuhre.h"
 #include "genz.h"
+#include "wave.h"
 
 namespace ccuba {
 
@@ -40,6 +42,11 @@ constexpr int kLaneRuleMaxDim = 8;          // lane-per-region rule up to this d
 constexpr long long kLaneRuleMinRegions = 512;  // and from this many regions on
 constexpr long long kOneLaneRuleMinRegions = 49152;  // one lane per region from here
 constexpr long long kWaveRuleBlocks = 2048;       // most blocks of a wave-per-region launch
+// Up to this many regions a launch over several integrals or above 8
+// dimensions gives each a whole workgroup (its four wavefronts share the rule
+// points): about what the device holds at once, so that the launch takes as
+// long as one region does.
+constexpr long long kBlockRuleRegions = 1024;
 constexpr int kScanItems = 4;
 constexpr int kScanBlock = 256;
 constexpr int kScanTile = kScanItems * kScanBlock;  // elements per scan block
@@ -116,25 +123,46 @@ __device__ __forceinline__ double rule_point_f(int d, const double *c, const dou
   return Genz<double, FAM>::finish(acc, d);
 }
 
-// One region per wavefront; returns (I7, err) in lane 0.
+// Order the LDS traffic of the W wavefronts that share a region.
+template <int W>
+__device__ __forceinline__ void sync_region() {
+  if constexpr (W == 1) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// LDS of one region.
+struct RuleLds {
+  double c[kMaxDim], h[kMaxDim];
+  double f[4 * kMaxDim + 1];  // class 1 values, class 2 values, the centre
+  double x[2 * kMaxDim];      // c + l5 h and c - l5 h per axis
+};
+
+// The class sums over the rule points that thread tid of NT = 2^LB takes, into
+// Sk; the class-1 and class-2 values and the centre's to L.f.  p0 and p1 are
+// the integrand's constants.
+//
+// Corners (class 4, all of the work at large d): a thread's low bits fix the
+// signs of the first axes, whose part of the integrand's running value is
+// formed once; the corners over the remaining axes are the leaves of a tree
+// whose last three levels are unrolled, so that a corner costs two to three
+// steps and not d (with every step in axis order, as rule_point_f takes them).
+// Requests of the serving loop up to d = 16: 15 us a launch, 107 with d steps a
+// corner and a wavefront per region.
 template <int FAM>
-__device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, int w, int lane,
-                               double (*sc)[kMaxDim], double (*sh)[kMaxDim],
-                               double (*sf)[4 * kMaxDim + 1], double (*sx)[2 * kMaxDim]) {
-  const int d = S.ndim;
-  if (lane < d) child_coord(S, r, lane, &sc[w][lane], &sh[w][lane]);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const double *c = sc[w], *h = sh[w];
-  const double *p0 = S.par;
-  const double *p1 = S.par + kParamRow;
+__device__ __forceinline__ void rule_points(const RuleLambdas &A, int d, int tid, int NT, int LB,
+                                            RuleLds &L, const double *p0, const double *p1,
+                                            double (&Sk)[5]) {
+  const double *c = L.c, *h = L.h;
   const double phase0 = p1[0];
-  const long long n2 = 2ll * d, n4 = 2ll * d * (d - 1);
-  const long long b2 = 1, b3 = 1 + n2, b4 = 1 + 2 * n2, b5 = 1 + 2 * n2 + n4;
-  double Sk[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  const int n2 = 2 * d, n4 = 2 * d * (d - 1);
+  const int b2 = 1, b3 = 1 + n2, b4 = 1 + 2 * n2, b5 = 1 + 2 * n2 + n4;
   // classes 0-3 (a few hundred points at most)
-  for (long long p = lane; p < b5; p += 64) {
+  for (int p = tid; p < b5; p += NT) {
     int cls, i = 0, jj = 0;
     unsigned sgn = 0;
     double lam = 0.0;
@@ -142,17 +170,17 @@ __device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, in
       cls = 0;
     } else if (p < b3) {
       cls = 1;
-      i = (int)((p - b2) >> 1);
+      i = (p - b2) >> 1;
       sgn = (unsigned)((p - b2) & 1);
       lam = A.l2;
     } else if (p < b4) {
       cls = 2;
-      i = (int)((p - b3) >> 1);
+      i = (p - b3) >> 1;
       sgn = (unsigned)((p - b3) & 1);
       lam = A.l3;
-    } else if (p < b5) {
+    } else {
       cls = 3;
-      long long q = (p - b4) >> 2;
+      int q = (p - b4) >> 2;
       sgn = (unsigned)((p - b4) & 3);
       i = 0;
       int row = d - 1;
@@ -161,55 +189,72 @@ __device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, in
         ++i;
         --row;
       }
-      jj = i + 1 + (int)q;
+      jj = i + 1 + q;
       lam = A.l4;
-    } else {
-      cls = 4;
-      sgn = (unsigned)(p - b5);
-      lam = A.l5;
     }
     const double f = rule_point_f<FAM>(d, c, h, p0, p1, cls, i, jj, sgn, lam, phase0);
-    Sk[cls] += f;
-    if (cls == 0) sf[w][4 * kMaxDim] = f;
-    if (cls == 1) sf[w][(int)(p - b2)] = f;                 // [2i + sign]
-    if (cls == 2) sf[w][2 * kMaxDim + (int)(p - b3)] = f;   // [2d.. + 2i + sign]
-  }
-  // class 4, the 2^d corners (all of the work at large d): both coordinates
-  // of every axis, c - l5 h and c + l5 h, are formed once per region (the
-  // values rule_point_f forms per point), so a corner is d selects and the
-  // integrand's own steps
-  if (lane < d) {
-    const double t = A.l5 * h[lane];
-    sx[w][2 * lane] = c[lane] + t;
-    sx[w][2 * lane + 1] = c[lane] - t;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const unsigned ncorner = 1u << d;
-  for (unsigned sg = lane; sg < ncorner; sg += 64) {
-    double acc = Genz<double, FAM>::init(phase0);
-    for (int j = 0; j < d; ++j)
-      acc = Genz<double, FAM>::step(acc, sx[w][2 * j + ((sg >> j) & 1u)], p0[j], p1[j]);
-    Sk[4] += Genz<double, FAM>::finish(acc, d);
-  }
 #pragma unroll
-  for (int k = 0; k < 5; ++k) Sk[k] = wsum(Sk[k]);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // fourth differences and the arg-max axis (lowest axis on ties)
+    for (int k = 0; k < 4; ++k) Sk[k] += k == cls ? f : 0.0;
+    if (cls == 0) L.f[4 * kMaxDim] = f;
+    if (cls == 1) L.f[p - b2] = f;                // [2i + sign]
+    if (cls == 2) L.f[2 * kMaxDim + p - b3] = f;  // [2d.. + 2i + sign]
+  }
+  const int pre = min(LB, d), rest = d - pre;
+  if (tid < (1 << pre)) {
+    double acc0 = Genz<double, FAM>::init(phase0);
+    for (int j = 0; j < pre; ++j)
+      acc0 = Genz<double, FAM>::step(acc0, L.x[2 * j + ((tid >> j) & 1)], p0[j], p1[j]);
+    // corners over the axes [pre, d), the low bits of m first
+    const int mid = rest >= 3 ? rest - 3 : rest;
+    double x3[6], q0[3], q1[3];
+    if (rest >= 3) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) x3[q] = L.x[2 * (d - 3) + q];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        q0[q] = p0[d - 3 + q];
+        q1[q] = p1[d - 3 + q];
+      }
+    }
+    for (unsigned m = 0; m < (1u << mid); ++m) {
+      double a = acc0;
+      for (int q = 0; q < mid; ++q)
+        a = Genz<double, FAM>::step(a, L.x[2 * (pre + q) + ((m >> q) & 1u)], p0[pre + q],
+                                    p1[pre + q]);
+      if (rest < 3) {
+        Sk[4] += Genz<double, FAM>::finish(a, d);
+        continue;
+      }
+#pragma unroll 1  // (four corners in flight: eight cost 60 registers more)
+      for (int e0 = 0; e0 < 2; ++e0) {
+        const double a0 = Genz<double, FAM>::step(a, e0 ? x3[1] : x3[0], q0[0], q1[0]);
+#pragma unroll
+        for (int e1 = 0; e1 < 2; ++e1) {
+          const double a1 = Genz<double, FAM>::step(a0, x3[2 + e1], q0[1], q1[1]);
+#pragma unroll
+          for (int e2 = 0; e2 < 2; ++e2)
+            Sk[4] += Genz<double, FAM>::finish(
+                Genz<double, FAM>::step(a1, x3[4 + e2], q0[2], q1[2]), d);
+        }
+      }
+    }
+  }
+}
+
+// The split axis of the region whose point values are in f: the arg-max of
+// the fourth differences, the lowest axis on ties (every lane below 16).
+__device__ __forceinline__ int rule_axis(const RuleLambdas &A, int d, int lane, const double *f) {
   double D = -1.0;
   if (lane < d) {
-    const double f0 = sf[w][4 * kMaxDim];
-    const double a2 = sf[w][2 * lane] + sf[w][2 * lane + 1] - 2.0 * f0;
-    const double a3 = sf[w][2 * kMaxDim + 2 * lane] + sf[w][2 * kMaxDim + 2 * lane + 1] - 2.0 * f0;
+    const double f0 = f[4 * kMaxDim];
+    const double a2 = f[2 * lane] + f[2 * lane + 1] - 2.0 * f0;
+    const double a3 = f[2 * kMaxDim + 2 * lane] + f[2 * kMaxDim + 2 * lane + 1] - 2.0 * f0;
     const double ratio = (A.l2 * A.l2) / (A.l3 * A.l3);
     D = fabs(a2 - ratio * a3);
   }
   int best = lane;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
+  for (int o = 1; o < 16; o <<= 1) {  // (lanes below 16 hold every axis)
     const double oD = __shfl_xor(D, o, 64);
     const int ob = __shfl_xor(best, o, 64);
     if (oD > D || (oD == D && ob < best)) {
@@ -217,21 +262,72 @@ __device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, in
       best = ob;
     }
   }
-  if (lane == 0) {
-    double vol = 1.0;
-    for (int j = 0; j < d; ++j) vol *= h[j];
-    const double *w7 = A.w7 + d * 5, *w5 = A.w5 + d * 5;
-    double r7 = 0.0, r5 = 0.0;
+  return best;
+}
+
+// (I7, I5) of a region from its class sums.
+__device__ __forceinline__ double2 rule_values(int d, const double *h, const double (&Sk)[5],
+                                               const double *w7, const double *w5) {
+  double vol = 1.0;
+  for (int j = 0; j < d; ++j) vol *= h[j];
+  double r7 = 0.0, r5 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    r7 += w7[k] * Sk[k];
+    r5 += w5[k] * Sk[k];
+  }
+  return make_double2(vol * r7, vol * r5);
+}
+
+// One region per W wavefronts; returns (I7, err) in the first thread.
+template <int FAM, int W>
+__device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, RuleLds &L,
+                               double (*part)[5]) {
+  const int tid = W == 1 ? threadIdx.x & 63 : threadIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int NT = 64 * W, LB = W == 1 ? 6 : 8;
+  static_assert(NT == 1 << LB, "threads of a region");
+  const int d = S.ndim;
+  if (tid < d) {
+    double cj, hj;
+    child_coord(S, r, tid, &cj, &hj);
+    L.c[tid] = cj;
+    L.h[tid] = hj;
+    // both coordinates of every axis at the corners, formed once per region
+    // (the values rule_point_f forms per point)
+    const double t = A.lam.l5 * hj;
+    L.x[2 * tid] = cj + t;
+    L.x[2 * tid + 1] = cj - t;
+  }
+  sync_region<W>();
+  double Sk[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  rule_points<FAM>(A.lam, d, tid, NT, LB, L, S.par, S.par + kParamRow, Sk);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) Sk[k] = wsum(Sk[k]);
+  if constexpr (W > 1) {
+    if (lane == 0)
+#pragma unroll
+      for (int k = 0; k < 5; ++k) part[w][k] = Sk[k];
+  }
+  sync_region<W>();
+  if (W > 1 && w != 0) return make_double2(0.0, 0.0);
+  if constexpr (W > 1) {
+#pragma unroll
     for (int k = 0; k < 5; ++k) {
-      r7 += w7[k] * Sk[k];
-      r5 += w5[k] * Sk[k];
+      Sk[k] = part[0][k];
+#pragma unroll
+      for (int q = 1; q < W; ++q) Sk[k] += part[q][k];
     }
-    const double I7 = vol * r7, I5 = vol * r5;
-    S.regs.I7[r] = I7;
-    S.regs.I5[r] = I5;
-    S.regs.err[r] = fabs(I7 - I5);
+  }
+  const int best = rule_axis(A.lam, d, lane, L.f);
+  if (lane == 0) {
+    const double2 v = rule_values(d, L.h, Sk, A.w7 + d * 5, A.w5 + d * 5);
+    const double err = fabs(v.x - v.y);
+    S.regs.I7[r] = v.x;
+    S.regs.I5[r] = v.y;
+    S.regs.err[r] = err;
     S.regs.axis[r] = best;
-    return make_double2(I7, fabs(I7 - I5));
+    return make_double2(v.x, err);
   }
   return make_double2(0.0, 0.0);
 }
@@ -260,8 +356,51 @@ __device__ __forceinline__ double lane_point(const double (&c)[D], const double 
   return Genz<double, FAM>::finish(acc, D);
 }
 
-// All the rule points of one region in one lane, in point order (the
-// arithmetic of rule_region's points); returns (I7, err).
+// The corners over the axes [J, D) as the leaves of a tree: acc is the running
+// value over the axes below J.
+template <int FAM, int D, int J>
+__device__ __forceinline__ void corner_tree(double acc, const double (&xp)[D],
+                                            const double (&xm)[D], const double *p0,
+                                            const double *p1, double &s) {
+  if constexpr (J == D) {
+    s += Genz<double, FAM>::finish(acc, D);
+  } else {
+    corner_tree<FAM, D, J + 1>(Genz<double, FAM>::step(acc, xp[J], p0[J], p1[J]), xp, xm, p0, p1,
+                               s);
+    corner_tree<FAM, D, J + 1>(Genz<double, FAM>::step(acc, xm[J], p0[J], p1[J]), xp, xm, p0, p1,
+                               s);
+  }
+}
+
+// Sum over the corners whose signs on the axes below J0 went into acc: a loop
+// over the next axes' signs, the last four axes (at most) as an unrolled tree,
+// so that a corner costs about two steps and not D.
+template <int FAM, int D, int J0>
+__device__ __forceinline__ double corner_sum(double acc, const double (&c)[D],
+                                             const double (&h)[D], const double *p0,
+                                             const double *p1, double l5) {
+  constexpr int R = D - J0, IN = R < 4 ? R : 4, M = R - IN;
+  double xp[D], xm[D];
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const double t = l5 * h[j];
+    xp[j] = c[j] + t;
+    xm[j] = c[j] - t;
+  }
+  double s = 0.0;
+  for (unsigned m = 0; m < (1u << M); ++m) {
+    double a = acc;
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+      a = Genz<double, FAM>::step(a, ((m >> q) & 1u) ? xm[J0 + q] : xp[J0 + q], p0[J0 + q],
+                                  p1[J0 + q]);
+    corner_tree<FAM, D, J0 + M>(a, xp, xm, p0, p1, s);
+  }
+  return s;
+}
+
+// All the rule points of one region in one lane (the arithmetic of
+// rule_region's points); returns (I7, err).
 template <int FAM, int D>
 __device__ double2 rule_region_lane(const RuleArgs &A, const CSeg &S, long long r) {
   const long long cap = S.regs.cap;
@@ -302,17 +441,17 @@ __device__ double2 rule_region_lane(const RuleArgs &A, const CSeg &S, long long 
   double a2[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) {
-    const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.l2);
-    const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.l2);
+    const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.lam.l2);
+    const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.lam.l2);
     s1 += fp;
     s1 += fm;
     a2[i] = fp + fm - 2.0 * f0;
   }
-  const double ratio = (A.l2 * A.l2) / (A.l3 * A.l3);
+  const double ratio = (A.lam.l2 * A.lam.l2) / (A.lam.l3 * A.lam.l3);
 #pragma unroll
   for (int i = 0; i < D; ++i) {
-    const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.l3);
-    const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.l3);
+    const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.lam.l3);
+    const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.lam.l3);
     s2 += fp;
     s2 += fm;
     const double a3 = fp + fm - 2.0 * f0;
@@ -332,21 +471,10 @@ __device__ double2 rule_region_lane(const RuleArgs &A, const CSeg &S, long long 
     for (int jj = i + 1; jj < D; ++jj)
 #pragma unroll
       for (int sg = 0; sg < 4; ++sg)
-        s3 += lane_point<FAM, D>(c, h, p0, p1, phase0, i, sg & 1, jj, (sg >> 1) & 1, A.l4);
+        s3 += lane_point<FAM, D>(c, h, p0, p1, phase0, i, sg & 1, jj, (sg >> 1) & 1, A.lam.l4);
   Sk[3] = s3;
   // class 4: every corner at +-lambda5
-  double s4 = 0.0;
-  for (unsigned sg = 0; sg < (1u << D); ++sg) {
-    double acc = Genz<double, FAM>::init(phase0);
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const double t = A.l5 * h[j];
-      const double x = ((sg >> j) & 1u) ? c[j] - t : c[j] + t;
-      acc = Genz<double, FAM>::step(acc, x, p0[j], p1[j]);
-    }
-    s4 += Genz<double, FAM>::finish(acc, D);
-  }
-  Sk[4] = s4;
+  Sk[4] = corner_sum<FAM, D, 0>(Genz<double, FAM>::init(phase0), c, h, p0, p1, A.lam.l5);
   double vol = 1.0;
 #pragma unroll
   for (int j = 0; j < D; ++j) vol *= h[j];
@@ -369,7 +497,7 @@ __device__ double2 rule_region_lane(const RuleArgs &A, const CSeg &S, long long 
 // (lane l of every wavefront holds region l of the block's 64): wavefront 0
 // takes the centre, classes 1 and 2 and the fourth differences; classes 3
 // (the pairs of axes, in order, dealt round-robin to wavefronts 1-3) and 4
-// (corner sg to wavefront sg mod 4) are shared.  Each wavefront's class sums
+// (the signs of axes 0 and 1 choose the wavefront) are shared.  Each wavefront's class sums
 // go to LDS (sums[w][k][lane]); wavefront 0 adds the four in wavefront order
 // and forms I7, I5, err and the split axis.  Returns (I7, err) in
 // wavefront 0's lanes of live regions.
@@ -419,17 +547,17 @@ __device__ double2 rule_region_quad(const RuleArgs &A, const CSeg &S, long long 
     double a2[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.l2);
-      const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.l2);
+      const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.lam.l2);
+      const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.lam.l2);
       s1 += fp;
       s1 += fm;
       a2[i] = fp + fm - 2.0 * f0;
     }
-    const double ratio = (A.l2 * A.l2) / (A.l3 * A.l3);
+    const double ratio = (A.lam.l2 * A.lam.l2) / (A.lam.l3 * A.lam.l3);
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.l3);
-      const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.l3);
+      const double fp = lane_point<FAM, D>(c, h, p0, p1, phase0, i, false, -1, false, A.lam.l3);
+      const double fm = lane_point<FAM, D>(c, h, p0, p1, phase0, i, true, -1, false, A.lam.l3);
       s2 += fp;
       s2 += fm;
       const double a3 = fp + fm - 2.0 * f0;
@@ -452,22 +580,19 @@ __device__ double2 rule_region_quad(const RuleArgs &A, const CSeg &S, long long 
         if (q % 3 == w - 1)
 #pragma unroll
           for (int sg = 0; sg < 4; ++sg)
-            s3 += lane_point<FAM, D>(c, h, p0, p1, phase0, i, sg & 1, jj, (sg >> 1) & 1, A.l4);
+            s3 += lane_point<FAM, D>(c, h, p0, p1, phase0, i, sg & 1, jj, (sg >> 1) & 1, A.lam.l4);
     Sk[3] = s3;
   }
-  // class 4: the corners at +-lambda5, corner sg to wavefront sg mod 4
-  double s4 = 0.0;
-  for (unsigned sg = (unsigned)w; sg < (1u << D); sg += 4u) {
+  // class 4: the corners at +-lambda5, the signs of axes 0 and 1 to wavefronts
+  {
     double acc = Genz<double, FAM>::init(phase0);
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const double t = A.l5 * h[j];
-      const double x = ((sg >> j) & 1u) ? c[j] - t : c[j] + t;
-      acc = Genz<double, FAM>::step(acc, x, p0[j], p1[j]);
+    for (int j = 0; j < 2; ++j) {
+      const double t = A.lam.l5 * h[j];
+      acc = Genz<double, FAM>::step(acc, ((w >> j) & 1) ? c[j] - t : c[j] + t, p0[j], p1[j]);
     }
-    s4 += Genz<double, FAM>::finish(acc, D);
+    Sk[4] = corner_sum<FAM, D, 2>(acc, c, h, p0, p1, A.lam.l5);
   }
-  Sk[4] = s4;
 #pragma unroll
   for (int k = 0; k < 5; ++k) sums[w][k][lane] = Sk[k];
   __syncthreads();
@@ -596,16 +721,18 @@ __global__ void __launch_bounds__(256) gm_rule_lane_kernel(RuleArgs A) {
   put_row(A.rows, v.x, v.y);
 }
 
-// A wavefront per region, the regions of a launch taken in turn by the grid's
-// wavefronts (a launch has at most kWaveRuleBlocks blocks).
+// W wavefronts per region, the regions of a launch taken in turn by the grid
+// (a launch has at most kWaveRuleBlocks blocks).
+template <int W>
 __global__ void __launch_bounds__(256) gm_rule_kernel(RuleArgs A) {
-  __shared__ double sc[4][kMaxDim], sh[4][kMaxDim];
-  __shared__ double sf[4][4 * kMaxDim + 1];
-  __shared__ double sx[4][2 * kMaxDim];
+  __shared__ RuleLds lds[4 / W];
+  __shared__ double part[4][5];
   if (stopped(A.done) || !open_step(A.rows, A.done)) return;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = W == 1 ? threadIdx.x >> 6 : 0;
+  constexpr int RB = 4 / W;  // regions of a block
   double a = 0.0, b = 0.0;
-  for (long long g = (long long)blockIdx.x * 4 + w; g < A.total; g += (long long)gridDim.x * 4) {
+  for (long long g = (long long)blockIdx.x * RB + w; g < A.total;
+       g += (long long)gridDim.x * RB) {
     CSeg S;
     long long before = 0;
     if (A.nseg == 1) {
@@ -625,17 +752,15 @@ __global__ void __launch_bounds__(256) gm_rule_kernel(RuleArgs A) {
     const long long r = S.first + (g - before);
     double2 v;
     switch (S.family) {
-      case GAUSSIAN: v = rule_region<GAUSSIAN>(A, S, r, w, lane, sc, sh, sf, sx); break;
-      case OSCILLATORY: v = rule_region<OSCILLATORY>(A, S, r, w, lane, sc, sh, sf, sx); break;
-      case PRODUCT_PEAK: v = rule_region<PRODUCT_PEAK>(A, S, r, w, lane, sc, sh, sf, sx); break;
-      case CORNER_PEAK: v = rule_region<CORNER_PEAK>(A, S, r, w, lane, sc, sh, sf, sx); break;
-      default: v = rule_region<C0>(A, S, r, w, lane, sc, sh, sf, sx); break;
+      case GAUSSIAN: v = rule_region<GAUSSIAN, W>(A, S, r, lds[w], part); break;
+      case OSCILLATORY: v = rule_region<OSCILLATORY, W>(A, S, r, lds[w], part); break;
+      case PRODUCT_PEAK: v = rule_region<PRODUCT_PEAK, W>(A, S, r, lds[w], part); break;
+      case CORNER_PEAK: v = rule_region<CORNER_PEAK, W>(A, S, r, lds[w], part); break;
+      default: v = rule_region<C0, W>(A, S, r, lds[w], part); break;
     }
-    a += v.x;  // lane 0 only: the others hold 0
+    a += v.x;  // the region's first thread only: the others hold 0
     b += v.y;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();  // the LDS rows are reused by the next region
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    sync_region<W>();  // the region's LDS is reused by the next one
   }
   put_row(A.rows, a, b);
 }
@@ -644,6 +769,276 @@ __global__ void __launch_bounds__(256) gm_rule_kernel(RuleArgs A) {
 __global__ void __launch_bounds__(256) cuhre_decide_kernel(CRows R, int *done) {
   if (stopped(done)) return;
   (void)open_step(R, done);
+}
+
+namespace {
+
+// The rule on one region per wavefront, for d = D <= 8: lane l takes the points
+// l, l + 64, ..., whose offsets (in half-widths, per axis) it holds in
+// registers for every region it takes, so that a point is D multiplications
+// and additions and the integrand's own steps, with no decoding and no
+// lane-varying branch.  The point values are those of rule_point_f.
+template <int FAM, int D>
+struct WaveRule {
+  static constexpr int NP = (1 << D) + 2 * D * D + 2 * D + 1, PT = (NP + 63) / 64;
+  // first points of the classes 0..4, and the end
+  static constexpr int kFirst[6] = {0, 1, 1 + 2 * D, 1 + 4 * D, 1 + 4 * D + 2 * D * (D - 1), NP};
+  double off[PT][D];
+  double p0[D], p1[D];
+
+  __device__ __forceinline__ WaveRule(const RuleLambdas &A, const double *params, int lane) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      p0[j] = uniform(params[j]);
+      p1[j] = uniform(params[kParamRow + j]);
+    }
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+      const int p = lane + 64 * k;
+      int i = -1, jj = -1;
+      unsigned sgn = 0;
+      double lam = 0.0;
+      if (p >= kFirst[1] && p < kFirst[3]) {  // classes 1 and 2
+        const int q = p - (p < kFirst[2] ? kFirst[1] : kFirst[2]);
+        i = q >> 1;
+        sgn = q & 1;
+        lam = p < kFirst[2] ? A.l2 : A.l3;
+      } else if (p >= kFirst[3] && p < kFirst[4]) {
+        int q = (p - kFirst[3]) >> 2, row = D - 1;
+        sgn = (p - kFirst[3]) & 3;
+        i = 0;
+        for (; q >= row; --row) {
+          q -= row;
+          ++i;
+        }
+        jj = i + 1 + q;
+        lam = A.l4;
+      } else if (p >= kFirst[4]) {
+        sgn = (unsigned)(p - kFirst[4]);
+        lam = A.l5;
+      }
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        const bool corner = p >= kFirst[4];
+        const bool on = corner || j == i || j == jj;
+        const bool neg = corner ? (sgn >> j) & 1u : j == i ? sgn & 1u : (sgn >> 1) & 1u;
+        off[k][j] = !on ? 0.0 : neg ? -lam : lam;
+      }
+    }
+  }
+
+  // The region (c, h): I7 and I5 (in lane 63) and the split axis (in lane 0).
+  __device__ __forceinline__ void eval(const RuleLambdas &A, int lane, const double (&c)[D],
+                                       const double (&h)[D], const double *w7, const double *w5,
+                                       double2 *v, int *axis) const {
+    double Sk[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, f0 = 0.0;
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+      double acc = Genz<double, FAM>::init(p1[0]);
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+        acc = Genz<double, FAM>::step(acc, c[j] + off[k][j] * h[j], p0[j], p1[j]);
+      const double f = Genz<double, FAM>::finish(acc, D);
+      if (k == 0) f0 = f;
+      const int p = lane + 64 * k;
+#pragma unroll
+      for (int q = 0; q < 5; ++q)  // (only classes with points among these 64)
+        if (kFirst[q] < 64 * k + 64 && kFirst[q + 1] > 64 * k)
+          Sk[q] += p >= kFirst[q] && p < kFirst[q + 1] ? f : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 5; ++q) Sk[q] = wave_reduce63_sum(Sk[q]);
+    // fourth differences: lane j < D of axis j (its points are the lanes' first)
+    const int j = lane & 7;
+    const double fc = __shfl(f0, 0, 64);
+    const double a2 = __shfl(f0, 1 + 2 * j, 64) + __shfl(f0, 2 + 2 * j, 64) - 2.0 * fc;
+    const double a3 =
+        __shfl(f0, 1 + 2 * D + 2 * j, 64) + __shfl(f0, 2 + 2 * D + 2 * j, 64) - 2.0 * fc;
+    double dm = j < D ? fabs(a2 - (A.l2 * A.l2) / (A.l3 * A.l3) * a3) : -1.0;
+    int best = j;
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+      const double od = __shfl_xor(dm, o, 64);
+      const int ob = __shfl_xor(best, o, 64);
+      if (od > dm || (od == dm && ob < best)) {
+        dm = od;
+        best = ob;
+      }
+    }
+    *axis = best;
+    double vol = 1.0, r7 = 0.0, r5 = 0.0;
+#pragma unroll
+    for (int q = 0; q < D; ++q) vol *= h[q];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      r7 += w7[q] * Sk[q];
+      r5 += w5[q] * Sk[q];
+    }
+    *v = make_double2(vol * r7, vol * r5);
+  }
+};
+
+}  // namespace
+
+// One integral (A.one), d = D <= 8, a wavefront per region: the launches too
+// small for a lane per region.  Latency: 64 to 256 regions take 6.8 us at d = 3
+// and 7.6 at d = 6, against 9.6 and 12 with the points decoded per region and
+// LDS sums.
+template <int FAM, int D>
+__global__ void __launch_bounds__(256) gm_rule_wave_kernel(RuleArgs A) {
+  if (stopped(A.done) || !open_step(A.rows, A.done)) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const long long g = (long long)blockIdx.x * 4 + w;
+  double2 t = make_double2(0.0, 0.0);
+  if (g < A.total) {
+    const CSeg &S = A.one;
+    const long long r = S.first + g, cap = S.regs.cap;
+    double c[D], h[D];
+    if (!S.children) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        c[j] = S.regs.c[j * cap + r];
+        h[j] = S.regs.h[j * cap + r];
+      }
+    } else {  // a child: formed from its parent, as child_coord does per axis
+      const long long p = S.parent ? S.parent[g >> 1] : S.pbase + (g >> 1);
+      const int ax = S.regs.axis[p];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        c[j] = S.regs.c[j * cap + p];
+        h[j] = S.regs.h[j * cap + p];
+      }
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+        if (j == ax) {
+          h[j] = h[j] / 2.0;
+          c[j] = (g & 1) ? c[j] + h[j] : c[j] - h[j];
+        }
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+        if (lane == j) {
+          S.regs.c[j * cap + r] = c[j];
+          S.regs.h[j * cap + r] = h[j];
+        }
+      if (S.retire && lane == 0 && !(g & 1)) S.regs.err[p] = -1.0;
+    }
+    const WaveRule<FAM, D> rule(A.lam, S.par, lane);
+    double2 v;
+    int axis;
+    rule.eval(A.lam, lane, c, h, A.w7 + D * 5, A.w5 + D * 5, &v, &axis);
+    if (lane == 0) S.regs.axis[r] = axis;
+    if (lane == 63) {
+      const double err = fabs(v.x - v.y);
+      S.regs.I7[r] = v.x;
+      S.regs.I5[r] = v.y;
+      S.regs.err[r] = err;
+      t = make_double2(v.x, err);
+    }
+  }
+  put_row(A.rows, t.x, t.y);
+}
+
+// The first states of a run, while every region splits: one workgroup takes
+// the root and A.doublings doublings of the live regions (at most
+// kGrowRegions), each generation's regions in LDS and a wavefront per region.
+// A launch of its own costs a generation about 10 us, nearly all of it the
+// launch and dependent trips to memory that other dies wrote; a generation
+// here has none.  Up to 32 regions (six states): 19 us at d = 3, 21 at d = 6.
+constexpr int kGrowThreads = 512;
+
+template <int FAM, int D>
+__global__ void __launch_bounds__(kGrowThreads) cuhre_grow_kernel(GrowArgs A) {
+  constexpr int NW = kGrowThreads / 64;
+  __shared__ double sc[2][kGrowRegions][D], sh[2][kGrowRegions][D];
+  __shared__ double s7[kGrowRegions], s5[kGrowRegions];
+  __shared__ int sax[kGrowRegions];
+  __shared__ int s_code;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const WaveRule<FAM, D> rule(A.lam, A.params, lane);
+  double w7[5], w5[5];
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    w7[q] = uniform(A.w7[D * 5 + q]);
+    w5[q] = uniform(A.w5[D * 5 + q]);
+  }
+  if (tid < D) sc[0][0][tid] = sh[0][0][tid] = 0.5;
+  if (tid == 0) *A.done = 0;
+  int n = 1, cur = 0;
+  long long base = 0;  // position of the generation's first region
+  __syncthreads();
+  for (int g = 0;; ++g) {
+    for (int r = w; r < n; r += NW) {
+      double c[D], h[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        c[j] = sc[cur][r][j];
+        h[j] = sh[cur][r][j];
+      }
+      double2 v;
+      int axis;
+      rule.eval(A.lam, lane, c, h, w7, w5, &v, &axis);
+      if (lane == 0) sax[r] = axis;
+      if (lane == 63) {
+        s7[r] = v.x;
+        s5[r] = v.y;
+      }
+    }
+    __syncthreads();
+    // the state's totals and outcome
+    if (w == 0) {
+      const double I = wave_reduce63_sum(lane < n ? s7[lane] : 0.0);
+      const double E = wave_reduce63_sum(lane < n ? fabs(s7[lane] - s5[lane]) : 0.0);
+      if (lane == 63) {
+        int code = 0;
+        if (g < A.doublings) {
+          CStop stop = A.stop;
+          stop.neval = A.np * (2ll * n - 1);
+          code = stop_code(I, E, stop);
+          if (code || g == A.doublings - 1) {
+            A.slot[0] = I;
+            A.slot[1] = E;
+            __hip_atomic_store((unsigned long long *)(A.slot + 2),
+                               ((unsigned long long)g << 8) | (unsigned long long)code,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (code) *A.done = 1;
+          }
+        } else {  // the next launch decides on these
+          A.row[0] = I;
+          A.row[A.stride] = E;
+        }
+        s_code = code;
+      }
+    }
+    if (g == A.doublings) break;
+    // form the children (not used if the state ends the run)
+    for (int e = tid; e < 2 * n * D; e += kGrowThreads) {
+      const int k = e / D, j = e % D, p = k >> 1;
+      double c = sc[cur][p][j], h = sh[cur][p][j];
+      if (j == sax[p]) {
+        h = h / 2.0;
+        c = (k & 1) ? c + h : c - h;
+      }
+      sc[cur ^ 1][k][j] = c;
+      sh[cur ^ 1][k][j] = h;
+    }
+    __syncthreads();
+    if (s_code) return;
+    if (tid < n) A.R.err[base + tid] = -1.0;  // the parents are retired
+    base += n;
+    n *= 2;
+    cur ^= 1;
+  }
+  for (int e = tid; e < n * D; e += kGrowThreads) {
+    const int k = e % n, j = e / n;
+    A.R.c[j * A.R.cap + base + k] = sc[cur][k][j];
+    A.R.h[j * A.R.cap + base + k] = sh[cur][k][j];
+  }
+  if (tid < n) {
+    A.R.I7[base + tid] = s7[tid];
+    A.R.I5[base + tid] = s5[tid];
+    A.R.err[base + tid] = fabs(s7[tid] - s5[tid]);
+    A.R.axis[base + tid] = sax[tid];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1128,25 +1523,56 @@ long long step_rows(long long cap) {
   return scratch_blocks(cap) + std::max<long long>((cap + 63) / 64, kWaveRuleBlocks);
 }
 
+enum RuleSplit { LANE, LANE4, WAVE };  // a lane, a lane of four wavefronts, a wavefront per region
+
 template <int FAM, int D>
-static void launch_rule_lane_dd(const RuleArgs &A, unsigned grid, bool one_lane, hipStream_t s) {
-  if (one_lane)
+static void launch_rule_lane_dd(const RuleArgs &A, unsigned grid, RuleSplit split, hipStream_t s) {
+  if (split == LANE)
     hipLaunchKernelGGL((gm_rule_lane1_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
+  else if (split == WAVE)
+    hipLaunchKernelGGL((gm_rule_wave_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
   else
     hipLaunchKernelGGL((gm_rule_lane_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
 }
 
 template <int FAM>
-static void launch_rule_lane_d(const RuleArgs &A, unsigned grid, bool one_lane, hipStream_t s) {
+static void launch_rule_lane_d(const RuleArgs &A, unsigned grid, RuleSplit split,
+                               hipStream_t s) {
   switch (A.one.ndim) {
-    case 2: launch_rule_lane_dd<FAM, 2>(A, grid, one_lane, s); break;
-    case 3: launch_rule_lane_dd<FAM, 3>(A, grid, one_lane, s); break;
-    case 4: launch_rule_lane_dd<FAM, 4>(A, grid, one_lane, s); break;
-    case 5: launch_rule_lane_dd<FAM, 5>(A, grid, one_lane, s); break;
-    case 6: launch_rule_lane_dd<FAM, 6>(A, grid, one_lane, s); break;
-    case 7: launch_rule_lane_dd<FAM, 7>(A, grid, one_lane, s); break;
-    default: launch_rule_lane_dd<FAM, 8>(A, grid, one_lane, s); break;
+    case 2: launch_rule_lane_dd<FAM, 2>(A, grid, split, s); break;
+    case 3: launch_rule_lane_dd<FAM, 3>(A, grid, split, s); break;
+    case 4: launch_rule_lane_dd<FAM, 4>(A, grid, split, s); break;
+    case 5: launch_rule_lane_dd<FAM, 5>(A, grid, split, s); break;
+    case 6: launch_rule_lane_dd<FAM, 6>(A, grid, split, s); break;
+    case 7: launch_rule_lane_dd<FAM, 7>(A, grid, split, s); break;
+    default: launch_rule_lane_dd<FAM, 8>(A, grid, split, s); break;
   }
+}
+
+template <int FAM>
+static void launch_grow_d(const GrowArgs &A, hipStream_t s) {
+  const dim3 grid(1), block(kGrowThreads);
+  switch (A.d) {
+    case 2: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 2>), grid, block, 0, s, A); break;
+    case 3: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 3>), grid, block, 0, s, A); break;
+    case 4: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 4>), grid, block, 0, s, A); break;
+    case 5: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 5>), grid, block, 0, s, A); break;
+    case 6: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 6>), grid, block, 0, s, A); break;
+    case 7: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 7>), grid, block, 0, s, A); break;
+    default: hipLaunchKernelGGL((cuhre_grow_kernel<FAM, 8>), grid, block, 0, s, A); break;
+  }
+}
+
+hipError_t launch_grow(const GrowArgs &A, int family, hipStream_t s) {
+  if (A.d > kGrowMaxDim) return hipErrorInvalidValue;
+  switch (family) {
+    case GAUSSIAN: launch_grow_d<GAUSSIAN>(A, s); break;
+    case OSCILLATORY: launch_grow_d<OSCILLATORY>(A, s); break;
+    case PRODUCT_PEAK: launch_grow_d<PRODUCT_PEAK>(A, s); break;
+    case CORNER_PEAK: launch_grow_d<CORNER_PEAK>(A, s); break;
+    default: launch_grow_d<C0>(A, s); break;
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t s) {
@@ -1154,38 +1580,51 @@ hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t
   return hipGetLastError();
 }
 
-// A lane per region needs enough regions to fill the device; below that,
-// and above 8 dimensions (the registers a lane holds grow with d, and the
-// 2^d corners with it), a wavefront per region.
-static bool lane_rule(const RuleArgs &A) {
-  return A.nseg == 1 && A.one.ndim <= kLaneRuleMaxDim && A.total >= kLaneRuleMinRegions;
+// One integral of at most 8 dimensions: a lane per region from
+// kOneLaneRuleMinRegions on, where a wavefront per SIMD and more fill the
+// device, a lane of each of four wavefronts from kLaneRuleMinRegions, a
+// wavefront per region below.  Above 8 dimensions (the registers a lane holds
+// grow with d, and the 2^d corners with it) and for launches over several
+// integrals, a workgroup or a wavefront per region.
+static bool dim_rule(const RuleArgs &A) {
+  return A.nseg == 1 && A.one.ndim <= kLaneRuleMaxDim;
 }
 
-// From this many regions on, one lane per region fills the device (a wavefront
-// per SIMD and more) without the four-way split's combine.
-static bool one_lane_rule(const RuleArgs &A) { return A.total >= kOneLaneRuleMinRegions; }
+static RuleSplit rule_split(const RuleArgs &A) {
+  return A.total >= kOneLaneRuleMinRegions ? LANE
+         : A.total >= kLaneRuleMinRegions  ? LANE4
+                                           : WAVE;
+}
 
 long long rule_blocks(const RuleArgs &A) {
   if (A.total <= 0) return 0;
-  if (lane_rule(A)) return one_lane_rule(A) ? (A.total + 255) / 256 : (A.total + 63) / 64;
+  if (dim_rule(A)) {
+    const long long per[3] = {256, 64, 4};  // regions of a block
+    const long long n = per[rule_split(A)];
+    return (A.total + n - 1) / n;
+  }
+  if (A.total <= kBlockRuleRegions) return A.total;
   return std::min<long long>((A.total + 3) / 4, kWaveRuleBlocks);
 }
 
 hipError_t launch_rule(const RuleArgs &A, hipStream_t s) {
   const long long grid = rule_blocks(A);
   if (grid <= 0) return hipSuccess;
-  if (lane_rule(A)) {
-    const bool one = one_lane_rule(A);
+  if (dim_rule(A)) {
+    const RuleSplit q = rule_split(A);
     switch (A.one.family) {
-      case GAUSSIAN: launch_rule_lane_d<GAUSSIAN>(A, (unsigned)grid, one, s); break;
-      case OSCILLATORY: launch_rule_lane_d<OSCILLATORY>(A, (unsigned)grid, one, s); break;
-      case PRODUCT_PEAK: launch_rule_lane_d<PRODUCT_PEAK>(A, (unsigned)grid, one, s); break;
-      case CORNER_PEAK: launch_rule_lane_d<CORNER_PEAK>(A, (unsigned)grid, one, s); break;
-      default: launch_rule_lane_d<C0>(A, (unsigned)grid, one, s); break;
+      case GAUSSIAN: launch_rule_lane_d<GAUSSIAN>(A, (unsigned)grid, q, s); break;
+      case OSCILLATORY: launch_rule_lane_d<OSCILLATORY>(A, (unsigned)grid, q, s); break;
+      case PRODUCT_PEAK: launch_rule_lane_d<PRODUCT_PEAK>(A, (unsigned)grid, q, s); break;
+      case CORNER_PEAK: launch_rule_lane_d<CORNER_PEAK>(A, (unsigned)grid, q, s); break;
+      default: launch_rule_lane_d<C0>(A, (unsigned)grid, q, s); break;
     }
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(gm_rule_kernel, dim3((unsigned)grid), dim3(256), 0, s, A);
+  if (A.total <= kBlockRuleRegions)
+    hipLaunchKernelGGL(gm_rule_kernel<4>, dim3((unsigned)grid), dim3(256), 0, s, A);
+  else
+    hipLaunchKernelGGL(gm_rule_kernel<1>, dim3((unsigned)grid), dim3(256), 0, s, A);
   return hipGetLastError();
 }
 

@@ -11,6 +11,7 @@
 #include "cuhre_engine.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <vector>
 
@@ -143,7 +144,7 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
   return CCUBA_OK;
 }
 
-int CuhreRun::start(const CuhreSpec &spec, hipStream_t s) {
+int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   if (validate_cuhre(spec)) return CCUBA_EINVAL;
   spec_ = spec;
   const int d = spec.ndim;
@@ -207,11 +208,17 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s) {
   CCUBA_HIP(hipMemcpyAsync(params_.p, hp64_, sizeof(hp64_), hipMemcpyHostToDevice, s));
   CCUBA_HIP(hipMemcpyAsync(w7_.p, T.w7, sizeof(T.w7), hipMemcpyHostToDevice, s));
   CCUBA_HIP(hipMemcpyAsync(w5_.p, T.w5, sizeof(T.w5), hipMemcpyHostToDevice, s));
+  rooted_ = false;
+  return root ? launch_root(s) : CCUBA_OK;
+}
+
+int CuhreRun::launch_root(hipStream_t s) {
   // root region [0,1]^d: centre 1/2, half-width 1/2, id 0; the stop flag clear
-  CCUBA_HIP(launch_root_clear(R_, d, stop_.p, s));
+  rooted_ = true;
+  CCUBA_HIP(launch_root_clear(R_, spec_.ndim, stop_.p, s));
   CSeg seg{};
-  seg.ndim = d;
-  seg.family = spec.family;
+  seg.ndim = spec_.ndim;
+  seg.family = spec_.family;
   seg.par = params_.p;
   seg.first = 0;
   seg.count = 1;
@@ -222,6 +229,20 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s) {
   const CRows rows{nullptr, 0, tot_.p, 0, rows_stride_, nullptr, 0, CStop{}};
   rows_par_ = 0;
   return launch_rule_alone(seg, s, &rows, &rows_n_);
+}
+
+// (A generation of kGrowRegions regions takes one workgroup no longer than a
+// launch of its own takes.)
+int CuhreRun::grow_doublings() const {
+  if (spec_.ndim > kGrowMaxDim) return -1;
+  int g = 0;
+  for (long long n = 1; 2 * n <= kGrowRegions; n *= 2, ++g) {
+    const long long neval = np_ * (2 * n - 1);  // of the state of n regions
+    if (spec_.batch / 2 < n || spec_.maxeval < neval ||
+        (spec_.maxeval - neval) / (2 * np_) < n || 4 * n - 1 > cap_)
+      break;
+  }
+  return g;
 }
 
 int CuhreRun::launch_rule_alone(const CSeg &seg, hipStream_t s, const CRows *rows,
@@ -259,10 +280,7 @@ int launch_rule_segments(ccuba_ctx *ctx, const CSeg *segs, int nseg, DevBuf<CSeg
   A.w7 = w7_dev;
   A.w5 = w5_dev;
   A.done = done;
-  A.l2 = T.l2;
-  A.l3 = T.l3;
-  A.l4 = T.l4;
-  A.l5 = T.l5;
+  A.lam = RuleLambdas{T.l2, T.l3, T.l4, T.l5};
   if (rows) A.rows = *rows;
   if (blocks) *blocks = rule_blocks(A);
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -405,7 +423,8 @@ int CuhreRun::run(hipStream_t s) {
   auto outcome = [&](int t) {
     return poll_outcome(host_slots + slot(t) + 2, (unsigned long long)t, s);
   };
-  // finish with state q, whose outcome (code) ended the run
+  // finish with the state of plan p, whose totals are in slot q's place and
+  // whose outcome (code) ended the run
   auto finish = [&](const Plan &p, int q, int code) -> int {
     CCUBA_HIP(hipStreamSynchronize(s));  // queued launches run empty; the last ones end
     n_ = p.n;
@@ -441,7 +460,75 @@ int CuhreRun::run(hipStream_t s) {
     return true;
   };
   Plan prev{};
-  for (int t = 0;; ++t) {
+  // The first states, while every region splits, in one launch: it ends at
+  // state t0, or the run ended at an earlier one.
+  const int t0 = rooted_ ? -1 : grow_doublings();
+  if (t0 < 0) {
+    int rc;
+    if (!rooted_ && (rc = launch_root(s))) return rc;
+  } else {
+    const GMTables &T = gm_tables();
+    GrowArgs G{};
+    G.R = R_;
+    G.d = spec_.ndim;
+    G.doublings = t0;
+    G.params = params_.p;
+    G.w7 = w7_.p;
+    G.w5 = w5_.p;
+    G.lam = RuleLambdas{T.l2, T.l3, T.l4, T.l5};
+    G.np = np_;
+    G.stop = CStop{spec_.epsrel, spec_.epsabs, spec_.mineval, 0};
+    G.row = tot_.p;
+    G.stride = rows_stride_;
+    G.slot = dev_slots + slot(std::max(0, t0 - 1));
+    G.done = stop_.p;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx_->profile) {  // (timed as the rule launches are)
+      CCUBA_HIP(hipEventCreate(&e0));
+      CCUBA_HIP(hipEventCreate(&e1));
+      CCUBA_HIP(hipEventRecord(e0, s));
+    }
+    CCUBA_HIP(launch_grow(G, spec_.family, s));
+    if (ctx_->profile) {
+      CCUBA_HIP(hipEventRecord(e1, s));
+      CCUBA_HIP(hipEventSynchronize(e1));
+      float ms = 0;
+      CCUBA_HIP(hipEventElapsedTime(&ms, e0, e1));
+      ctx_->stats.rule_launches += 1;
+      ctx_->stats.rule_ms += ms;
+      ctx_->stats.rule_evals += np_ * ((2ll << t0) - 1);
+      (void)hipEventDestroy(e0);
+      (void)hipEventDestroy(e1);
+    }
+    rooted_ = true;
+    rows_par_ = 0;
+    rows_n_ = 1;
+    n_ = 1ll << t0;
+    next_id_ = 2 * n_ - 1;
+    neval_ = np_ * next_id_;
+    batches_ = t0;
+  }
+  // learn how the first launch's states ended, as learn() does
+  auto learn_grown = [&](int *rc) -> bool {
+    const int q = t0 - 1;
+    const volatile unsigned long long *w = host_word(host_slots + slot(q) + 2);
+    const auto begin = std::chrono::steady_clock::now();
+    for (unsigned spin = 0; *w == ~0ull; ++spin)
+      if ((spin & 4095u) == 4095u &&
+          std::chrono::steady_clock::now() - begin > std::chrono::seconds(1)) {
+        if (hipStreamSynchronize(s) != hipSuccess || *w == ~0ull) {
+          *rc = CCUBA_EHIP;
+          return true;
+        }
+      }
+    known = q;
+    const int state = (int)(*w >> 8), code = (int)(*w & 0xFFull);
+    if (code == 0) return false;
+    const long long n = 1ll << state;
+    *rc = finish(Plan{n, np_ * (2 * n - 1), 2 * n - 1, state}, q, code);
+    return true;
+  };
+  for (int t = std::max(0, t0);; ++t) {
     const Plan cur{n_, neval_, next_id_, batches_};
     const CStop stop{spec_.epsrel, spec_.epsabs, spec_.mineval, neval_};
     // this state's rows; the step's first launch decides on them
@@ -460,7 +547,7 @@ int CuhreRun::run(hipStream_t s) {
     if (grow) {
       // the store must grow (a synchronisation and a copy; the rows move
       // too): only for a step known to run, so learn steps t - 1 and t first
-      if (t - 1 > known && learn(t - 1, prev, &rc)) return rc;
+      if (t - 1 > known && (t == t0 ? learn_grown(&rc) : learn(t - 1, prev, &rc))) return rc;
       if (learn(t, cur, &rc)) return rc;
       if ((rc = ensure(next_id_ + 2 * K, s))) return rc < 0 ? rc : CCUBA_EHIP;
     }
@@ -486,7 +573,7 @@ int CuhreRun::run(hipStream_t s) {
       pendK_ = K;
       commit_pending();
     }
-    if (t - 1 > known && learn(t - 1, prev, &rc)) return rc;
+    if (t - 1 > known && (t == t0 ? learn_grown(&rc) : learn(t - 1, prev, &rc))) return rc;
     if (K <= 0) {  // out of budget after step t, unless its totals ended it first
       if (t > known && learn(t, cur, &rc)) return rc;
       return finish(cur, t, 0);  // fail 1

@@ -26,8 +26,9 @@ const GMTables &gm_tables();
 class CuhreRun {
  public:
   explicit CuhreRun(ccuba_ctx *ctx) : ctx_(ctx) {}
-  // Allocate, evaluate the root region (asynchronous).
-  int start(const CuhreSpec &spec, hipStream_t s);
+  // Allocate and upload the constants; with root, evaluate the root region
+  // (asynchronous; run() does so itself otherwise).
+  int start(const CuhreSpec &spec, hipStream_t s, bool root = true);
   // Totals of the current leaves into the device result (asynchronous).
   int launch_totals(hipStream_t s);
   // After the totals are read: decide, and if work remains select + split.
@@ -79,9 +80,14 @@ class CuhreRun {
   // live regions [next_id_ - n_, next_id_) when all split and they are
   // contiguous, else from the positions launch_split wrote.
   CSeg children_segment(long long K, bool from_range) const;
+  int launch_root(hipStream_t s);
+  // Doublings of the live regions that one launch takes from the root on (-1:
+  // not even the root).
+  int grow_doublings() const;
   ccuba_ctx *ctx_;
   CuhreSpec spec_;
   // n_ live regions among the next_id_ of the store (positions are ids)
+  bool rooted_ = false;  // the root has been evaluated (n_, neval_ count it)
   long long np_ = 0, n_ = 0, next_id_ = 1, neval_ = 0, cap_ = 0, pendK_ = 0;
   int fail_ = 1, batches_ = 0;
   bool done_ = false;

@@ -27,6 +27,7 @@
 #include "philox.h"
 #include "refine.h"
 #include "suave.h"
+#include "wave.h"
 
 namespace ccuba {
 
@@ -311,31 +312,6 @@ __device__ __forceinline__ double max_num(double a, double b) {
   double r;
   asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
-}
-
-// A reduction over the wavefront by DPP, its result in lane 63: the row
-// shifts leave each row's result in its lane 15, the row broadcasts carry it
-// on.  A lane without a source takes the identity.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_or(double v, double identity) {
-  const long long b = __double_as_longlong(v), z = __double_as_longlong(identity);
-  const int lo = __builtin_amdgcn_update_dpp((int)z, (int)b, CTRL, ROWS, 0xf, false);
-  const int hi =
-      __builtin_amdgcn_update_dpp((int)(z >> 32), (int)(b >> 32), CTRL, ROWS, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-template <typename OP>
-__device__ __forceinline__ double wave_reduce63(double v, double identity, OP op) {
-  v = op(v, dpp_or<0x111, 0xf>(v, identity));  // row_shr:1
-  v = op(v, dpp_or<0x112, 0xf>(v, identity));  // row_shr:2
-  v = op(v, dpp_or<0x114, 0xf>(v, identity));  // row_shr:4
-  v = op(v, dpp_or<0x118, 0xf>(v, identity));  // row_shr:8
-  v = op(v, dpp_or<0x142, 0xa>(v, identity));  // row_bcast:15 into rows 1 and 3
-  v = op(v, dpp_or<0x143, 0xc>(v, identity));  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-__device__ __forceinline__ double wave_reduce63_sum(double v) {
-  return wave_reduce63(v, 0.0, [](double a, double b) { return a + b; });
 }
 
 __device__ __forceinline__ double p1_merge(int q, double x, double y) {
@@ -713,18 +689,6 @@ __global__ void __launch_bounds__(256) suave_split_kernel(SuaveArgs A, int R, lo
     Gu[c * row + k] = sOut[1][k];
   }
 }
-
-namespace {
-
-// a value that is the same in every lane, in scalar registers
-__device__ __forceinline__ double uniform(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readfirstlane((int)b);
-  const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-}  // namespace
 
 // DoSample of every child: one workgroup per (tile of A.tile points, child).
 // Bound by VALU issue, with the LDS (a cell read and an FP64 add per

@@ -69,3 +69,21 @@ def test_suave_converging_run_matches_oracle(cc, ctx):
     # the run ends on its accuracy while the next step's statistics are queued
     _suave_both(cc, ctx, W.PRODUCT_PEAK, 3, seed=3, nnew=2000, nbins=32, nsplit=4, flatness=5.0,
                 epsrel=2e-3, maxeval=10**6)
+
+
+@pytest.mark.parametrize("fam,d,kw", [
+    (W.GAUSSIAN, 2, dict(epsrel=1e-3, maxeval=10**6)),            # ends among the first states
+    (W.CORNER_PEAK, 3, dict(epsrel=1e-30, maxeval=33 * 20)),      # the budget ends them
+    (W.C0, 4, dict(epsrel=1e-30, maxeval=57 * 300, max_regions_per_batch=64)),  # the batch does
+    (W.PRODUCT_PEAK, 5, dict(epsrel=1e-6, maxeval=10**6, max_regions_per_batch=2)),
+    (W.OSCILLATORY, 10, dict(epsrel=1e-30, maxeval=1245 * 63)),   # corners beyond a wavefront
+    (W.GAUSSIAN, 13, dict(epsrel=1e-30, maxeval=8557 * 7)),       # one doubling
+    (W.C0, 15, dict(epsrel=1e-30, maxeval=33249 * 5)),            # no shared first launch
+    (W.GAUSSIAN, 3, dict(epsrel=1e-3, mineval=33 * 40, maxeval=10**6))])
+def test_cuhre_first_states_match_oracle(cc, ctx, fam, d, kw):
+    a, u = W.genz_params(fam, d, 60 + d)
+    g = cc.cuhre(fam, a, u, ctx=ctx, **kw)
+    o = O.cuhre(O.genz(fam, a, u), d, **kw)
+    assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
+    assert abs(g["error"] - o["error"]) <= 1e-10 * o["error"] + 1e-14 * abs(o["integral"])
