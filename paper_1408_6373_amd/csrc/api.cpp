@@ -150,6 +150,12 @@ int pinned_block(ccuba_ctx *ctx, double **host, double **dev) {
   return CCUBA_OK;
 }
 
+int second_stream(ccuba_ctx *ctx) {
+  if (!ctx->stream2)
+    CCUBA_HIP(hipStreamCreateWithFlags(&ctx->stream2, hipStreamNonBlocking));
+  return CCUBA_OK;
+}
+
 int poll_outcome(double *slot, unsigned long long seq, hipStream_t s) {
   const volatile unsigned long long *word = host_word(slot);
   const auto t0 = std::chrono::steady_clock::now();
@@ -246,7 +252,6 @@ int ccuba_init(ccuba_ctx **ctx, int device, size_t hbm_budget) {
   }
   c->budget = hbm_budget;
   if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) return CCUBA_EHIP;
-  if (hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking) != hipSuccess) return CCUBA_EHIP;
   if (set_kernel_limits() != hipSuccess) return CCUBA_EHIP;
   // the allocation-free entry point's scratch: its address on this device
   if (noalloc_init(device) != CCUBA_OK) return CCUBA_EHIP;
@@ -587,30 +592,31 @@ int ccuba_vegas_ex(ccuba_ctx **ctxp, int ndim, int ncomp, const ccuba_integrand 
 namespace {
 int vegas_results(ccuba_ctx *ctx, VegasEngine &eng, long long *neval, int *fail,
                   double integral[], double error[], double prob[], ccuba_vegas_trace *trace) {
-  int rc;
-  std::vector<VState> st;
-  if ((rc = eng.read_states(st, ctx->stream))) return rc;
-  *neval = st[0].neval;
-  *fail = st[0].fail;
-  integral[0] = st[0].integral;
-  error[0] = st[0].error;
-  prob[0] = st[0].prob;
+  VState st;
+  const bool history = trace && (trace->iter_I || trace->iter_var);
+  int rc = eng.read_results(st, history ? trace->iter_I : nullptr,
+                            history ? trace->iter_var : nullptr, history ? trace->max_iter : 0,
+                            trace ? trace->grid : nullptr, ctx->stream);
+  if (rc) return rc;
+  *neval = st.neval;
+  *fail = st.fail;
+  integral[0] = st.integral;
+  error[0] = st.error;
+  prob[0] = st.prob;
   if (trace) {
-    trace->n_iter = st[0].T;
-    trace->chi2 = st[0].chi2;
-    trace->dof = st[0].dof;
-    const int n = std::min(trace->max_iter, st[0].T);
-    if (n > 0 && (trace->iter_I || trace->iter_var))
-      if ((rc = eng.read_history(0, n, trace->iter_I, trace->iter_var, ctx->stream))) return rc;
-    if (trace->grid)
-      if ((rc = eng.read_grid(0, trace->grid, ctx->stream))) return rc;
+    trace->n_iter = st.T;
+    trace->chi2 = st.chi2;
+    trace->dof = st.dof;
   }
   return CCUBA_OK;
 }
 
 int vegas_finish(ccuba_ctx *ctx, VegasEngine &eng, long long *neval, int *fail,
                  double integral[], double error[], double prob[], ccuba_vegas_trace *trace) {
-  const int rc = eng.run(ctx->stream);
+  eng.set_alone();
+  // (the results are read after the stream has drained)
+  int rc = eng.launch_run(ctx->stream);
+  if (rc == CCUBA_OK && ctx->profile) rc = eng.finish_run(ctx->stream);
   if (rc) return rc;
   return vegas_results(ctx, eng, neval, fail, integral, error, prob, trace);
 }
@@ -753,7 +759,7 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   static_assert(sizeof(VJob) <= 256 && sizeof(VState) <= 256 &&
                     2 * kParamRow * sizeof(double) <= 256 && 2 * kParamRow * sizeof(float) <= 256,
                 "the scratch header's slots");
-  static_assert(sizeof(NoallocSetup) <= 4096, "kernel arguments");
+  static_assert(sizeof(JobSetup) <= 4096, "kernel arguments");
   const long long o_st = 256, o_end = 512, o_p64 = 768, o_p32 = 1024, o_hsum = 1280;
   const long long o_rows = o_hsum + a256(row);
   const long long avail = (long long)kNoallocScratchBytes - o_rows - 1024;
@@ -775,7 +781,7 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   const long long o_tsums = o_rows, o_thist = o_tsums + a256(nt * 16);
   const long long o_gsums = o_thist + a256(nt * dN * 8), o_ghist = o_gsums + a256(ng * 16);
 
-  NoallocSetup S{};
+  JobSetup S{};
   VJob &J = S.job;
   J.ndim = ndim;
   J.nbins = nbins;
@@ -810,7 +816,7 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   S.p64_dst = (double *)(base + o_p64);
   S.p32_dst = (float *)(base + o_p32);
   S.ends_dst = (long long *)(base + o_end);
-  CCUBA_HIP(launch_noalloc_setup(S, s));
+  CCUBA_HIP(launch_job_setup(S, s));
 
   VegasArgs A{};
   A.jobs = S.job_dst;
@@ -1050,6 +1056,7 @@ int run_halves(ccuba_ctx *ctx, const std::vector<VegasSpec> &h0,
                std::vector<std::pair<double, double>> &iv) {
   VegasEngine e0(ctx), e1(ctx);
   int rc;
+  if ((rc = second_stream(ctx))) return rc;
   if ((rc = e0.setup(h0, h0.size() == 1, ctx->stream))) return rc;
   if ((rc = e1.setup(h1, h1.size() == 1, ctx->stream2))) return rc;
   e0.set_time_reference(ref);
@@ -1157,6 +1164,7 @@ int ccuba_vegas_batch(ccuba_ctx *ctx, int njobs, const ccuba_job jobs[], ccuba_r
     hipEvent_t ref = nullptr;
     std::vector<std::pair<double, double>> iv;
     if (ctx->profile) {
+      if ((rc = second_stream(ctx))) return rc;
       CCUBA_HIP(hipEventCreate(&ref));
       if (hipEventRecord(ref, ctx->stream) != hipSuccess ||
           hipStreamWaitEvent(ctx->stream2, ref, 0) != hipSuccess) {

@@ -25,7 +25,8 @@ struct ccuba_ctx {
   size_t budget = 0;                // bytes the context may hold on the device
   std::atomic<size_t> used{0};      // bytes currently held
   hipStream_t stream = nullptr;     // the context's own stream (default priority)
-  // a second stream (default priority) for the second half of a Vegas batch
+  // a second stream (default priority) for the second half of a Vegas batch,
+  // made on first use (second_stream)
   hipStream_t stream2 = nullptr;
   ccuba::VegasTune tune[2];         // per precision: [FP64], [FP32]
   int use_graph = 1;
@@ -45,12 +46,12 @@ struct ccuba_ctx {
   int engine_cache = 1;
   // DoSample kernels compiled at run time for callers' device integrands
   ccuba::RtcCache *rtc = nullptr;
-  // a small mapped pinned host block (host and device addresses) that the
-  // step-wise integrators' totals kernels write into, so that the host reads
-  // a step's totals after a stream synchronisation without a copy; calls on
-  // one context are serialised by `lock', so one block serves them all
+  // a mapped pinned host block (host and device addresses) that kernels write
+  // a step's outcome and totals or a run's results into, so that the host
+  // reads them without a copy; calls on one context are serialised by `lock',
+  // so one block serves them all
   double *pinned_host = nullptr, *pinned_dev = nullptr;
-  static constexpr size_t kPinnedBytes = 256;
+  static constexpr size_t kPinnedBytes = 128 * 1024;
   // Vegas grids kept between calls (gridno): slot -> ((ndim, nbins), edges)
   std::map<int, std::pair<std::pair<int, int>, std::vector<double>>> grid_table;
   // freed device blocks kept for reuse, by size class (see dev_alloc)
@@ -75,6 +76,9 @@ void pool_release(ccuba_ctx *ctx);
 // The context's mapped pinned block (allocated on first use).  Returns
 // CCUBA_OK or CCUBA_EHIP.
 int pinned_block(ccuba_ctx *ctx, double **host, double **dev);
+
+// Make sure that the context's second stream is there.
+int second_stream(ccuba_ctx *ctx);
 
 // The word a kernel writes its outcome to, seq << 8 | code, in mapped pinned
 // memory (a slot of doubles).

@@ -14,6 +14,8 @@ namespace ccuba {
 constexpr int kMaxDim = 16;
 constexpr int kMaxBins = 256;  // bin indices are packed 4 per 32-bit word
 constexpr int kGroupTiles = 32;  // tiles folded by one wavefront of the fold kernel
+// Up to this many tiles an integral's refine launch sums the tile rows itself.
+constexpr int kDirectTiles = 64;
 constexpr int kParamRow = kMaxDim;
 
 enum Precision { FP64 = 0, FP32 = 1 };
@@ -36,7 +38,7 @@ struct VJob {
   int hist_cap;           // capacity of the per-iteration history
   int pad;
   VState *state;
-  // the state as the iteration's fold found it (null: no refine follows):
+  // the state as the iteration's sampling found it (null: no refine follows):
   // the refine kernel's workgroups read it, so that none of them reads a
   // state that another one has already advanced
   VState *snap;

@@ -17,10 +17,10 @@ int noalloc_init(int device);
 // The recorded address of the device's scratch array, or nullptr.
 void *noalloc_scratch(int device);
 
-// The descriptors of one DoSample pass, passed by value to a kernel that
-// writes them into the scratch (kernel arguments need no host buffer that
-// must outlive the call, nor a copy to wait for).
-struct NoallocSetup {
+// The descriptors of one integral, passed by value to a kernel that writes
+// them to device memory (kernel arguments need no host buffer that must
+// outlive the call, nor a copy to wait for).
+struct JobSetup {
   VJob job;
   VState st;
   double p64[2][kParamRow];
@@ -31,7 +31,8 @@ struct NoallocSetup {
   double *p64_dst;
   float *p32_dst;
   long long *ends_dst;
+  double *grid_dst;  // the uniform starting grid goes here (null: none)
 };
-hipError_t launch_noalloc_setup(const NoallocSetup &S, hipStream_t s);
+hipError_t launch_job_setup(const JobSetup &S, hipStream_t s);
 
 }  // namespace ccuba

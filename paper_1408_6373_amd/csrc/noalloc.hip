@@ -48,7 +48,7 @@ __device__ void copy_words(void *dst, const void *src, int nbytes, int tid) {
   for (int w = tid; w < nbytes / 4; w += blockDim.x) d[w] = s[w];
 }
 
-__global__ void __launch_bounds__(256) noalloc_setup_kernel(NoallocSetup S) {
+__global__ void __launch_bounds__(256) job_setup_kernel(JobSetup S) {
   const int tid = threadIdx.x;
   static_assert(sizeof(VJob) % 4 == 0 && sizeof(VState) % 4 == 0, "whole words");
   copy_words(S.job_dst, &S.job, (int)sizeof(VJob), tid);
@@ -56,12 +56,16 @@ __global__ void __launch_bounds__(256) noalloc_setup_kernel(NoallocSetup S) {
   copy_words(S.p64_dst, S.p64, (int)sizeof(S.p64), tid);
   copy_words(S.p32_dst, S.p32, (int)sizeof(S.p32), tid);
   if (tid < 2) S.ends_dst[tid] = S.ends[tid];
+  if (S.grid_dst) {  // E_j[k] = k/N
+    const int N = S.job.nbins, row = N + 1, tot = S.job.ndim * row;
+    for (int e = tid; e < tot; e += blockDim.x) S.grid_dst[e] = (double)(e % row) / N;
+  }
 }
 
 }  // namespace
 
-hipError_t launch_noalloc_setup(const NoallocSetup &S, hipStream_t s) {
-  hipLaunchKernelGGL(noalloc_setup_kernel, dim3(1), dim3(256), 0, s, S);
+hipError_t launch_job_setup(const JobSetup &S, hipStream_t s) {
+  hipLaunchKernelGGL(job_setup_kernel, dim3(1), dim3(256), 0, s, S);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // refine.h -- device pieces shared by the Vegas and Suave finishing kernels:
-// wave-wide scans, the regularized incomplete gamma function of the chi^2
+// a wave-wide scan, the regularized incomplete gamma function of the chi^2
 // probability, and Lepage's refinement of one grid dimension.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -67,8 +67,9 @@ __device__ __forceinline__ void rebin_dimension(double *h, double *dd, const dou
                                                 double *En, int N, int lane) {
   const int per = (N + 63) >> 6;  // contiguous bins per lane
   const int k0 = lane * per, k1 = min(k0 + per, N);
-  // smoothing and the two row sums
-  double hs = 0.0, ds = 0.0;
+  // smoothing and the row's sum
+  bool any = false;
+  double ds = 0.0;
   for (int k = k0; k < k1; ++k) {
     double v;
     if (k == 0)
@@ -77,13 +78,12 @@ __device__ __forceinline__ void rebin_dimension(double *h, double *dd, const dou
       v = (h[N - 2] + h[N - 1]) / 2.0;
     else
       v = (h[k - 1] + h[k] + h[k + 1]) / 3.0;
-    hs += h[k];
+    any = any || h[k] > 0.0;
     ds += v;
     dd[k] = v;
   }
-  hs = wave_sum(hs);
   ds = wave_sum(ds);
-  if (!(hs > 0.0)) {  // nothing sampled in this dimension: the edges are kept
+  if (!__any(any)) {  // nothing sampled in this dimension: the edges are kept
     for (int i = lane; i <= N; i += 64) En[i] = Eo[i];
     return;
   }

@@ -347,11 +347,12 @@ int Server::tick() {
     if (fold_end_.n < ends.size() && (rc = fold_end_.alloc(ctx_, ends.size() * 2))) return rc;
     CCUBA_HIP(hipMemcpyAsync(fold_end_.p, ends.data(), ends.size() * sizeof(long long),
                              hipMemcpyHostToDevice, s));
+    const bool direct = direct_refine(table);
     FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, fold_end_.p + table.size(), ftot2};
-    CCUBA_HIP(launch_fold(F, false, s));
+    if (!direct) CCUBA_HIP(launch_fold(F, false, s));
     int dmax = 1;
     for (const VJob &J : table) dmax = std::max(dmax, J.ndim);
-    CCUBA_HIP(launch_refine(A, (int)table.size(), dmax, s));
+    CCUBA_HIP(launch_refine(A, (int)table.size(), dmax, direct, s));
   }
   // Cuhre: one rule launch over the children of every stepping request
   if (!segs.empty()) {

@@ -212,7 +212,8 @@ double time_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs, bool spli
   }
   for (int r = 0; r < 3; ++r) {
     VegasEngine e0(ctx), e1(ctx);
-    bool ok = e0.setup(h0, h0.size() == 1, ctx->stream) == CCUBA_OK &&
+    bool ok = (h1.empty() || second_stream(ctx) == CCUBA_OK) &&
+              e0.setup(h0, h0.size() == 1, ctx->stream) == CCUBA_OK &&
               (h1.empty() || e1.setup(h1, h1.size() == 1, ctx->stream2) == CCUBA_OK) &&
               e0.prepare_run(ctx->stream) == CCUBA_OK &&
               (h1.empty() || e1.prepare_run(ctx->stream2) == CCUBA_OK);

@@ -20,6 +20,9 @@ struct VegasArgs {
   long long lds_hist_byte_off;
   int njobs;  // jobs in the table (1: every tile is job 0's)
   int pad;
+  // the refine launch of a single integral writes T << 8 | done here (mapped
+  // host memory; null: nowhere) once it has settled iteration T - 1
+  unsigned long long *word;
 };
 
 // The fold launch: task_end[j] = inclusive prefix over jobs of
@@ -99,14 +102,19 @@ void dosample_fns_f64hfx(std::vector<const void *> &fns);
 // (group rows -> hsum), which only the raw DoSample entry point needs.
 hipError_t launch_fold(const FoldArgs &F, bool level2, hipStream_t s);
 // The refine kernel over njobs integrals, one workgroup per (integral,
-// dimension); dmax: the largest dimension among them.
-hipError_t launch_refine(const VegasArgs &A, int njobs, int dmax, hipStream_t s);
+// dimension); dmax: the largest dimension among them.  direct: no fold came
+// before it (every integral has at most kDirectTiles tiles).
+hipError_t launch_refine(const VegasArgs &A, int njobs, int dmax, bool direct, hipStream_t s);
 // Uniform starting grids of jobs[0, njobs) (device table).
 hipError_t launch_init_grids(const VJob *jobs, int njobs, hipStream_t s);
 // The same for one grid of ndim rows of nbins + 1 edges.
 hipError_t launch_init_grid(double *grid, int ndim, int nbins, hipStream_t s);
 hipError_t launch_collect(const VegasArgs &A, int njobs, double *sums, double *hist,
                           hipStream_t s);
+// Job 0's state, the first n entries of its history and its grid into mapped
+// host memory (history and grid where given).
+hipError_t launch_publish(const VJob *jobs, double *state, int n, double *I, double *var,
+                          double *grid, hipStream_t s);
 hipError_t launch_points(const PointsArgs &P, hipStream_t s);
 hipError_t set_kernel_limits();
 #endif

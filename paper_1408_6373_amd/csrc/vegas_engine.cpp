@@ -2,8 +2,11 @@
 #include "vegas_engine.h"
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
+
+#include "noalloc.h"
 
 namespace ccuba {
 
@@ -208,6 +211,12 @@ void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, lon
   *total2 = t2;
 }
 
+bool direct_refine(const std::vector<VJob> &jobs) {
+  for (const VJob &J : jobs)
+    if (J.ntiles > kDirectTiles) return false;
+  return true;
+}
+
 VegasEngine::~VegasEngine() {
   for (auto &g : graphs_) (void)hipGraphExecDestroy(g.exec);
 }
@@ -360,6 +369,8 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   std::vector<double> p64((size_t)n * 2 * kParamRow);
   std::vector<float> p32((size_t)n * 2 * kParamRow);
   std::vector<VState> st(n);
+  std::vector<long long> ends;
+  fold_tasks(hjobs_, ends, &fold_total_, &fold_total2_);
   for (int j = 0; j < n; ++j) {
     const VegasSpec &sp = specs[j];
     double a64[2][kParamRow];
@@ -373,14 +384,30 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
       st[j].fail = 1;
     }
   }
-  if ((rc = upload(jobs_, hjobs_, s)) || (rc = upload(tile_job_, tile_job, s)) ||
-      (rc = upload(p64_, p64, s)) || (rc = upload(p32_, p32, s)) ||
-      (rc = upload(state_, st, s)))
-    return rc;
-  CCUBA_HIP(launch_init_grids(jobs_.p, n, s));
-  std::vector<long long> ends;
-  fold_tasks(hjobs_, ends, &fold_total_, &fold_total2_);
-  if ((rc = upload(fold_end_, ends, s))) return rc;
+  if (n == 1) {
+    // one launch instead of six uploads and the grid's (each upload is staged
+    // and waited for); with one job the kernels look no tile up
+    JobSetup S{};
+    S.job = hjobs_[0];
+    S.st = st[0];
+    std::memcpy(S.p64, p64.data(), sizeof(S.p64));
+    std::memcpy(S.p32, p32.data(), sizeof(S.p32));
+    S.ends[0] = ends[0];
+    S.ends[1] = ends[1];
+    S.job_dst = jobs_.p;
+    S.st_dst = state_.p;
+    S.p64_dst = p64_.p;
+    S.p32_dst = p32_.p;
+    S.ends_dst = fold_end_.p;
+    S.grid_dst = grids_.p;
+    CCUBA_HIP(launch_job_setup(S, s));
+  } else {
+    if ((rc = upload(jobs_, hjobs_, s)) || (rc = upload(tile_job_, tile_job, s)) ||
+        (rc = upload(p64_, p64, s)) || (rc = upload(p32_, p32, s)) ||
+        (rc = upload(state_, st, s)) || (rc = upload(fold_end_, ends, s)))
+      return rc;
+    CCUBA_HIP(launch_init_grids(jobs_.p, n, s));
+  }
 
   args_.jobs = jobs_.p;
   args_.tile_job = tile_job_.p;
@@ -388,6 +415,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   args_.tile_count = ntiles_;
   args_.hist64 = 0;  // set per tile group at launch
   args_.njobs = n;
+  direct_ = direct_refine(hjobs_);
   pending_.clear();
   iter_launched_ = 0;
   // captured graphs stay valid only while every kernel argument they hold
@@ -396,7 +424,8 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
                                 (long long)(intptr_t)tile_job_.p,
                                 (long long)(intptr_t)fold_end_.p, (long long)(intptr_t)user_fn_,
                                 fold_total_, fold_total2_,
-                                n, ntiles_, (long long)lds_refine_, hist64_[0], hist64_[1]};
+                                n, ntiles_, (long long)lds_refine_, hist64_[0], hist64_[1],
+                                direct_, dmax_};
   for (int p = 0; p < 2; ++p) {
     const VegasTune &t = ctx_->tune[p];
     sig.insert(sig.end(), {t.block, t.blocks_per_cu, t.ilp, t.hist64, ctx_->ncu});
@@ -410,7 +439,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     graph_sig_ = sig;
   }
   // host copies of the tables must outlive the async uploads
-  CCUBA_HIP(hipStreamSynchronize(s));
+  if (n > 1) CCUBA_HIP(hipStreamSynchronize(s));
   return CCUBA_OK;
 }
 
@@ -418,6 +447,7 @@ int VegasEngine::dosample_only(hipStream_t s, bool level2, hipEvent_t between) {
   const int rc = launch_tile_groups(ctx_, args_, tgroups_, s, user_fn_);
   if (rc) return rc;
   if (between) CCUBA_HIP(hipEventRecord(between, s));
+  if (direct_ && !level2) return CCUBA_OK;
   FoldArgs F{jobs_.p, fold_end_.p, njobs(), fold_total_, fold_end_.p + njobs(), fold_total2_};
   CCUBA_HIP(launch_fold(F, level2, s));
   return CCUBA_OK;
@@ -433,14 +463,14 @@ int VegasEngine::launch_iteration(hipStream_t s) {
     int rc = dosample_only(s, false, ev[1]);
     if (rc) return rc;
     CCUBA_HIP(hipEventRecord(ev[2], s));
-    CCUBA_HIP(launch_refine(args_, njobs(), dmax_, s));
+    CCUBA_HIP(launch_refine(args_, njobs(), dmax_, direct_, s));
     CCUBA_HIP(hipEventRecord(ev[3], s));
     pending_.push_back({ev[0], ev[1], ev[2], ev[3], iter_launched_++});
     return CCUBA_OK;
   }
   int rc = dosample_only(s);
   if (rc) return rc;
-  CCUBA_HIP(launch_refine(args_, njobs(), dmax_, s));
+  CCUBA_HIP(launch_refine(args_, njobs(), dmax_, direct_, s));
   ++iter_launched_;
   return CCUBA_OK;
 }
@@ -522,10 +552,40 @@ int VegasEngine::prepare_run(hipStream_t s) {
   return CCUBA_OK;
 }
 
+// A single integral that may stop early: an iteration is queued while the one
+// before it runs, and the refine launch reports each outcome through a word of
+// the pinned block that the host polls.  So the device does not idle between
+// iterations, no state is copied, and at most one iteration is queued in vain
+// (its launches find the state done).
+int VegasEngine::launch_polled(hipStream_t s) {
+  double *host = nullptr, *dev = nullptr;
+  int rc = pinned_block(ctx_, &host, &dev);
+  if (rc) return rc;
+  volatile unsigned long long *word = host_word(host);
+  *word = 0;
+  args_.word = (unsigned long long *)dev;
+  unsigned long long w = 0;
+  for (int t = 0; rc == CCUBA_OK && t < max_iters_ && !(w & 0xFF); ++t) {
+    rc = launch_iteration(s);
+    // iteration t - 1's outcome, while iteration t runs
+    const auto t0 = std::chrono::steady_clock::now();
+    for (unsigned spin = 0; rc == CCUBA_OK && (long long)((w = *word) >> 8) < t; ++spin)
+      if ((spin & 4095u) == 4095u &&
+          std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
+        if (hipStreamSynchronize(s) != hipSuccess || (long long)(*word >> 8) < t)
+          rc = CCUBA_EHIP;
+      }
+  }
+  args_.word = nullptr;
+  // (the word is not written again once the caller has drained the stream)
+  return rc;
+}
+
 int VegasEngine::launch_run(hipStream_t s) {
   const bool fixed = this->fixed();
   int remaining = max_iters_;
   if (remaining == 0) return CCUBA_OK;
+  if (!fixed && alone_ && njobs() == 1 && !ctx_->profile) return launch_polled(s);
   // Iterations are launched in chunks between host checks of the states:
   // all of them at once when no job can stop early, else 2, 4, 8, ... (a
   // finished job's state makes the remaining launches of its chunk skip it).
@@ -611,6 +671,33 @@ int VegasEngine::read_states(std::vector<VState> &out, hipStream_t s) {
   return CCUBA_OK;
 }
 
+int VegasEngine::read_results(VState &st, double *I, double *var, int max_iter, double *grid,
+                              hipStream_t s) {
+  const VJob &J = hjobs_[0];
+  const long long row = (long long)J.ndim * (J.nbins + 1);
+  const long long n = I || var ? std::min(std::max(max_iter, 0), J.hist_cap) : 0;
+  // the state, then the history's two rows, then the grid
+  constexpr long long kState = 32;  // doubles
+  static_assert(sizeof(VState) <= kState * sizeof(double), "the state's place");
+  static_assert((kState + 2 * kIterCap + kMaxDim * (kMaxBins + 1)) * sizeof(double) <=
+                    ccuba_ctx::kPinnedBytes,
+                "every run's results fit the pinned block");
+  double *host = nullptr, *dev = nullptr;
+  const int rc = pinned_block(ctx_, &host, &dev);
+  if (rc) return rc;
+  // (the launch comes after every launch that writes the block's first word)
+  CCUBA_HIP(launch_publish(jobs_.p, dev, (int)n, I ? dev + kState : nullptr,
+                           var ? dev + kState + n : nullptr,
+                           grid ? dev + kState + 2 * n : nullptr, s));
+  CCUBA_HIP(hipStreamSynchronize(s));
+  std::memcpy(&st, host, sizeof(VState));
+  const size_t done = (size_t)std::min<long long>(n, st.T);
+  if (I && done) std::memcpy(I, host + kState, done * sizeof(double));
+  if (var && done) std::memcpy(var, host + kState + n, done * sizeof(double));
+  if (grid) std::memcpy(grid, host + kState + 2 * n, row * sizeof(double));
+  return CCUBA_OK;
+}
+
 int VegasEngine::read_history(int job, int n, double *I, double *var, hipStream_t s) {
   if (job < 0 || job >= njobs()) return CCUBA_EINVAL;
   n = std::min(n, hjobs_[job].hist_cap);
@@ -690,7 +777,7 @@ int VegasEngine::refine_only(const double *hist, const double *grid_in, double *
   // (the refine kernel reads the state through the snapshot the fold takes)
   CCUBA_HIP(hipMemcpyAsync(hjobs_[0].snap, hjobs_[0].state, sizeof(VState),
                            hipMemcpyDeviceToDevice, s));
-  CCUBA_HIP(launch_refine(args_, 1, dmax_, s));
+  CCUBA_HIP(launch_refine(args_, 1, dmax_, false, s));
   return read_grid(0, grid_out, s);
 }
 

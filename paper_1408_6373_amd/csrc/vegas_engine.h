@@ -63,6 +63,9 @@ int launch_tile_groups(ccuba_ctx *ctx, VegasArgs A, const std::vector<TileGroup>
 void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total,
                 long long *total2);
 
+// Whether the refine launch can sum every job's tile rows itself (no fold).
+bool direct_refine(const std::vector<VJob> &jobs);
+
 class VegasEngine {
  public:
   explicit VegasEngine(ccuba_ctx *ctx) : ctx_(ctx) {}
@@ -78,7 +81,9 @@ class VegasEngine {
   // queues them.
   int prepare_run(hipStream_t s);
   // Launch the iterations: all without waiting when every job runs its
-  // whole budget (fixed()), else in chunks with host checks of the states.
+  // whole budget (fixed()); else in chunks with host checks of the states, or
+  // (one integral, set_alone) one at a time, one ahead of the last whose
+  // outcome the host has polled.
   int launch_run(hipStream_t s);
   // Wait for what launch_run queued; the profile-mode timings.
   int finish_run(hipStream_t s);
@@ -94,6 +99,11 @@ class VegasEngine {
                       hipStream_t s);
   // Job 0's history capacity (iterations the budget allows).
   int hist_cap() const { return hjobs_.empty() ? 0 : hjobs_[0].hist_cap; }
+  // Job 0's state, its history (the first max_iter iterations at most) and its
+  // grid, where given, once the stream has drained (through the context's
+  // pinned block).
+  int read_results(VState &st, double *I, double *var, int max_iter, double *grid,
+                   hipStream_t s);
   int read_states(std::vector<VState> &out, hipStream_t s);
   int read_history(int job, int n, double *I, double *var, hipStream_t s);
   int read_grid(int job, double *grid, hipStream_t s);
@@ -105,12 +115,16 @@ class VegasEngine {
   int set_iteration(int job, int t, hipStream_t s);
   int load_grid(int job, const double *src, hipMemcpyKind kind, hipStream_t s);
   // the sampling kernels, then the fold (with level2 both levels, into
-  // hsum); records `between` (if given) after the sampling kernels
+  // hsum; without, only where the refine launch needs it); records `between`
+  // (if given) after the sampling kernels
   int dosample_only(hipStream_t s, bool level2 = false, hipEvent_t between = nullptr);
   int collect(double *sums_dev, double *hist_dev, hipStream_t s);
   // One refinement of job 0 from a given histogram and grid.
   int refine_only(const double *hist, const double *grid_in, double *grid_out, hipStream_t s);
 
+  // The caller runs this engine alone on the context, so that its run may use
+  // the context's pinned block (launch_polled).
+  void set_alone() { alone_ = true; }
   // A caller's device integrand (family USER): its compiled DoSample kernel,
   // set before setup.
   void set_user_kernel(hipFunction_t f) { user_fn_ = f; }
@@ -133,6 +147,7 @@ class VegasEngine {
 
  private:
   int launch_iteration(hipStream_t s);
+  int launch_polled(hipStream_t s);
   int flush_timing();
   struct Timed {
     hipEvent_t e0, e1, e2, e3;
@@ -141,7 +156,7 @@ class VegasEngine {
   std::vector<Timed> pending_;
   hipEvent_t ref_ = nullptr;
   std::vector<std::pair<double, double>> ds_iv_;
-  bool capturing_ = false;
+  bool capturing_ = false, alone_ = false;
   int iter_launched_ = 0;
   ccuba_ctx *ctx_;
   std::vector<VegasSpec> specs_;
@@ -156,6 +171,7 @@ class VegasEngine {
   DevBuf<double> hsum_;
   long long fold_total_ = 0, fold_total2_ = 0;
   VegasArgs args_{};
+  bool direct_ = false;  // the refine launch sums the tile rows (direct_refine)
   int ntiles_ = 0, ngroups_ = 0;
   std::vector<TileGroup> tgroups_;
   int has_prec_[2] = {0, 0};

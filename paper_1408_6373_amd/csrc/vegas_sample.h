@@ -136,9 +136,38 @@ __device__ __forceinline__ void stage_cells(const double *__restrict__ E, int d,
   for (int e0 = threadIdx.x + kStageCells * bs; e0 < dN; e0 += kStageCells * bs) batch(e0);
 }
 
+// The sum over the wavefront, in every lane: the butterfly over lane distances
+// 32, 16, ..., 1 (so the same pairs are added as with exchanges by lane
+// index), without LDS traffic: row swaps bring the halves and the rows
+// together, then each row holds all sums and rotates.
+template <int CTRL>
+__device__ __forceinline__ double row_rotated(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32),
+                                                    false, false);
+    v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+        __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  }
+  {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32),
+                                                    false, false);
+    v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+        __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  }
+  v += row_rotated<0x128>(v);  // row_ror:8
+  v += row_rotated<0x124>(v);  // (lanes equal mod 8 hold the same value)
+  v += row_rotated<0x122>(v);
+  v += row_rotated<0x121>(v);
   return v;
 }
 
@@ -442,9 +471,12 @@ __global__ void __launch_bounds__(256) vegas_dosample_kernel(VegasArgs A) {
     // the state words are first used here, after the cells' loads are issued
     // (without this the compiler waits for them before issuing those loads)
     asm volatile("" : "+v"(sw)::"memory");
+    const int lt = tt - J.tile0;
+    // the state as this iteration samples it, for the refine launch (also once
+    // the integral is done)
+    if (J.snap && lt == 0 && wid == 0 && lane < kStateWords) ((uint32_t *)J.snap)[lane] = sw;
     const VState st = from_words<VState>(sw);
     if (st.done) continue;  // the same for the whole block: nothing read the cells yet
-    const int lt = tt - J.tile0;
     const long long n_t = J.nstart + (long long)st.T * J.nincrease;
     const long long i0 = (long long)lt * J.tile_pts;
     long long c = n_t - i0;

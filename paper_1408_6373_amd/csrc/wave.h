@@ -15,7 +15,7 @@ __device__ __forceinline__ double dpp_or(double v, double identity) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// A reduction over the wavefront, its result in lane 63: the row shifts leave
+// A reduction over the wavefront, its result in lane 63 the row shifts leave
 // each row's result in its lane 15, the row broadcasts carry it on.
 template <typename OP>
 __device__ __forceinline__ double wave_reduce63(double v, double identity, OP op) {
@@ -36,14 +36,6 @@ __device__ __forceinline__ double uniform(double v) {
   const long long b = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_readfirstlane((int)b);
   const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// Lane 63's value in every lane.
-__device__ __forceinline__ double from_lane63(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, 63);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
