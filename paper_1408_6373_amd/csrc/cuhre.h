@@ -63,6 +63,7 @@ struct CRows {
   double *slot;
   long long seq;
   CStop stop;
+  int *window;  // the opening launch leaves the selection's key window here (may be null)
 };
 
 // The rule's generators.
@@ -76,7 +77,6 @@ struct RuleArgs {
   const long long *seg_end;  // inclusive prefix sums of the segment counts
   long long total;
   CSeg one;                  // the segment itself when nseg == 1 (no table)
-  const double *w7, *w5;     // [ndim][5] rule weights (rows 0..16)
   RuleLambdas lam;
   int *done;                 // a run's stop flag (null: none): set, the launch does nothing
   CRows rows;                // step opening and rows of the next state (zero: neither)
@@ -93,7 +93,6 @@ struct GrowArgs {
   CRegions R;
   int d, doublings;
   const double *params;    // [2][kParamRow]
-  const double *w7, *w5;   // as in RuleArgs
   RuleLambdas lam;
   long long np;            // rule points of a region
   CStop stop;              // (neval is the state's own)
@@ -104,12 +103,14 @@ struct GrowArgs {
 };
 hipError_t launch_grow(const GrowArgs &A, int family, hipStream_t s);
 
+constexpr int kTopBins = 4096;  // digits of the selection's histogram
+
 // Per-integral scratch for selection, splitting and totals.
 struct CScratch {
   unsigned long long *prefix;  // [1]: the boundary digit, then the threshold key
   long long *krem;             // [1]: the rank wanted within the digit, then the
                                // threshold position
-  long long *bsum;             // [nblocks] block counts, then their exclusive scan
+  long long *bsum;             // [nblocks] selected regions per tile
   double *tot;                 // [nblocks*2] partial totals (launch_totals)
   long long nbmax;
   long long *parent;           // [cap / 2] positions of the regions split in a step
@@ -119,11 +120,11 @@ struct CScratch {
   // next step before learning the outcome of this one loses nothing but the
   // empty launches.
   int *done;
-  // top-K by a 16-bit first digit: the digit histogram and the histogram of
-  // its top 8 bits (zero between uses), and the keys and positions of the
-  // boundary digit's regions ([cap] each)
-  unsigned *hist16;
-  unsigned *coarse;
+  // top-K by a windowed 16-bit first digit: the digit histogram (kTopBins
+  // words, zero between uses), the window's base, and the keys and positions
+  // of the boundary digit's regions ([cap] each)
+  unsigned *hist;
+  int *window;
   unsigned long long *cand_key;
   long long *cand_pos;
   unsigned long long *cand_cnt;  // [1]
@@ -133,18 +134,18 @@ hipError_t launch_rule(const RuleArgs &A, hipStream_t s);
 // Blocks of the rule launch that launch_rule makes for A (one row each).
 long long rule_blocks(const RuleArgs &A);
 // Top-K selection among the m regions of a store (retired ones never
-// qualify) by (err desc, position asc): a histogram of the keys' top 16 bits
-// finds the boundary digit, then an exact rank among the boundary digit's
-// regions only gives the threshold (key, position), written to S.prefix[0],
-// S.krem[0].
-hipError_t launch_select16(const CRegions &R, long long m, long long K, const CScratch &S,
-                           hipStream_t s, const CRows *open = nullptr);
-// The split of the K regions at or above the threshold that launch_select16
+// qualify) by (err desc, position asc): the threshold (key, position), written
+// to S.prefix[0], S.krem[0], and the selected regions per tile, to S.bsum.  E
+// (the sum of the live regions' errors) where no launch of this step opens or
+// has opened it with S.window.
+hipError_t launch_select(const CRegions &R, long long m, long long K, const CScratch &S,
+                         hipStream_t s, const CRows *open = nullptr, const double *E = nullptr);
+// The split of the K regions at or above the threshold that launch_select
 // left in S: each is retired and its position written to S.parent[j], j its
 // rank in position order.  A rule launch in children mode (CSeg::parent =
 // S.parent) then forms and evaluates the children.  With rows (out set),
 // the sums of the regions that stay live go to split_rows(m) rows.  Clears
-// the top-K histograms for the next selection.
+// the digit histogram for the next selection.
 hipError_t launch_split(const CRegions &R, long long m, long long K, const CScratch &S,
                         hipStream_t s, const CRows *rows = nullptr);
 long long split_rows(long long m);
@@ -161,7 +162,5 @@ hipError_t launch_totals(const CRegions &R, long long m, const CScratch &S, doub
 // the run's stop flag cleared (done may be null).
 hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t s);
 long long scratch_blocks(long long n);
-
-hipError_t cuhre_set_kernel_limits();
 
 }  // namespace ccuba

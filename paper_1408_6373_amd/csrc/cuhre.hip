@@ -38,6 +38,30 @@ namespace ccuba {
 
 namespace {
 
+// The rule's weights per dimension (rows 0..16): degree 7 and degree 5.
+struct GMWeights {
+  double w7[17 * 5], w5[17 * 5];
+};
+constexpr GMWeights gm_weights() {
+  GMWeights t{};
+  for (int d = 0; d <= 16; ++d) {
+    const double p2 = (double)(1 << d), dd = d;
+    double *w7 = t.w7 + 5 * d, *w5 = t.w5 + 5 * d;
+    w7[0] = p2 * (12824.0 - 9120.0 * dd + 400.0 * dd * dd) / 19683.0;
+    w7[1] = p2 * 980.0 / 6561.0;
+    w7[2] = p2 * (1820.0 - 400.0 * dd) / 19683.0;
+    w7[3] = p2 * 200.0 / 19683.0;
+    w7[4] = 6859.0 / 19683.0;
+    w5[0] = p2 * (729.0 - 950.0 * dd + 50.0 * dd * dd) / 729.0;
+    w5[1] = p2 * 245.0 / 486.0;
+    w5[2] = p2 * (265.0 - 100.0 * dd) / 1458.0;
+    w5[3] = p2 * 25.0 / 729.0;
+    w5[4] = 0.0;
+  }
+  return t;
+}
+__constant__ GMWeights kWeights = gm_weights();
+
 constexpr int kLaneRuleMaxDim = 8;          // lane-per-region rule up to this d
 constexpr long long kLaneRuleMinRegions = 512;  // and from this many regions on
 constexpr long long kOneLaneRuleMinRegions = 49152;  // one lane per region from here
@@ -66,6 +90,21 @@ __device__ __forceinline__ unsigned long long key_of(double e) {
 }
 
 __device__ __forceinline__ bool retired(double e) { return signbit(e); }
+
+// The selection's digits are the keys' top 16 bits (sign, exponent and 4
+// mantissa bits) in a window of kTopBins values that ends just above the
+// digit of the errors' sum E, which no error can exceed: all errors down to
+// 2^-255 of the sum have a digit of their own, and smaller ones share digit 0.
+__host__ __device__ inline int key_window(double E) {
+  unsigned long long b;
+  __builtin_memcpy(&b, &E, sizeof(b));
+  const long long top = (long long)((b + 1ull) >> 48) + 2;
+  return (int)(top > kTopBins ? top - kTopBins : 0);
+}
+__device__ __forceinline__ int window_digit(unsigned long long key, int base) {
+  const int d = (int)(key >> 48) - base;
+  return d < 0 ? 0 : d < kTopBins ? d : kTopBins - 1;
+}
 
 // The geometry of region r of a segment: loaded, or formed from its parent
 // (children mode) and stored.  Lane `j' (< d) handles coordinate j.
@@ -321,7 +360,7 @@ __device__ double2 rule_region(const RuleArgs &A, const CSeg &S, long long r, Ru
   }
   const int best = rule_axis(A.lam, d, lane, L.f);
   if (lane == 0) {
-    const double2 v = rule_values(d, L.h, Sk, A.w7 + d * 5, A.w5 + d * 5);
+    const double2 v = rule_values(d, L.h, Sk, kWeights.w7 + d * 5, kWeights.w5 + d * 5);
     const double err = fabs(v.x - v.y);
     S.regs.I7[r] = v.x;
     S.regs.I5[r] = v.y;
@@ -478,7 +517,7 @@ __device__ double2 rule_region_lane(const RuleArgs &A, const CSeg &S, long long 
   double vol = 1.0;
 #pragma unroll
   for (int j = 0; j < D; ++j) vol *= h[j];
-  const double *w7 = A.w7 + D * 5, *w5 = A.w5 + D * 5;
+  const double *w7 = kWeights.w7 + D * 5, *w5 = kWeights.w5 + D * 5;
   double r7 = 0.0, r5 = 0.0;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
@@ -603,7 +642,7 @@ __device__ double2 rule_region_quad(const RuleArgs &A, const CSeg &S, long long 
   double vol = 1.0;
 #pragma unroll
   for (int j = 0; j < D; ++j) vol *= h[j];
-  const double *w7 = A.w7 + D * 5, *w5 = A.w5 + D * 5;
+  const double *w7 = kWeights.w7 + D * 5, *w5 = kWeights.w5 + D * 5;
   double r7 = 0.0, r5 = 0.0;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
@@ -665,7 +704,8 @@ __device__ __forceinline__ int stop_code(double I, double E, const CStop &stop) 
 
 // The opening of a step (CRows): true if the run goes on.  Every thread of
 // the block must call it.
-__device__ __forceinline__ bool open_step(const CRows &R, int *done) {
+// (*base: see key_window.)
+__device__ __forceinline__ bool open_step(const CRows &R, int *done, int *base = nullptr) {
   if (!R.in) return true;
   double x = 0.0, y = 0.0;
   for (long long i = threadIdx.x; i < R.nin; i += blockDim.x) {
@@ -674,7 +714,10 @@ __device__ __forceinline__ bool open_step(const CRows &R, int *done) {
   }
   const double2 T = block_sum2(x, y);
   const int code = stop_code(T.x, T.y, R.stop);
+  const int win = key_window(T.y);
+  if (base) *base = win;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (R.window) *R.window = win;
     R.slot[0] = T.x;
     R.slot[1] = T.y;
     __hip_atomic_store((unsigned long long *)(R.slot + 2),
@@ -925,7 +968,7 @@ __global__ void __launch_bounds__(256) gm_rule_wave_kernel(RuleArgs A) {
     const WaveRule<FAM, D> rule(A.lam, S.par, lane);
     double2 v;
     int axis;
-    rule.eval(A.lam, lane, c, h, A.w7 + D * 5, A.w5 + D * 5, &v, &axis);
+    rule.eval(A.lam, lane, c, h, kWeights.w7 + D * 5, kWeights.w5 + D * 5, &v, &axis);
     if (lane == 0) S.regs.axis[r] = axis;
     if (lane == 63) {
       const double err = fabs(v.x - v.y);
@@ -958,8 +1001,8 @@ __global__ void __launch_bounds__(kGrowThreads) cuhre_grow_kernel(GrowArgs A) {
   double w7[5], w5[5];
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
-    w7[q] = uniform(A.w7[D * 5 + q]);
-    w5[q] = uniform(A.w5[D * 5 + q]);
+    w7[q] = uniform(kWeights.w7[D * 5 + q]);
+    w5[q] = uniform(kWeights.w5[D * 5 + q]);
   }
   if (tid < D) sc[0][0][tid] = sh[0][0][tid] = 0.5;
   if (tid == 0) *A.done = 0;
@@ -1074,53 +1117,27 @@ __device__ __forceinline__ bool selected(double e, long long i, unsigned long lo
   return k > thr || (k == thr && i <= tpos);
 }
 
-constexpr int kTopBins = 1 << 16;
 constexpr int kTopThreads = 1024;
-
-// Per tile of kScanTile positions, the count of selected regions.  Also
-// clears the top-K histograms, which this step's selection has used.
-__global__ void __launch_bounds__(kScanBlock) sel_count_kernel(const double *err, long long m,
-                                                               const unsigned long long *prefix,
-                                                               const long long *krem,
-                                                               long long *bsum, unsigned *ghist,
-                                                               unsigned *gcoarse,
-                                                               const int *done) {
-  if (stopped(done)) return;
-  for (long long i = (long long)blockIdx.x * kScanBlock + threadIdx.x; i < kTopBins + 256;
-       i += (long long)gridDim.x * kScanBlock) {
-    if (i < kTopBins)
-      ghist[i] = 0u;
-    else
-      gcoarse[i - kTopBins] = 0u;
-  }
-  const unsigned long long thr = prefix[0];
-  const long long tpos = krem[0];
-  const long long base = (long long)blockIdx.x * kScanTile;
-  long long c = 0;
-#pragma unroll
-  for (int q = 0; q < kScanItems; ++q) {
-    const long long i = base + q * kScanBlock + threadIdx.x;
-    if (i < m && selected(err[i], i, thr, tpos)) ++c;
-  }
-  long long tot;
-  (void)block_excl_scan(c, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
+static_assert(kTopThreads == kScanTile, "the gather's passes are the split's tiles");
 
 // Each selected region is retired and its position written to parent[j],
 // j its rank in position order: the counts of the tiles before this one
 // (summed by every block itself) plus the selected positions before it in
 // the tile (the tile's kScanItems chunks of 256 in order, within a chunk the
 // wavefronts in order, within a wavefront the lanes below).  With rows, the
-// block's sums over the regions that stay live.
+// block's sums over the regions that stay live.  Clears the histogram.
 __global__ void __launch_bounds__(kScanBlock) split_mark_kernel(double *err, const double *I7,
                                                                 long long m,
                                                                 const unsigned long long *prefix,
                                                                 const long long *krem,
                                                                 const long long *bsum,
                                                                 long long *parent, long long K,
-                                                                CRows rows, const int *done) {
+                                                                unsigned *ghist, CRows rows,
+                                                                const int *done) {
   if (stopped(done)) return;
+  // (the selection's histogram is clear again for the next one)
+  for (int q = blockIdx.x * kScanBlock + threadIdx.x; q < kTopBins; q += gridDim.x * kScanBlock)
+    ghist[q] = 0u;
   __shared__ int cnt[kScanItems][kScanBlock / 64];
   const unsigned long long thr = prefix[0];
   const long long tpos = krem[0];
@@ -1168,14 +1185,17 @@ __global__ void __launch_bounds__(kScanBlock) split_mark_kernel(double *err, con
   put_row(rows, a, b);
 }
 
-// top-K by a 16-bit first digit ------------------------------------------------
+// top-K by a windowed 16-bit first digit ---------------------------------------
 //
 // The K largest keys, ties to the lower position, in three launches: the
-// histogram of the keys' top 16 bits (sign, exponent and 4 mantissa bits of
-// the error) and of their top 8 bits; the digit that holds the K-th key (the
-// 8-bit digit first, then the 16-bit one within it, found by every block)
-// and the keys and positions of that digit's regions gathered; the exact
-// K-th (key, position) among them.
+// histogram of the keys' window digits; the digit that holds the K-th key
+// (found by every block), the keys and positions of that digit's regions
+// gathered, and the count per tile of the regions above it, which are all
+// selected; the exact K-th (key, position) among the gathered, whose selected
+// ones join the tile counts.  Latency: a 4096-word histogram is cleared, summed
+// and scanned in a fraction of what all 65536 digits took (4.4 against 8.2 us a
+// launch at d = 3 and 10^4 regions a batch, 6.6 against 11.7 at d = 6 and 10^5),
+// and the tile counts need no launch of their own (3.2 us).
 
 __device__ __forceinline__ long long block_excl_scan_1024(long long v, long long *total) {
   __shared__ long long wtot[kTopThreads / 64];
@@ -1237,107 +1257,122 @@ __device__ __forceinline__ void pick_digit(const long long (&c)[PER], long long 
   __syncthreads();
 }
 
-// Per block a histogram of 16-bit counters in LDS (two to a 32-bit word: a
-// block sees fewer than 2^16 keys, so a half never carries into the other),
-// added into the global 16-bit-digit histogram and its 8-bit-digit one.
-// Opens the step (open) and clears the candidate count.
+// Opens the step (open), or takes the window from `base' (not negative) or from
+// the launch that did (window), and clears the candidate count.
 __global__ void __launch_bounds__(kTopThreads) topk_hist_kernel(const double *err, long long m,
                                                                 unsigned *ghist,
-                                                                unsigned *gcoarse,
                                                                 unsigned long long *cnt,
+                                                                int *window, int base,
                                                                 CRows open, int *done) {
-  if (stopped(done) || !open_step(open, done)) return;
-  extern __shared__ unsigned lh[];  // kTopBins / 2 words, then 256 coarse counters
-  unsigned *lc = lh + kTopBins / 2;
+  if (stopped(done)) return;
+  __shared__ unsigned lh[kTopBins];
+  for (int q = threadIdx.x; q < kTopBins; q += kTopThreads) lh[q] = 0u;
+  if (open.in) {
+    if (!open_step(open, done, &base)) return;
+  } else if (base < 0) {
+    base = *window;
+  } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *window = base;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) cnt[0] = 0ull;
-  for (int q = threadIdx.x; q < kTopBins / 2 + 256; q += kTopThreads) lh[q] = 0u;
   __syncthreads();
-  for (long long i = (long long)blockIdx.x * kTopThreads + threadIdx.x; i < m;
-       i += (long long)gridDim.x * kTopThreads) {
-    const unsigned b = (unsigned)(key_of(err[i]) >> 48);
-    atomicAdd(&lh[b >> 1], 1u << ((b & 1u) << 4));
+  constexpr int kKeys = 4;  // loads in flight
+  const long long step = (long long)gridDim.x * kTopThreads;
+  for (long long i0 = (long long)blockIdx.x * kTopThreads + threadIdx.x; i0 < m;
+       i0 += kKeys * step) {
+    double e[kKeys];
+#pragma unroll
+    for (int q = 0; q < kKeys; ++q) e[q] = i0 + q * step < m ? err[i0 + q * step] : -1.0;
+#pragma unroll
+    for (int q = 0; q < kKeys; ++q) {
+      const unsigned long long k = key_of(e[q]);
+      if (k) atomicAdd(&lh[window_digit(k, base)], 1u);  // (retired regions are in no digit)
+    }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < kTopBins / 2; q += kTopThreads) {
-    const unsigned w = lh[q], lo = w & 0xFFFFu, hi = w >> 16;
-    if (lo) atomicAdd(&ghist[2 * q], lo);
-    if (hi) atomicAdd(&ghist[2 * q + 1], hi);
-    if (w) atomicAdd(&lc[q >> 7], lo + hi);  // words q hold digits 2q, 2q + 1
-  }
-  __syncthreads();
-  if (threadIdx.x < 256 && lc[threadIdx.x]) atomicAdd(&gcoarse[threadIdx.x], lc[threadIdx.x]);
+  for (int q = threadIdx.x; q < kTopBins; q += kTopThreads)
+    if (const unsigned c = lh[q]) atomicAdd(&ghist[q], c);
 }
 
-// Every block finds the boundary digit (the 8-bit digit holding the K-th
-// key, then the 16-bit digit within it) from the histograms; block 0 writes
-// it to prefix[0] and the rank wanted within it (from 1) to krem[0].  Then
-// the keys and positions of the digit's regions are gathered (any order),
-// one atomic add per block and pass.
+// Every block finds the boundary digit; block 0 writes it to prefix[0] and
+// the rank wanted within it (from 1) to krem[0].  Then, tile by tile: the keys
+// and positions of the digit's regions are gathered (any order, one atomic
+// add per tile), and the number of regions above it goes to bsum.
 __global__ void __launch_bounds__(kTopThreads) topk_gather_kernel(const double *err, long long m,
                                                                   long long K,
                                                                   const unsigned *ghist,
-                                                                  const unsigned *gcoarse,
+                                                                  const int *window,
                                                                   unsigned long long *prefix,
                                                                   long long *krem,
                                                                   unsigned long long *ckey,
                                                                   long long *cpos,
                                                                   unsigned long long *cnt,
+                                                                  long long *bsum,
                                                                   const int *done) {
   if (stopped(done)) return;
-  __shared__ unsigned wc[kTopThreads / 64];
+  __shared__ unsigned wc[kTopThreads / 64], wa[kTopThreads / 64];
   __shared__ unsigned long long s_base;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  int hi8, lo8;
-  long long need, c8;
+  const int base = *window;
+  int dg;
+  long long need, count;
   {
-    const long long c1[1] = {t < 256 ? (long long)gcoarse[255 - t] : 0};
-    pick_digit<1>(c1, K, 256, &hi8, &need, &c8);
-    const long long c2[1] = {t < 256 ? (long long)ghist[(hi8 << 8) + 255 - t] : 0};
-    pick_digit<1>(c2, need, 256, &lo8, &need, &c8);
+    const uint4 h = ((const uint4 *)ghist)[kTopBins / 4 - 1 - t];  // digits 4095 - 4t down
+    const long long c[4] = {(long long)h.w, (long long)h.z, (long long)h.y, (long long)h.x};
+    pick_digit<4>(c, K, kTopBins, &dg, &need, &count);
   }
-  // (pick_digit counts digit 255 - t for thread t; threads from 256 on hold 0)
-  const unsigned long long dg = (unsigned long long)((hi8 << 8) | lo8);
   if (blockIdx.x == 0 && t == 0) {
-    prefix[0] = dg;
+    prefix[0] = (unsigned long long)dg;
     krem[0] = need;
   }
-  for (long long i0 = (long long)blockIdx.x * kTopThreads; i0 < m;
-       i0 += (long long)gridDim.x * kTopThreads) {
-    const long long i = i0 + t;
+  for (long long tile = blockIdx.x; tile * kTopThreads < m; tile += gridDim.x) {
+    const long long i = tile * kTopThreads + t;
     const unsigned long long k = i < m ? key_of(err[i]) : 0ull;
-    const bool sel = i < m && (k >> 48) == dg;
-    const unsigned long long bal = __ballot(sel);
-    if (lane == 0) wc[w] = (unsigned)__popcll(bal);
+    const int kd = window_digit(k, base);
+    const bool sel = k && kd == dg;
+    const unsigned long long bal = __ballot(sel), up = __ballot(k && kd > dg);
+    if (lane == 0) {
+      wc[w] = (unsigned)__popcll(bal);
+      wa[w] = (unsigned)__popcll(up);
+    }
     __syncthreads();
-    unsigned off = 0, all = 0;
+    unsigned off = 0, all = 0, above = 0;
     for (int q = 0; q < kTopThreads / 64; ++q) {
       if (q < w) off += wc[q];
       all += wc[q];
+      above += wa[q];
     }
-    if (t == 0 && all) s_base = atomicAdd(cnt, (unsigned long long)all);
+    if (t == 0) {
+      bsum[tile] = above;
+      if (all) s_base = atomicAdd(cnt, (unsigned long long)all);
+    }
     __syncthreads();
     if (sel) {
       const unsigned long long o = s_base + off + __popcll(bal & ((1ull << lane) - 1ull));
       ckey[o] = k;
       cpos[o] = i;
     }
-    __syncthreads();  // wc and s_base are rewritten by the next pass
+    __syncthreads();  // the counts and s_base are rewritten by the next tile
   }
 }
 
 // One workgroup: among the gathered regions, the one of rank krem[0] (from
 // 1) in the order key descending, position ascending: radix passes of 12
-// bits over the key's low 48 bits (descending), until at most 1024
+// bits over the key's low 48 bits (descending; for the window's digit 0, whose
+// keys differ above them too, first two passes of 8), until at most 1024
 // candidates share the bits fixed so far, which then rank themselves
-// directly; if all 48 bits get fixed first: when the regions with that key
+// directly; if all bits get fixed first: when the regions with that key
 // are not all taken (a tie across the threshold), passes of 8 bits over the
 // positions (ascending), else the largest of their positions.  Its key to
-// prefix[0], its position to krem[0].
+// prefix[0], its position to krem[0]; the selected candidates are added to
+// their tiles' counts.
 __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned long long *ckey,
                                                                  const long long *cpos,
                                                                  const unsigned long long *cnt,
+                                                                 const int *window,
                                                                  unsigned long long *prefix,
                                                                  long long *krem,
+                                                                 long long *bsum,
                                                                  const int *done) {
   if (stopped(done)) return;
   __shared__ unsigned h[4096];
@@ -1345,32 +1380,38 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
   const int t = threadIdx.x;
   const unsigned long long dg = prefix[0];
   const long long mc = (long long)cnt[0];
+  const int base = *window;
   long long need = krem[0], group = 0;
-  unsigned long long pre = dg << 48, mask = 0xFFFFull << 48;  // key bits fixed so far
+  // key bits fixed so far: the digit, unless it is the one that smaller keys share
+  const bool shared_digit = dg == 0 && base > 0;
+  unsigned long long pre = shared_digit ? 0ull : (dg + (unsigned long long)base) << 48;
+  unsigned long long mask = shared_digit ? 0ull : 0xFFFFull << 48;
   int dig;
-  // up to kExactReg keys per thread stay in registers across the passes (the
-  // padding ~0 has top digit 0xFFFF, which no live key has: the sign bit of
-  // a live error is clear)
+  // up to kExactReg keys per thread, and their positions (below 2^32: a store
+  // of 2^32 regions would need over 500 GB), stay in registers
   constexpr int kExactReg = 16;
   constexpr long long kDirect = kTopThreads;  // candidates ranked directly
   const bool inreg = mc <= (long long)kExactReg * kTopThreads;
   unsigned long long kr[kExactReg];
+  unsigned pr[kExactReg];
 #pragma unroll
   for (int q = 0; q < kExactReg; ++q) {
     const long long i = t + (long long)q * kTopThreads;
-    kr[q] = inreg && i < mc ? ckey[i] : ~0ull;
+    kr[q] = inreg && i < mc ? ckey[i] : 0ull;  // (a live key is not 0)
+    pr[q] = inreg && i < mc ? (unsigned)cpos[i] : 0u;
   }
-  for (int shift = 36; shift >= 0; shift -= 12) {
+  for (int shift = shared_digit ? 56 : 36; shift >= 0; shift -= shift > 48 ? 8 : 12) {
+    const unsigned long long bits = shift >= 48 ? 255ull : 4095ull;
     for (int q = t; q < 4096; q += kTopThreads) h[q] = 0u;
     __syncthreads();
     if (inreg) {
 #pragma unroll
       for (int q = 0; q < kExactReg; ++q)
-        if ((kr[q] & mask) == pre) atomicAdd(&h[(kr[q] >> shift) & 4095ull], 1u);
+        if (kr[q] && (kr[q] & mask) == pre) atomicAdd(&h[(kr[q] >> shift) & bits], 1u);
     } else {
       for (long long i = t; i < mc; i += kTopThreads) {
         const unsigned long long k = ckey[i];
-        if ((k & mask) == pre) atomicAdd(&h[(k >> shift) & 4095ull], 1u);
+        if ((k & mask) == pre) atomicAdd(&h[(k >> shift) & bits], 1u);
       }
     }
     __syncthreads();
@@ -1379,7 +1420,7 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     for (int q = 0; q < 4; ++q) c4[q] = h[4095 - (4 * t + q)];
     pick_digit<4>(c4, need, 4096, &dig, &need, &group);
     pre |= (unsigned long long)dig << shift;
-    mask |= 4095ull << shift;
+    mask |= bits << shift;
     if (group <= kDirect) break;  // (group is the same in every thread)
   }
   unsigned long long tpos;
@@ -1397,10 +1438,10 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     if (inreg) {
 #pragma unroll
       for (int q = 0; q < kExactReg; ++q)
-        if ((kr[q] & mask) == pre) {
+        if (kr[q] && (kr[q] & mask) == pre) {
           const int o = atomicAdd(&gcnt, 1);
           gk[o] = kr[q];
-          gp[o] = cpos[t + (long long)q * kTopThreads];
+          gp[o] = pr[q];
         }
     } else {
       for (long long i = t; i < mc; i += kTopThreads) {
@@ -1434,7 +1475,7 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     if (inreg) {
 #pragma unroll
       for (int q = 0; q < kExactReg; ++q)
-        if (kr[q] == pre) mx = max(mx, (unsigned long long)cpos[t + (long long)q * kTopThreads]);
+        if (kr[q] == pre) mx = max(mx, (unsigned long long)pr[q]);
     } else {
       for (long long i = t; i < mc; i += kTopThreads)
         if (ckey[i] == pre) mx = max(mx, (unsigned long long)cpos[i]);
@@ -1443,8 +1484,7 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     __syncthreads();
     tpos = s_max;
   } else {
-    // positions are below 2^32 (a store of 2^32 regions would need over
-    // 500 GB); thread t counts position digit t, which pick_digit sees as
+    // thread t counts position digit t, which pick_digit sees as
     // digit 255 - t
     unsigned long long ppre = 0ull, pmask = 0xFFFFFFFF00000000ull;
     long long gc;
@@ -1466,6 +1506,20 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
   if (t == 0) {
     prefix[0] = pre;
     krem[0] = (long long)tpos;
+  }
+  auto count = [&](unsigned long long k, long long p) {
+    if (k > pre || (k == pre && p <= (long long)tpos))
+      atomicAdd((unsigned long long *)&bsum[p / kScanTile], 1ull);
+  };
+  if (inreg) {
+#pragma unroll
+    for (int q = 0; q < kExactReg; ++q)
+      if (kr[q]) count(kr[q], pr[q]);
+  } else {
+    for (long long i = t; i < mc; i += kTopThreads) {
+      const unsigned long long k = ckey[i];
+      if (k >= pre) count(k, cpos[i]);
+    }
   }
 }
 
@@ -1628,22 +1682,19 @@ hipError_t launch_rule(const RuleArgs &A, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_select16(const CRegions &R, long long m, long long K, const CScratch &S,
-                           hipStream_t s, const CRows *open) {
-  // blocks see fewer than 2^16 keys each (the LDS counters are 16-bit)
-  const long long per = 32768;
-  const int hgrid = (int)std::max<long long>(std::min<long long>(64, (m + kTopThreads - 1) /
-                                                                         kTopThreads),
-                                             (m + per - 1) / per);
+hipError_t launch_select(const CRegions &R, long long m, long long K, const CScratch &S,
+                         hipStream_t s, const CRows *open, const double *E) {
+  const int hgrid = (int)std::min<long long>(64, (m + kTopThreads - 1) / kTopThreads);
   const CRows none{};
-  hipLaunchKernelGGL(topk_hist_kernel, dim3(hgrid), dim3(kTopThreads), (kTopBins / 2 + 256) * 4,
-                     s, R.err, m, S.hist16, S.coarse, S.cand_cnt, open ? *open : none, S.done);
+  hipLaunchKernelGGL(topk_hist_kernel, dim3(hgrid), dim3(kTopThreads), 0, s, R.err, m, S.hist,
+                     S.cand_cnt, S.window, E ? key_window(*E) : -1, open ? *open : none, S.done);
   const int ggrid = (int)std::min<long long>(256, (m + kTopThreads - 1) / kTopThreads);
   hipLaunchKernelGGL(topk_gather_kernel, dim3(ggrid), dim3(kTopThreads), 0, s, R.err, m, K,
-                     S.hist16, S.coarse, S.prefix, S.krem, S.cand_key, S.cand_pos, S.cand_cnt,
-                     (const int *)S.done);
+                     S.hist, (const int *)S.window, S.prefix, S.krem, S.cand_key, S.cand_pos,
+                     S.cand_cnt, S.bsum, (const int *)S.done);
   hipLaunchKernelGGL(topk_exact_kernel, dim3(1), dim3(kTopThreads), 0, s, S.cand_key, S.cand_pos,
-                     S.cand_cnt, S.prefix, S.krem, (const int *)S.done);
+                     S.cand_cnt, (const int *)S.window, S.prefix, S.krem, S.bsum,
+                     (const int *)S.done);
   return hipGetLastError();
 }
 
@@ -1651,10 +1702,8 @@ hipError_t launch_split(const CRegions &R, long long m, long long K, const CScra
                         hipStream_t s, const CRows *rows) {
   const long long nb = scratch_blocks(m);
   const CRows none{};
-  hipLaunchKernelGGL(sel_count_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, s, R.err, m,
-                     S.prefix, S.krem, S.bsum, S.hist16, S.coarse, (const int *)S.done);
   hipLaunchKernelGGL(split_mark_kernel, dim3((unsigned)nb), dim3(kScanBlock), 0, s, R.err, R.I7,
-                     m, S.prefix, S.krem, S.bsum, S.parent, K, rows ? *rows : none,
+                     m, S.prefix, S.krem, S.bsum, S.parent, K, S.hist, rows ? *rows : none,
                      (const int *)S.done);
   return hipGetLastError();
 }
@@ -1672,14 +1721,6 @@ hipError_t launch_totals(const CRegions &R, long long m, const CScratch &S, doub
   hipLaunchKernelGGL(totals_final_kernel, dim3(1), dim3(kScanBlock), 0, s, S.tot, nb, out,
                      (const int *)S.done);
   return hipGetLastError();
-}
-
-hipError_t cuhre_set_kernel_limits() {
-  // the top-K histogram keeps 2^16 16-bit counters and 256 32-bit ones in
-  // LDS (129 KB)
-  return hipFuncSetAttribute((const void *)topk_hist_kernel,
-                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (kTopBins / 2 + 256) * 4);
 }
 
 }  // namespace ccuba

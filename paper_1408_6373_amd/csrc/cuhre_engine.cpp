@@ -31,30 +31,9 @@ int validate_cuhre(const CuhreSpec &s) {
   return CCUBA_OK;
 }
 
-const GMTables &gm_tables() {
-  static GMTables T = [] {
-    GMTables t{};
-    for (int d = 0; d <= 16; ++d) {
-      const double p2 = std::ldexp(1.0, d), dd = d;
-      double *w7 = t.w7 + 5 * d, *w5 = t.w5 + 5 * d;
-      w7[0] = p2 * (12824.0 - 9120.0 * dd + 400.0 * dd * dd) / 19683.0;
-      w7[1] = p2 * 980.0 / 6561.0;
-      w7[2] = p2 * (1820.0 - 400.0 * dd) / 19683.0;
-      w7[3] = p2 * 200.0 / 19683.0;
-      w7[4] = 6859.0 / 19683.0;
-      w5[0] = p2 * (729.0 - 950.0 * dd + 50.0 * dd * dd) / 729.0;
-      w5[1] = p2 * 245.0 / 486.0;
-      w5[2] = p2 * (265.0 - 100.0 * dd) / 1458.0;
-      w5[3] = p2 * 25.0 / 729.0;
-      w5[4] = 0.0;
-    }
-    t.l2 = std::sqrt(9.0 / 70.0);
-    t.l3 = std::sqrt(9.0 / 10.0);
-    t.l4 = std::sqrt(9.0 / 10.0);
-    t.l5 = std::sqrt(9.0 / 19.0);
-    return t;
-  }();
-  return T;
+RuleLambdas gm_lambdas() {
+  return RuleLambdas{std::sqrt(9.0 / 70.0), std::sqrt(9.0 / 10.0), std::sqrt(9.0 / 10.0),
+                     std::sqrt(9.0 / 19.0)};
 }
 
 // bytes of store per region (centre, width, I7, I5, err, axis) and of the
@@ -81,7 +60,7 @@ int CuhreRun::alloc_store(CRegions &R, DevBuf<double> &cb, DevBuf<double> &hb,
 }
 
 // Scratch sized for a store of cap regions.
-int CuhreRun::alloc_scratch(long long cap) {
+int CuhreRun::alloc_scratch(long long cap, hipStream_t s) {
   int rc;
   const long long nb = scratch_blocks(cap);
   rows_stride_ = step_rows(cap);
@@ -91,7 +70,7 @@ int CuhreRun::alloc_scratch(long long cap) {
       (rc = cand_pos_.alloc(ctx_, cap)))
     return rc;
   // (positions read by a rule launch are always in the store)
-  CCUBA_HIP(hipMemset(parent_.p, 0, parent_.n * sizeof(long long)));
+  CCUBA_HIP(hipMemsetAsync(parent_.p, 0, parent_.n * sizeof(long long), s));
   S_.cand_key = cand_key_.p;
   S_.cand_pos = cand_pos_.p;
   S_.parent = parent_.p;
@@ -115,21 +94,33 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
   CRegions R{};
   DevBuf<double> cb, hb, vals;
   DevBuf<int> ax;
-  int rc = alloc_store(R, cb, hb, vals, ax, cap);
-  if (rc) return rc;
-  const CRegions &O = R_;
-  const long long m = next_id_;
-  if (m > 0) {
-    for (int j = 0; j < d; ++j) {
-      CCUBA_HIP(hipMemcpyAsync(R.c + j * cap, O.c + j * O.cap, m * 8, hipMemcpyDeviceToDevice, s));
-      CCUBA_HIP(hipMemcpyAsync(R.h + j * cap, O.h + j * O.cap, m * 8, hipMemcpyDeviceToDevice, s));
+  for (;; cap = need) {
+    int rc = alloc_store(R, cb, hb, vals, ax, cap);
+    if (rc == CCUBA_OK) {
+      const CRegions &O = R_;
+      const long long m = next_id_;
+      if (m > 0) {
+        for (int j = 0; j < d; ++j) {
+          CCUBA_HIP(hipMemcpyAsync(R.c + j * cap, O.c + j * O.cap, m * 8, hipMemcpyDeviceToDevice,
+                                   s));
+          CCUBA_HIP(hipMemcpyAsync(R.h + j * cap, O.h + j * O.cap, m * 8, hipMemcpyDeviceToDevice,
+                                   s));
+        }
+        CCUBA_HIP(hipMemcpyAsync(R.I7, O.I7, m * 8, hipMemcpyDeviceToDevice, s));
+        CCUBA_HIP(hipMemcpyAsync(R.I5, O.I5, m * 8, hipMemcpyDeviceToDevice, s));
+        CCUBA_HIP(hipMemcpyAsync(R.err, O.err, m * 8, hipMemcpyDeviceToDevice, s));
+        CCUBA_HIP(hipMemcpyAsync(R.axis, O.axis, m * 4, hipMemcpyDeviceToDevice, s));
+      }
+      CCUBA_HIP(hipStreamSynchronize(s));
+      rc = alloc_scratch(cap, s);
     }
-    CCUBA_HIP(hipMemcpyAsync(R.I7, O.I7, m * 8, hipMemcpyDeviceToDevice, s));
-    CCUBA_HIP(hipMemcpyAsync(R.I5, O.I5, m * 8, hipMemcpyDeviceToDevice, s));
-    CCUBA_HIP(hipMemcpyAsync(R.err, O.err, m * 8, hipMemcpyDeviceToDevice, s));
-    CCUBA_HIP(hipMemcpyAsync(R.axis, O.axis, m * 4, hipMemcpyDeviceToDevice, s));
+    if (rc == CCUBA_OK) break;
+    if (rc != CCUBA_ENOMEM || cap <= need) return rc;
+    cb.release();  // the larger store does not fit after all
+    hb.release();
+    vals.release();
+    ax.release();
   }
-  CCUBA_HIP(hipStreamSynchronize(s));
   c_.swap(cb);
   h_.swap(hb);
   vals_.swap(vals);
@@ -139,7 +130,6 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
   hb.release();
   vals.release();
   ax.release();
-  if ((rc = alloc_scratch(cap))) return rc;
   cap_ = cap;
   return CCUBA_OK;
 }
@@ -160,19 +150,16 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   int rc;
   if ((rc = prefix_.alloc(ctx_, 1)) || (rc = krem_.alloc(ctx_, 1)) ||
       (rc = out_.alloc(ctx_, 2)) ||
-      (rc = params_.alloc(ctx_, 2 * kParamRow)) || (rc = w7_.alloc(ctx_, 17 * 5)) ||
-      (rc = w5_.alloc(ctx_, 17 * 5)) || (rc = seg_.alloc(ctx_, 1)) ||
-      (rc = seg_end_.alloc(ctx_, 1)) || (rc = stop_.alloc(ctx_, 1)) ||
-      (rc = hist16_.alloc(ctx_, 1 << 16)) || (rc = coarse_.alloc(ctx_, 256)) ||
-      (rc = cand_cnt_.alloc(ctx_, 1)))
+      (rc = params_.alloc(ctx_, 2 * kParamRow)) || (rc = seg_.alloc(ctx_, 1)) ||
+      (rc = seg_end_.alloc(ctx_, 1)) || (rc = stop_.alloc(ctx_, 2)) ||
+      (rc = hist_.alloc(ctx_, kTopBins)) || (rc = cand_cnt_.alloc(ctx_, 1)))
     return rc;
   S_.done = stop_.p;
-  S_.hist16 = hist16_.p;
-  S_.coarse = coarse_.p;
+  S_.window = stop_.p + 1;
+  S_.hist = hist_.p;
   S_.cand_cnt = cand_cnt_.p;
-  // (the top-K kernels leave the histograms cleared after every use)
-  CCUBA_HIP(hipMemsetAsync(hist16_.p, 0, (1 << 16) * sizeof(unsigned), s));
-  CCUBA_HIP(hipMemsetAsync(coarse_.p, 0, 256 * sizeof(unsigned), s));
+  // (a split leaves the histogram cleared after every selection)
+  CCUBA_HIP(hipMemsetAsync(hist_.p, 0, kTopBins * sizeof(unsigned), s));
   S_.prefix = prefix_.p;
   S_.krem = krem_.p;
   // room for the first few batches, so that the store rarely grows (growing
@@ -180,10 +167,12 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   const long long first_cap = std::max<long long>(
       16, std::min<long long>(std::min<long long>(8 * spec.batch + 1, 1 << 23),
                               spec.maxeval / np_ + 2));
-  // the initial store (room for one batch only if a tight budget refuses more)
+  // the initial store and its scratch (room for one batch only if a tight
+  // budget refuses more)
   long long cap0 = first_cap;
   for (;;) {
     rc = alloc_store(R_, c_, h_, vals_, axis_, cap0);
+    if (rc == CCUBA_OK) rc = alloc_scratch(cap0, s);
     if (rc != CCUBA_ENOMEM) break;
     const long long small = std::max<long long>(
         16, std::min<long long>(2 * spec.batch + 1, spec.maxeval / np_ + 2));
@@ -191,7 +180,6 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
     cap0 = small;
   }
   if (rc) return rc;
-  if ((rc = alloc_scratch(cap0))) return rc;
   cap_ = cap0;
   // constants
   VegasSpec vs;
@@ -203,11 +191,8 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   }
   float p32[2][kParamRow];
   genz_constants(vs, hp64_, p32);
-  const GMTables &T = gm_tables();
-  // (host sources: members and static tables, alive while the copies run)
+  // (the host source is a member, alive while the copy runs)
   CCUBA_HIP(hipMemcpyAsync(params_.p, hp64_, sizeof(hp64_), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipMemcpyAsync(w7_.p, T.w7, sizeof(T.w7), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipMemcpyAsync(w5_.p, T.w5, sizeof(T.w5), hipMemcpyHostToDevice, s));
   rooted_ = false;
   return root ? launch_root(s) : CCUBA_OK;
 }
@@ -226,7 +211,7 @@ int CuhreRun::launch_root(hipStream_t s) {
   n_ = 1;
   neval_ = np_;
   // the root's totals: rows of half 0
-  const CRows rows{nullptr, 0, tot_.p, 0, rows_stride_, nullptr, 0, CStop{}};
+  const CRows rows{nullptr, 0, tot_.p, 0, rows_stride_, nullptr, 0, CStop{}, nullptr};
   rows_par_ = 0;
   return launch_rule_alone(seg, s, &rows, &rows_n_);
 }
@@ -247,13 +232,11 @@ int CuhreRun::grow_doublings() const {
 
 int CuhreRun::launch_rule_alone(const CSeg &seg, hipStream_t s, const CRows *rows,
                                 long long *blocks) {
-  return launch_rule_segments(ctx_, &seg, 1, seg_, seg_end_, w7_.p, w5_.p, s, stop_.p, rows,
-                              blocks);
+  return launch_rule_segments(ctx_, &seg, 1, seg_, seg_end_, s, stop_.p, rows, blocks);
 }
 
 int launch_rule_segments(ccuba_ctx *ctx, const CSeg *segs, int nseg, DevBuf<CSeg> &dsegs,
-                         DevBuf<long long> &dends, const double *w7_dev, const double *w5_dev,
-                         hipStream_t s, int *done, const CRows *rows, long long *blocks) {
+                         DevBuf<long long> &dends, hipStream_t s, int *done, const CRows *rows, long long *blocks) {
   if (nseg <= 0) return CCUBA_OK;
   int rc;
   std::vector<long long> ends(nseg);
@@ -262,7 +245,6 @@ int launch_rule_segments(ccuba_ctx *ctx, const CSeg *segs, int nseg, DevBuf<CSeg
     tot += segs[q].count;
     ends[q] = tot;
   }
-  const GMTables &T = gm_tables();
   RuleArgs A{};
   A.nseg = nseg;
   A.total = tot;
@@ -277,10 +259,8 @@ int launch_rule_segments(ccuba_ctx *ctx, const CSeg *segs, int nseg, DevBuf<CSeg
     A.segs = dsegs.p;
     A.seg_end = dends.p;
   }
-  A.w7 = w7_dev;
-  A.w5 = w5_dev;
   A.done = done;
-  A.lam = RuleLambdas{T.l2, T.l3, T.l4, T.l5};
+  A.lam = gm_lambdas();
   if (rows) A.rows = *rows;
   if (blocks) *blocks = rule_blocks(A);
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -372,7 +352,7 @@ int CuhreRun::plan_and_split(hipStream_t s) {
   if (rc) return rc < 0 ? rc : CCUBA_EHIP;
   pend_range_ = K == n_ && contig_;
   if (!pend_range_) {
-    CCUBA_HIP(launch_select16(R_, next_id_, K, S_, s));
+    CCUBA_HIP(launch_select(R_, next_id_, K, S_, s, nullptr, &E_));
     CCUBA_HIP(launch_split(R_, next_id_, K, S_, s));
     contig_ = false;
   }
@@ -467,15 +447,12 @@ int CuhreRun::run(hipStream_t s) {
     int rc;
     if (!rooted_ && (rc = launch_root(s))) return rc;
   } else {
-    const GMTables &T = gm_tables();
     GrowArgs G{};
     G.R = R_;
     G.d = spec_.ndim;
     G.doublings = t0;
     G.params = params_.p;
-    G.w7 = w7_.p;
-    G.w5 = w5_.p;
-    G.lam = RuleLambdas{T.l2, T.l3, T.l4, T.l5};
+    G.lam = gm_lambdas();
     G.np = np_;
     G.stop = CStop{spec_.epsrel, spec_.epsabs, spec_.mineval, 0};
     G.row = tot_.p;
@@ -533,7 +510,7 @@ int CuhreRun::run(hipStream_t s) {
     const CStop stop{spec_.epsrel, spec_.epsabs, spec_.mineval, neval_};
     // this state's rows; the step's first launch decides on them
     CRows open{tot_.p + 2 * rows_stride_ * rows_par_, rows_n_, nullptr, 0, rows_stride_,
-               dev_slots + slot(t), t, stop};
+               dev_slots + slot(t), t, stop, S_.window};
     long long K = std::min(spec_.batch / 2, n_);
     const long long budget = spec_.maxeval > neval_ ? (spec_.maxeval - neval_) / (2 * np_) : 0;
     K = std::min(K, budget);
@@ -556,15 +533,15 @@ int CuhreRun::run(hipStream_t s) {
       double *next = tot_.p + 2 * rows_stride_ * npar;
       long long rb = 0;
       if (K == n_ && contig_) {  // every region splits: no selection
-        CRows rows{opened ? nullptr : open.in, open.nin, next, 0, rows_stride_, open.slot, t, stop};
+        CRows rows{opened ? nullptr : open.in, open.nin, next, 0, rows_stride_, open.slot, t, stop, nullptr};
         if ((rc = launch_rule_alone(children_segment(K, true), s, &rows, &rb))) return rc;
         rows_n_ = rb;
       } else {
-        CCUBA_HIP(launch_select16(R_, next_id_, K, S_, s, opened ? nullptr : &open));
+        CCUBA_HIP(launch_select(R_, next_id_, K, S_, s, opened ? nullptr : &open));
         const long long sr = split_rows(next_id_);
-        const CRows keep{nullptr, 0, next, 0, rows_stride_, nullptr, 0, CStop{}};
+        const CRows keep{nullptr, 0, next, 0, rows_stride_, nullptr, 0, CStop{}, nullptr};
         CCUBA_HIP(launch_split(R_, next_id_, K, S_, s, &keep));
-        const CRows kids{nullptr, 0, next, sr, rows_stride_, nullptr, 0, CStop{}};
+        const CRows kids{nullptr, 0, next, sr, rows_stride_, nullptr, 0, CStop{}, nullptr};
         if ((rc = launch_rule_alone(children_segment(K, false), s, &kids, &rb))) return rc;
         rows_n_ = sr + rb;
         contig_ = false;

@@ -17,11 +17,7 @@ int validate_cuhre(const CuhreSpec &s);
 long long gm_npoints(int ndim);
 
 // Rule weights (w7, w5: [17][5]) and generators, from Genz & Malik (1980).
-struct GMTables {
-  double w7[17 * 5], w5[17 * 5];
-  double l2, l3, l4, l5;
-};
-const GMTables &gm_tables();
+RuleLambdas gm_lambdas();
 
 class CuhreRun {
  public:
@@ -75,7 +71,7 @@ class CuhreRun {
   int ensure(long long need, hipStream_t s);
   int alloc_store(CRegions &R, DevBuf<double> &cb, DevBuf<double> &hb, DevBuf<double> &vals,
                   DevBuf<int> &ax, long long cap);
-  int alloc_scratch(long long cap);
+  int alloc_scratch(long long cap, hipStream_t s);
   // The segment of the 2K children of step with K splits: formed from the
   // live regions [next_id_ - n_, next_id_) when all split and they are
   // contiguous, else from the positions launch_split wrote.
@@ -102,10 +98,9 @@ class CuhreRun {
   DevBuf<int> axis_;
   DevBuf<unsigned long long> prefix_;
   DevBuf<long long> krem_, bsum_, parent_;
-  DevBuf<unsigned> coarse_;
-  DevBuf<double> tot_, out_, params_, w7_, w5_;
-  DevBuf<int> stop_;  // the run's stop flag (CScratch::done)
-  DevBuf<unsigned> hist16_;  // the top-K digit histogram (CScratch::hist16)
+  DevBuf<double> tot_, out_, params_;
+  DevBuf<int> stop_;  // the run's stop flag and the key window (CScratch::done, window)
+  DevBuf<unsigned> hist_;  // the top-K digit histogram (CScratch::hist)
   DevBuf<unsigned long long> cand_key_, cand_cnt_;
   DevBuf<long long> cand_pos_;
   DevBuf<CSeg> seg_;
@@ -118,8 +113,7 @@ class CuhreRun {
 // Launch the rule over segments of several integrals in one kernel.  segs
 // and ends are host arrays copied to the device buffers given.
 int launch_rule_segments(ccuba_ctx *ctx, const CSeg *segs, int nseg, DevBuf<CSeg> &dsegs,
-                         DevBuf<long long> &dends, const double *w7_dev, const double *w5_dev,
-                         hipStream_t s, int *done = nullptr, const CRows *rows = nullptr,
+                         DevBuf<long long> &dends, hipStream_t s, int *done = nullptr, const CRows *rows = nullptr,
                          long long *blocks = nullptr);
 
 }  // namespace ccuba

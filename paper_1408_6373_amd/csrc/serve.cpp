@@ -282,15 +282,11 @@ int Server::tick() {
   if (!tables_ready_) {
     const int slots = ctx_->serve_slots;
     // (the states, then their snapshots for the refine kernel)
-    if ((rc = states_.alloc(ctx_, 2 * slots)) || (rc = jobs_.alloc(ctx_, slots)) ||
-        (rc = w7_.alloc(ctx_, 17 * 5)) || (rc = w5_.alloc(ctx_, 17 * 5)))
+    if ((rc = states_.alloc(ctx_, 2 * slots)) || (rc = jobs_.alloc(ctx_, slots)))
       return rc;
     for (int q = slots - 1; q >= 0; --q) free_slots_.push_back(q);
     CCUBA_HIP(hipHostMalloc((void **)&tot_host_, 2 * sizeof(double) * slots, 0));
     CCUBA_HIP(hipHostGetDevicePointer((void **)&tot_dev_, tot_host_, 0));
-    const GMTables &T = gm_tables();
-    CCUBA_HIP(hipMemcpy(w7_.p, T.w7, sizeof(T.w7), hipMemcpyHostToDevice));
-    CCUBA_HIP(hipMemcpy(w5_.p, T.w5, sizeof(T.w5), hipMemcpyHostToDevice));
     tables_ready_ = true;
   }
   {
@@ -356,8 +352,7 @@ int Server::tick() {
   }
   // Cuhre: one rule launch over the children of every stepping request
   if (!segs.empty()) {
-    if ((rc = launch_rule_segments(ctx_, segs.data(), (int)segs.size(), segs_, seg_end_, w7_.p,
-                                   w5_.p, s)))
+    if ((rc = launch_rule_segments(ctx_, segs.data(), (int)segs.size(), segs_, seg_end_, s)))
       return rc;
     for (Req *r : stepping) {
       r->cuhre->commit_pending();

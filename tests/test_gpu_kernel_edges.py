@@ -87,3 +87,20 @@ def test_cuhre_first_states_match_oracle(cc, ctx, fam, d, kw):
     assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
     assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
     assert abs(g["error"] - o["error"]) <= 1e-10 * o["error"] + 1e-14 * abs(o["integral"])
+
+
+@pytest.mark.parametrize("d,a0,batch,regions", [(2, 30.0, 100, 900), (3, 40.0, 600, 1500),
+                                                (3, 60.0, 1500, 3000), (2, 0.0, 100, 400)])
+def test_cuhre_selection_of_tiny_errors_matches_oracle(cc, ctx, d, a0, batch, regions):
+    # a narrow peak: errors from 1e-3 of their sum down past 2^-255 of it and to
+    # exact zeros, with the boundary of the selection among the smallest (and,
+    # for a constant, every error equal)
+    a, u = np.full(d, a0), np.full(d, 0.3)
+    npt = 2**d + 2 * d * d + 2 * d + 1
+    kw = dict(epsrel=1e-30, mineval=npt * regions, maxeval=npt * regions,
+              max_regions_per_batch=batch)
+    g = cc.cuhre(W.GAUSSIAN, a, u, ctx=ctx, **kw)
+    o = O.cuhre(O.genz(W.GAUSSIAN, a, u), d, **kw)
+    assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
+    assert abs(g["error"] - o["error"]) <= 1e-10 * o["error"] + 1e-14 * abs(o["integral"])
