@@ -285,8 +285,7 @@ int ccuba_shutdown(ccuba_ctx **ctx) {
   if (!ctx || !*ctx) return CCUBA_OK;
   ccuba_ctx *c = *ctx;
   (void)hipSetDevice(c->device);
-  delete c->server;  // stops the serving thread and frees its requests
-  c->server = nullptr;
+  delete c->server.exchange(nullptr);  // stops the serving thread and frees its requests
   drop_engine_cache(c);
   rtc_release(c);
   if (c->pinned_host) (void)hipHostFree(c->pinned_host);
@@ -1196,24 +1195,29 @@ int ccuba_vegas_batch(ccuba_ctx *ctx, int njobs, const ccuba_job jobs[], ccuba_r
 
 int ccuba_submit(ccuba_ctx *ctx, const ccuba_job *job, unsigned long long *ticket) {
   if (!ctx || !job || !ticket) return CCUBA_EINVAL;
-  {
-    std::lock_guard<std::mutex> g(ctx->lock);
-    if (!ctx->server) ctx->server = new (std::nothrow) Server(ctx);
-    if (!ctx->server) return CCUBA_ENOMEM;
+  Server *server = ctx->server.load();
+  if (!server) {
+    std::lock_guard<std::mutex> g(ctx->server_lock);
+    server = ctx->server.load();
+    if (!server) {
+      server = new (std::nothrow) Server(ctx);
+      if (!server) return CCUBA_ENOMEM;
+      ctx->server.store(server);
+    }
   }
-  return ctx->server->submit(*job, ticket);
+  return server->submit(*job, ticket);
 }
 
 int ccuba_poll(ccuba_ctx *ctx, unsigned long long ticket, ccuba_result *out) {
   if (!ctx || !out) return CCUBA_EINVAL;
-  if (!ctx->server) return CCUBA_ENOENT;
-  return ctx->server->poll(ticket, out);
+  Server *server = ctx->server.load();
+  return server ? server->poll(ticket, out) : CCUBA_ENOENT;
 }
 
 int ccuba_drain(ccuba_ctx *ctx) {
   if (!ctx) return CCUBA_EINVAL;
-  if (!ctx->server) return CCUBA_OK;
-  return ctx->server->drain();
+  Server *server = ctx->server.load();
+  return server ? server->drain() : CCUBA_OK;
 }
 
 }  // extern "C"

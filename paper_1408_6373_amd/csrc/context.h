@@ -39,7 +39,11 @@ struct ccuba_ctx {
   std::mutex stats_lock;            // guards stats (a batch's halves run in two threads)
   std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
   std::mutex lock;                  // serialises engine use with the server thread
-  ccuba::Server *server = nullptr;  // the serving loop, started by the first submit
+  // the serving loop, started by the first submit; `server_lock' serialises
+  // that start (not `lock', which a tick of the loop holds: a submission does not wait
+  // for the work in flight)
+  std::atomic<ccuba::Server *> server{nullptr};
+  std::mutex server_lock;
   // the engine of the last single-integral Vegas call, kept (with its device
   // buffers and captured graphs) for the next call of the same shape
   ccuba::VegasEngine *vcache = nullptr;

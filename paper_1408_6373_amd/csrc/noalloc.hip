@@ -51,11 +51,11 @@ __device__ void copy_words(void *dst, const void *src, int nbytes, int tid) {
 __global__ void __launch_bounds__(256) job_setup_kernel(JobSetup S) {
   const int tid = threadIdx.x;
   static_assert(sizeof(VJob) % 4 == 0 && sizeof(VState) % 4 == 0, "whole words");
-  copy_words(S.job_dst, &S.job, (int)sizeof(VJob), tid);
+  if (S.job_dst) copy_words(S.job_dst, &S.job, (int)sizeof(VJob), tid);
   copy_words(S.st_dst, &S.st, (int)sizeof(VState), tid);
   copy_words(S.p64_dst, S.p64, (int)sizeof(S.p64), tid);
   copy_words(S.p32_dst, S.p32, (int)sizeof(S.p32), tid);
-  if (tid < 2) S.ends_dst[tid] = S.ends[tid];
+  if (S.ends_dst && tid < 2) S.ends_dst[tid] = S.ends[tid];
   if (S.grid_dst) {  // E_j[k] = k/N
     const int N = S.job.nbins, row = N + 1, tot = S.job.ndim * row;
     for (int e = tid; e < tot; e += blockDim.x) S.grid_dst[e] = (double)(e % row) / N;

@@ -1,6 +1,8 @@
 // serve.cpp -- the serving loop (see serve.h).
 #include "serve.h"
 
+#include "noalloc.h"
+
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -21,11 +23,6 @@ struct Server::Req {
   bool vdone = false;
   DevBuf<double> grid, tsums, thist, gsums, ghist, hsum, iters, p64;
   DevBuf<float> p32;
-  // host sources of the activation's uploads, alive while the copies are in
-  // flight (the request outlives them)
-  double a64[2][kParamRow];
-  float a32[2][kParamRow];
-  VState st0{};
   // Cuhre
   std::unique_ptr<CuhreRun> cuhre;
   bool cpending = false;
@@ -235,18 +232,19 @@ int Server::activate(Req &r) {
   J.iter_var = r.iters.p + cap;
   J.p64 = r.p64.p;
   J.p32 = r.p32.p;
-  genz_constants(sp, r.a64, r.a32);
-  r.st0 = VState{};
-  if (iters == 0) {
-    r.st0.done = 1;
-    r.st0.fail = 1;
-  }
   r.vdone = iters == 0;
-  (void)row;
-  CCUBA_HIP(launch_init_grid(J.grid, sp.ndim, sp.nbins, s));
-  CCUBA_HIP(hipMemcpyAsync(r.p64.p, r.a64, sizeof(r.a64), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipMemcpyAsync(r.p32.p, r.a32, sizeof(r.a32), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipMemcpyAsync(J.state, &r.st0, sizeof(r.st0), hipMemcpyHostToDevice, s));
+  JobSetup S{};
+  S.job = J;
+  if (iters == 0) {
+    S.st.done = 1;
+    S.st.fail = 1;
+  }
+  genz_constants(sp, S.p64, S.p32);
+  S.st_dst = J.state;
+  S.p64_dst = r.p64.p;
+  S.p32_dst = r.p32.p;
+  S.grid_dst = J.grid;
+  CCUBA_HIP(launch_job_setup(S, s));
   return CCUBA_OK;
 }
 
@@ -340,12 +338,15 @@ int Server::tick() {
     if ((rc = launch_tile_groups(ctx_, A, groups, s))) return rc;
     long long ftot = 0, ftot2 = 0;
     fold_tasks(table, ends, &ftot, &ftot2);
-    if (fold_end_.n < ends.size() && (rc = fold_end_.alloc(ctx_, ends.size() * 2))) return rc;
-    CCUBA_HIP(hipMemcpyAsync(fold_end_.p, ends.data(), ends.size() * sizeof(long long),
-                             hipMemcpyHostToDevice, s));
     const bool direct = direct_refine(table);
-    FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, fold_end_.p + table.size(), ftot2};
-    if (!direct) CCUBA_HIP(launch_fold(F, false, s));
+    if (!direct) {
+      if (fold_end_.n < ends.size() && (rc = fold_end_.alloc(ctx_, ends.size() * 2))) return rc;
+      CCUBA_HIP(hipMemcpyAsync(fold_end_.p, ends.data(), ends.size() * sizeof(long long),
+                               hipMemcpyHostToDevice, s));
+      FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, fold_end_.p + table.size(),
+                 ftot2};
+      CCUBA_HIP(launch_fold(F, false, s));
+    }
     int dmax = 1;
     for (const VJob &J : table) dmax = std::max(dmax, J.ndim);
     CCUBA_HIP(launch_refine(A, (int)table.size(), dmax, direct, s));
