@@ -258,7 +258,7 @@ int ccuba_init(ccuba_ctx **ctx, int device, size_t hbm_budget) {
   for (int p = 0; p < 2; ++p) {
     c->tune[p].block = (int)env_ll("CCUBA_BLOCK", 256);
     c->tune[p].blocks_per_cu = (int)env_ll("CCUBA_BLOCKS_PER_CU", 3);
-    c->tune[p].min_tile = env_ll("CCUBA_MIN_TILE", 16384);
+    c->tune[p].min_tile = env_ll("CCUBA_MIN_TILE", 2048);
     // measured best on gfx950: two points per lane for FP32, one for FP64
     c->tune[p].ilp = (int)env_ll("CCUBA_ILP", p == FP32 ? 2 : 1) == 2 ? 2 : 1;
     c->tune[p].streams = env_ll("CCUBA_BATCH_STREAMS", 2) == 1 ? 1 : 2;
