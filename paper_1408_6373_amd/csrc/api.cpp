@@ -721,8 +721,7 @@ int ccuba_vegas_dosample_raw(ccuba_ctx *ctx, int ndim, int nbins, const ccuba_in
   if ((rc = eng.setup({sp}, true, s))) return rc;
   if ((rc = eng.set_iteration(0, iteration, s))) return rc;
   if ((rc = eng.load_grid(0, grid_dev, hipMemcpyDeviceToDevice, s))) return rc;
-  if ((rc = eng.dosample_only(s, true))) return rc;
-  if ((rc = eng.collect(sums_dev, hist_dev, s))) return rc;
+  if ((rc = eng.dosample_only(s, nullptr, sums_dev, hist_dev))) return rc;
   // the engine's buffers are released on return: finish before that
   CCUBA_HIP(hipStreamSynchronize(s));
   return CCUBA_OK;
@@ -749,24 +748,23 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   const int p = sp.prec;
   const VegasTune &t = ctx->tune[p];
   const long long dN = (long long)ndim * nbins, row = (2 + dN) * 8;
-  // Layout, 256-byte aligned: descriptor, state, fold ends, parameters, the
-  // folded sums, then per tile and per group of 32 tiles a row of sums and
-  // histogram.  Tiles as the allocating entry point takes them (one per
-  // persistent block); fewer and larger when their rows would not fit.
+  // Layout, 256-byte aligned: descriptor, state, fold tasks, parameters, then
+  // per tile and per group of 32 tiles a row of sums and histogram.  Tiles as
+  // the allocating entry point takes them (one per persistent block); fewer
+  // and larger when their rows would not fit.
   auto a256 = [](long long b) { return (b + 255) / 256 * 256; };
   static_assert(sizeof(VJob) <= 256 && sizeof(VState) <= 256 &&
                     2 * kParamRow * sizeof(double) <= 256 && 2 * kParamRow * sizeof(float) <= 256,
                 "the scratch header's slots");
   static_assert(sizeof(JobSetup) <= 4096, "kernel arguments");
-  const long long o_st = 256, o_end = 512, o_p64 = 768, o_p32 = 1024, o_hsum = 1280;
-  const long long o_rows = o_hsum + a256(row);
+  const long long o_st = 256, o_end = 512, o_p64 = 768, o_p32 = 1024, o_rows = 1280;
   const long long avail = (long long)kNoallocScratchBytes - o_rows - 1024;
   const long long bs = t.block, B = (long long)ctx->ncu * t.blocks_per_cu;
   auto round_up = [](long long v, long long m) { return (v + m - 1) / m * m; };
   auto bytes_for = [&](long long nt) {
     return a256(nt * 16) + a256(nt * dN * 8) + a256((long long)ngroups_of((int)nt) * row);
   };
-  long long P = std::max(round_up((npts + B - 1) / B, bs), bs);
+  long long P = single_tile(npts, bs, ctx->ncu, t.blocks_per_cu);
   long long nt = (npts + P - 1) / P;
   for (long long fit = avail / (row + row / kGroupTiles + 64); bytes_for(nt) > avail;
        fit -= std::max(1ll, fit / 64)) {
@@ -801,19 +799,17 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   J.thist = (double *)(base + o_thist);
   J.gsums = (double *)(base + o_gsums);
   J.ghist = (double *)(base + o_ghist);
-  J.hsum = (double *)(base + o_hsum);
   J.p64 = (const double *)(base + o_p64);
   J.p32 = (const float *)(base + o_p32);
   S.st.T = iteration;  // the rest zero: the state before its first iteration
   genz_constants(sp, S.p64, S.p32);
   const long long nch = (dN + 63) / 64;
-  S.ends[0] = (long long)ng * nch;
-  S.ends[1] = nch;
+  S.end = (long long)ng * nch;
   S.job_dst = (VJob *)base;
   S.st_dst = J.state;
   S.p64_dst = (double *)(base + o_p64);
   S.p32_dst = (float *)(base + o_p32);
-  S.ends_dst = (long long *)(base + o_end);
+  S.end_dst = (long long *)(base + o_end);
   CCUBA_HIP(launch_job_setup(S, s));
 
   VegasArgs A{};
@@ -824,16 +820,15 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   A.njobs = 1;
   A.ilp = t.ilp;
   A.hist64 = fixed_hist(p, t.hist64, dN) ? 0 : 1;
-  const size_t grid_bytes = (size_t)(dN * (p == FP64 ? 16 : 8) + 15) / 16 * 16;
-  const size_t hsz = A.hist64 ? 8 : (p == FP64 ? 24 : 16);
-  A.lds_hist_byte_off = (long long)grid_bytes;
   const int nb = (ndim + 3) / 4;
-  CCUBA_HIP(launch_dosample(A, p, nb, (nbins & (nbins - 1)) == 0, ndim == 4 * nb,
-                            (int)std::min<long long>(B, nt), (int)bs,
-                            grid_bytes + (size_t)dN * hsz, s));
-  FoldArgs F{S.job_dst, S.ends_dst, 1, S.ends[0], S.ends_dst + 1, S.ends[1]};
-  CCUBA_HIP(launch_fold(F, true, s));
-  CCUBA_HIP(launch_collect(A, 1, sums_dev, hist_dev, s));
+  const bool pow2 = (nbins & (nbins - 1)) == 0;
+  size_t hist_off = 0;
+  const size_t lds = dosample_lds(p, !A.hist64, nb, pow2, ndim, nbins, &hist_off);
+  A.lds_hist_byte_off = (long long)hist_off;
+  CCUBA_HIP(launch_dosample(A, p, nb, pow2, ndim == 4 * nb, (int)std::min<long long>(B, nt),
+                            (int)bs, lds, s));
+  FoldArgs F{S.job_dst, S.end_dst, 1, S.end, nch, sums_dev, hist_dev};
+  CCUBA_HIP(launch_fold(F, s));
   return CCUBA_OK;
 }
 

@@ -32,6 +32,7 @@
 
 #include "cuhre.h"
 #include "genz.h"
+#include "vegas_sample.h"  // uniform
 #include "wave.h"
 
 namespace ccuba {

@@ -47,7 +47,6 @@ struct VJob {
   double *thist;          // [ntiles][ndim * nbins]
   double *gsums;          // [ngroups][2]
   double *ghist;          // [ngroups][ndim * nbins]
-  double *hsum;           // [2 + ndim * nbins]: S1, S2 and the folded histogram
   double *iter_I;         // [hist_cap]
   double *iter_var;       // [hist_cap]
   const double *p64;      // [2][kParamRow]

@@ -25,12 +25,12 @@ struct JobSetup {
   VState st;
   double p64[2][kParamRow];
   float p32[2][kParamRow];
-  long long ends[2];  // the fold tasks of the one job: level 1, level 2
+  long long end;  // the fold tasks of the one job
   VJob *job_dst;        // (null: the descriptor is not wanted)
   VState *st_dst;
   double *p64_dst;
   float *p32_dst;
-  long long *ends_dst;  // (null: not wanted)
+  long long *end_dst;   // (null: not wanted)
   double *grid_dst;     // the uniform starting grid goes here (null: none)
 };
 hipError_t launch_job_setup(const JobSetup &S, hipStream_t s);

@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(256) job_setup_kernel(JobSetup S) {
   copy_words(S.st_dst, &S.st, (int)sizeof(VState), tid);
   copy_words(S.p64_dst, S.p64, (int)sizeof(S.p64), tid);
   copy_words(S.p32_dst, S.p32, (int)sizeof(S.p32), tid);
-  if (S.ends_dst && tid < 2) S.ends_dst[tid] = S.ends[tid];
+  if (S.end_dst && tid == 0) *S.end_dst = S.end;
   if (S.grid_dst) {  // E_j[k] = k/N
     const int N = S.job.nbins, row = N + 1, tot = S.job.ndim * row;
     for (int e = tid; e < tot; e += blockDim.x) S.grid_dst[e] = (double)(e % row) / N;

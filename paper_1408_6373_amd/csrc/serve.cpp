@@ -21,7 +21,7 @@ struct Server::Req {
   VegasSpec vs;
   VJob hj{};
   bool vdone = false;
-  DevBuf<double> grid, tsums, thist, gsums, ghist, hsum, iters, p64;
+  DevBuf<double> grid, tsums, thist, gsums, ghist, iters, p64;
   DevBuf<float> p32;
   // Cuhre
   std::unique_ptr<CuhreRun> cuhre;
@@ -120,7 +120,6 @@ void Server::release(Req &r) {
   r.thist.release();
   r.gsums.release();
   r.ghist.release();
-  r.hsum.release();
   r.iters.release();
   r.p64.release();
   r.p32.release();
@@ -194,7 +193,7 @@ int Server::activate(Req &r) {
   int rc;
   if ((rc = r.grid.alloc(ctx_, row)) || (rc = r.tsums.alloc(ctx_, 2 * nt)) ||
       (rc = r.thist.alloc(ctx_, nt * dN)) || (rc = r.gsums.alloc(ctx_, 2 * ng)) ||
-      (rc = r.ghist.alloc(ctx_, ng * dN)) || (rc = r.hsum.alloc(ctx_, 2 + dN)) ||
+      (rc = r.ghist.alloc(ctx_, ng * dN)) ||
       (rc = r.iters.alloc(ctx_, 2 * (size_t)cap)) ||
       (rc = r.p64.alloc(ctx_, 2 * kParamRow)) || (rc = r.p32.alloc(ctx_, 2 * kParamRow)))
     return rc;
@@ -227,7 +226,6 @@ int Server::activate(Req &r) {
   J.thist = r.thist.p;
   J.gsums = r.gsums.p;
   J.ghist = r.ghist.p;
-  J.hsum = r.hsum.p;
   J.iter_I = r.iters.p;
   J.iter_var = r.iters.p + cap;
   J.p64 = r.p64.p;
@@ -338,16 +336,15 @@ int Server::tick() {
     A.tile_job = tiles_.p;
     A.njobs = (int)table.size();
     if ((rc = launch_tile_groups(ctx_, A, groups, s))) return rc;
-    long long ftot = 0, ftot2 = 0;
-    fold_tasks(table, ends, &ftot, &ftot2);
+    long long ftot = 0;
+    fold_tasks(table, ends, &ftot);
     const bool direct = direct_refine(table);
     if (!direct) {
       if (fold_end_.n < ends.size() && (rc = fold_end_.alloc(ctx_, ends.size() * 2))) return rc;
       CCUBA_HIP(hipMemcpyAsync(fold_end_.p, ends.data(), ends.size() * sizeof(long long),
                                hipMemcpyHostToDevice, s));
-      FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, fold_end_.p + table.size(),
-                 ftot2};
-      CCUBA_HIP(launch_fold(F, false, s));
+      FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, 0, nullptr, nullptr};
+      CCUBA_HIP(launch_fold(F, s));
     }
     int dmax = 1;
     for (const VJob &J : table) dmax = std::max(dmax, J.ndim);

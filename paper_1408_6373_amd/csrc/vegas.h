@@ -32,8 +32,10 @@ struct FoldArgs {
   const long long *task_end;   // level 1 tasks
   int njobs;
   long long total;
-  const long long *task_end2;  // level 2: ceil(ndim * nbins / 64) per job
+  // level 2, of a launch's one job: ceil(ndim * nbins / 64) tasks, the totals
+  // into sums[2] and hist[ndim * nbins] (null: no second level)
   long long total2;
+  double *sums, *hist;
 };
 
 struct PointsArgs {
@@ -98,9 +100,9 @@ void dosample_fns_f64(std::vector<const void *> &fns);
 void dosample_fns_f32h64(std::vector<const void *> &fns);
 void dosample_fns_f32hfx(std::vector<const void *> &fns);
 void dosample_fns_f64hfx(std::vector<const void *> &fns);
-// First fold level (tile rows -> group rows); with level2 also the second
-// (group rows -> hsum), which only the raw DoSample entry point needs.
-hipError_t launch_fold(const FoldArgs &F, bool level2, hipStream_t s);
+// First fold level (tile rows -> group rows); with F.sums also the second
+// (group rows -> totals), which only the raw DoSample entry points need.
+hipError_t launch_fold(const FoldArgs &F, hipStream_t s);
 // The refine kernel over njobs integrals, one workgroup per (integral,
 // dimension); dmax: the largest dimension among them.  direct: no fold came
 // before it (every integral has at most kDirectTiles tiles).
@@ -109,8 +111,6 @@ hipError_t launch_refine(const VegasArgs &A, int njobs, int dmax, bool direct, h
 hipError_t launch_init_grids(const VJob *jobs, int njobs, hipStream_t s);
 // The same for one grid of ndim rows of nbins + 1 edges.
 hipError_t launch_init_grid(double *grid, int ndim, int nbins, hipStream_t s);
-hipError_t launch_collect(const VegasArgs &A, int njobs, double *sums, double *hist,
-                          hipStream_t s);
 // Job 0's state, the first n entries of its history and its grid into mapped
 // host memory (history and grid where given).
 hipError_t launch_publish(const VJob *jobs, double *state, int n, double *I, double *var,

@@ -12,8 +12,8 @@
 //   a5 sums    v = w f: S1 += v, S2 += v^2 in FP64 per lane, wave shuffles,
 //              then a fixed-order block sum -> one FP64 partial per tile
 //   a6 hist    H_j[k_j] += v^2 with LDS atomics, written per tile as FP64
-// A fold kernel sums the tile rows 32 at a time in tile order and a second
-// one sums those group rows in group order (so the sums are deterministic);
+// A fold kernel sums the tile rows 32 at a time in tile order, and those group
+// rows are summed in group order (so the sums are deterministic);
 // the refine kernel (one workgroup per integral) then does a7: iteration
 // statistics, the inverse-variance combination with chi^2 and its
 // probability, the convergence test and Lepage's grid refinement, all in FP64.
@@ -105,39 +105,38 @@ __global__ void __launch_bounds__(256) vegas_fold_kernel(FoldArgs F) {
   }
 }
 
-// Second fold level, for callers that want the iteration totals themselves
-// (the refine kernel does this level on its own): one wavefront per
-// (integral, 64-bin chunk) sums the group rows in group order into
-// hsum = (S1, S2, H[d*N]).
+// Second fold level, for a caller that wants a pass's totals themselves (the
+// refine kernel does this level on its own): one wavefront per 64-bin chunk
+// of the launch's one integral sums the group rows in group order, straight into the
+// caller's sums and histogram.
 __global__ void __launch_bounds__(256) vegas_fold2_kernel(FoldArgs F) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const long long g = (long long)blockIdx.x * 4 + w;
-  if (g >= F.total2) return;
-  int lo = 0, hi = F.njobs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (F.task_end2[mid] > g)
-      hi = mid;
-    else
-      lo = mid + 1;
-  }
-  const VJob &J = F.jobs[lo];
-  if (J.state->done) return;
-  const int ch = (int)(g - (lo > 0 ? F.task_end2[lo - 1] : 0));
-  const int dN = J.ndim * J.nbins, ng = ngroups_of(J.ntiles);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int ch = (int)blockIdx.x * 4 + w;
+  if (ch >= F.total2) return;
+  const uint32_t jw = load_words<kJobWords>(F.jobs, lane);
+  const int dN = JOB_FIELD(jw, ndim) * JOB_FIELD(jw, nbins);
+  const int ng = ngroups_of(JOB_FIELD(jw, ntiles));
   const int bin = ch * 64 + lane;
-  if (bin < dN) {
-    const double *src = J.ghist + bin;
-    double s = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < ng; ++q, src += dN) s += *src;
-    J.hsum[2 + bin] = s;
+  const gbl<double> *src = gload(JOB_FIELD(jw, ghist)) + (bin < dN ? bin : 0);
+  const gbl<double> *gs = gload(JOB_FIELD(jw, gsums)) + (lane & 1);
+  double s = 0.0, t = 0.0;
+  for (int q0 = 0; q0 < ng; q0 += kFoldBatch) {
+    double v[kFoldBatch], u[kFoldBatch];
+#pragma unroll
+    for (int q = 0; q < kFoldBatch; ++q) {
+      v[q] = q0 + q < ng ? src[(long long)(q0 + q) * dN] : 0.0;
+      u[q] = ch == 0 && q0 + q < ng ? gs[2 * (q0 + q)] : 0.0;
+    }
+    asm volatile("" ::: "memory");  // every load of the batch before the adds
+#pragma unroll
+    for (int q = 0; q < kFoldBatch; ++q)
+      if (q0 + q < ng) {
+        s += v[q];
+        t += u[q];
+      }
   }
-  if (ch == 0 && lane < 2) {
-    double s = 0.0;
-    for (int q = 0; q < ng; ++q) s += J.gsums[2 * q + lane];
-    J.hsum[lane] = s;
-  }
+  if (bin < dN) F.hist[bin] = s;
+  if (ch == 0 && lane < 2) F.sums[lane] = t;
 }
 
 // a7, the iteration's statistics for one component: the estimate I_t and
@@ -405,17 +404,6 @@ __global__ void __launch_bounds__(256) vegas_publish_kernel(const VJob *jobs, do
     for (int e = tid; e < row; e += bs) grid[e] = J.grid[e];
 }
 
-// Copy out every job's folded iteration totals: sums[2] and hist[d*N]; used by
-// the raw DoSample entry point.
-__global__ void __launch_bounds__(256) vegas_collect_kernel(VegasArgs A, double *sums,
-                                                            double *hist) {
-  const int jb = blockIdx.x, tid = threadIdx.x;
-  const VJob J = A.jobs[jb];
-  const int dN = J.ndim * J.nbins;
-  if (tid < 2) sums[2 * jb + tid] = J.hsum[tid];
-  for (int e = tid; e < dN; e += blockDim.x) hist[e] = J.hsum[2 + e];
-}
-
 // Parity kernel: the points of one iteration (a1-a3), computed with the
 // staging and the per-coordinate arithmetic of the DoSample kernel.
 template <typename T>
@@ -631,10 +619,10 @@ hipError_t launch_dosample(const VegasArgs &A, int prec, int nb, bool pow2, bool
   return launch_dosample_f32hfx(A, nb, pow2, full, grid, block, lds, s);
 }
 
-hipError_t launch_fold(const FoldArgs &F, bool level2, hipStream_t s) {
+hipError_t launch_fold(const FoldArgs &F, hipStream_t s) {
   if (F.total <= 0) return hipSuccess;
   hipLaunchKernelGGL(vegas_fold_kernel, dim3((unsigned)((F.total + 3) / 4)), dim3(256), 0, s, F);
-  if (level2)
+  if (F.sums)
     hipLaunchKernelGGL(vegas_fold2_kernel, dim3((unsigned)((F.total2 + 3) / 4)), dim3(256), 0,
                        s, F);
   return hipGetLastError();
@@ -655,12 +643,6 @@ hipError_t launch_init_grids(const VJob *jobs, int njobs, hipStream_t s) {
 
 hipError_t launch_init_grid(double *grid, int ndim, int nbins, hipStream_t s) {
   hipLaunchKernelGGL(vegas_init_grid_kernel, dim3(1), dim3(256), 0, s, grid, ndim, nbins);
-  return hipGetLastError();
-}
-
-hipError_t launch_collect(const VegasArgs &A, int njobs, double *sums, double *hist,
-                          hipStream_t s) {
-  hipLaunchKernelGGL(vegas_collect_kernel, dim3(njobs), dim3(256), 0, s, A, sums, hist);
   return hipGetLastError();
 }
 

@@ -151,8 +151,8 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
     tend = (long long)ng * ((R + 63) / 64);
     CCUBA_HIP(hipMemcpyAsync(view.p, &jv, sizeof(VJob), hipMemcpyHostToDevice, s));
     CCUBA_HIP(hipMemcpyAsync(task_end.p, &tend, sizeof(long long), hipMemcpyHostToDevice, s));
-    FoldArgs fo{view.p, task_end.p, 1, tend, nullptr, 0};
-    CCUBA_HIP(launch_fold(fo, false, s));
+    FoldArgs fo{view.p, task_end.p, 1, tend, 0, nullptr, nullptr};
+    CCUBA_HIP(launch_fold(fo, s));
     BatchedFinishArgs fa{};
     fa.ndim = d;
     fa.nbins = N;

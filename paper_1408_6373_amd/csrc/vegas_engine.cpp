@@ -134,6 +134,18 @@ bool fixed_hist(int prec, int hist64, long long dN) {
   return !hist64 && (prec == FP32 || dN * (16 + 3 * 8) <= kLds);
 }
 
+size_t dosample_lds(int prec, bool fixed, int nb, bool pow2, int d, int N, size_t *hist_off) {
+  // one (lower edge, span) cell per bin and the histogram (the fixed-point one
+  // holds one integer sum per bin, two with FP64 evaluation, and an FP64
+  // histogram beside them for the other values)
+  const size_t dN = (size_t)d * N, cells = dN * (prec == FP64 ? 16 : 8);
+  *hist_off = align16(cells);
+  if (!pow2 || (fixed && prec == FP64))
+    return *hist_off + dN * (!fixed ? 8 : (prec == FP64 ? 24 : 16));
+  const size_t region = (size_t)4 * nb * kMaxBins * 8;
+  return region + cells + (fixed && 2 * dN * 8 > region ? dN * 8 : 0);
+}
+
 void plan_tile_groups(std::vector<VJob> &jobs, std::vector<int> &tiles,
                       std::vector<TileGroup> &groups, const int hist64[2],
                       const long long blocks[2], size_t *refine_lds) {
@@ -176,14 +188,16 @@ void plan_tile_groups(std::vector<VJob> &jobs, std::vector<int> &tiles,
       // refine: histogram, smoothed histogram and the current grid
       ref = std::max(ref, (2 * dN + (size_t)J.ndim * (J.nbins + 1)) * 8);
     }
-    // LDS: one (lower edge, span) cell per bin, then the histogram (the
-    // fixed-point one holds one integer sum per bin, two with FP64
-    // evaluation, and an FP64 histogram beside them for the other values)
-    const size_t csz = p == FP64 ? 16 : 8;
-    const size_t hsz = !g.hfx ? 8 : (p == FP64 ? 24 : 16);
-    g.grid_bytes = align16((size_t)dNmax * csz);
+    // (the largest of its jobs; where the histogram follows the cells, after the
+    // most cells)
+    for (const VJob &J : jobs)
+      if (mine(J)) {
+        size_t off = 0;
+        const size_t lds = dosample_lds(p, g.hfx, nb, pw, J.ndim, J.nbins, &off);
+        g.grid_bytes = std::max(g.grid_bytes, off);
+        g.lds = std::max(g.lds, lds);
+      }
     g.count = (int)tiles.size() - g.first;
-    g.lds = g.grid_bytes + (size_t)dNmax * hsz;
     if (g.count > 0) groups.push_back(g);
   }
   *refine_lds = ref;
@@ -211,20 +225,32 @@ int launch_tile_groups(ccuba_ctx *ctx, VegasArgs A, const std::vector<TileGroup>
   return CCUBA_OK;
 }
 
-void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total,
-                long long *total2) {
-  const size_t n = jobs.size();
-  ends.resize(2 * n);
-  long long t1 = 0, t2 = 0;
-  for (size_t j = 0; j < n; ++j) {
-    const long long dN = (long long)jobs[j].ndim * jobs[j].nbins, nch = (dN + 63) / 64;
-    t1 += (long long)ngroups_of(jobs[j].ntiles) * nch;
-    t2 += nch;
-    ends[j] = t1;
-    ends[n + j] = t2;
+void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total) {
+  ends.resize(jobs.size());
+  long long t = 0;
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    const long long dN = (long long)jobs[j].ndim * jobs[j].nbins;
+    t += (long long)ngroups_of(jobs[j].ntiles) * ((dN + 63) / 64);
+    ends[j] = t;
   }
-  *total = t1;
-  *total2 = t2;
+  *total = t;
+}
+
+// Every tile costs its block's setup and a row of d N results that the folds
+// read again, so a small iteration takes fewer and larger tiles: at most 64 (the
+// refine launch then needs no fold) up to 2^16 points, a tile per compute unit
+// up to 3072 points each, two up to 12288, the setting's from there on.
+// 10 iterations at d = 8, FP32 / FP64, us: 3 x 10^4 points in 64 tiles 193 / 189,
+// in one per compute unit 226 / 223; with 1, 2 and 3 tiles per compute unit
+//   10^5      238 / 237   261 / 254   258 / 254
+//   10^6      328 / 328   329 / 341   340 / 358
+//   2 x 10^6  427 / 419   402 / 432   412 / 442
+//   4 x 10^6  614 / 607   544 / 596   541 / 604
+long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu) {
+  const long long per_cu = n <= 3072ll * ncu ? 1 : n <= 12288ll * ncu ? 2 : blocks_per_cu;
+  long long tiles = (long long)ncu * std::min<long long>(per_cu, blocks_per_cu);
+  if (n <= 1 << 16) tiles = std::min<long long>(tiles, kDirectTiles);
+  return std::max(round_up((n + tiles - 1) / tiles, bs), bs);
 }
 
 bool direct_refine(const std::vector<VJob> &jobs) {
@@ -300,19 +326,17 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   struct Offsets {
     long long grid, thist, ghist, iter;
     int tile0, group0;
-    long long hsum;
   };
   std::vector<Offsets> off(n);
   std::vector<int> tile_job;
-  long long goff = 0, thoff = 0, ghoff = 0, ioff = 0, hsoff = 0;
+  long long goff = 0, thoff = 0, ghoff = 0, ioff = 0;
   int tile0 = 0, group0 = 0;
   for (int j = 0; j < n; ++j) {
     const VegasSpec &sp = specs[j];
     const int p = sp.prec;
     const int bs = block_[p];
-    const long long B = (long long)ctx_->ncu * ctx_->tune[p].blocks_per_cu;
-    long long P = single ? round_up((nmax[j] + B - 1) / B, bs) : batch_P[p];
-    P = std::max<long long>(P, bs);
+    const long long P =
+        single ? single_tile(nmax[j], bs, ctx_->ncu, ctx_->tune[p].blocks_per_cu) : batch_P[p];
     const int nt = (int)std::max<long long>(1, (nmax[j] + P - 1) / P);
     VJob &J = hjobs_[j];
     J.ndim = sp.ndim;
@@ -334,8 +358,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     J.tile_pts = P;
     J.hist_cap = std::max(1, iters[j]);
     const long long dN = (long long)sp.ndim * sp.nbins, row = (long long)sp.ndim * (sp.nbins + 1);
-    off[j] = Offsets{goff, thoff, ghoff, ioff, tile0, group0, hsoff};
-    hsoff += 2 + dN;
+    off[j] = Offsets{goff, thoff, ghoff, ioff, tile0, group0};
     goff += row;
     thoff += nt * dN;
     ghoff += ngroups_of(nt) * dN;
@@ -364,8 +387,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
       (rc = tile_sums_.reserve(ctx_, 2 * (size_t)ntiles_)) ||
       (rc = tile_hist_.reserve(ctx_, thoff)) ||
       (rc = group_sums_.reserve(ctx_, 2 * (size_t)ngroups_)) ||
-      (rc = group_hist_.reserve(ctx_, ghoff)) || (rc = fold_end_.reserve(ctx_, 2 * n)) ||
-      (rc = hsum_.reserve(ctx_, hsoff)) ||
+      (rc = group_hist_.reserve(ctx_, ghoff)) || (rc = fold_end_.reserve(ctx_, n)) ||
       (rc = iter_I_.reserve(ctx_, ioff)) || (rc = iter_var_.reserve(ctx_, ioff)))
     return rc;
 
@@ -378,7 +400,6 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     J.thist = tile_hist_.p + off[j].thist;
     J.gsums = group_sums_.p + 2ll * off[j].group0;
     J.ghist = group_hist_.p + off[j].ghist;
-    J.hsum = hsum_.p + off[j].hsum;
     J.iter_I = iter_I_.p + off[j].iter;
     J.iter_var = iter_var_.p + off[j].iter;
     J.p64 = p64_.p + (size_t)j * 2 * kParamRow;
@@ -388,7 +409,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   std::vector<float> p32((size_t)n * 2 * kParamRow);
   std::vector<VState> st(n);
   std::vector<long long> ends;
-  fold_tasks(hjobs_, ends, &fold_total_, &fold_total2_);
+  fold_tasks(hjobs_, ends, &fold_total_);
   for (int j = 0; j < n; ++j) {
     const VegasSpec &sp = specs[j];
     double a64[2][kParamRow];
@@ -410,13 +431,12 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     S.st = st[0];
     std::memcpy(S.p64, p64.data(), sizeof(S.p64));
     std::memcpy(S.p32, p32.data(), sizeof(S.p32));
-    S.ends[0] = ends[0];
-    S.ends[1] = ends[1];
+    S.end = ends[0];
     S.job_dst = jobs_.p;
     S.st_dst = state_.p;
     S.p64_dst = p64_.p;
     S.p32_dst = p32_.p;
-    S.ends_dst = fold_end_.p;
+    S.end_dst = fold_end_.p;
     S.grid_dst = grids_.p;
     CCUBA_HIP(launch_job_setup(S, s));
   } else {
@@ -441,7 +461,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   std::vector<long long> sig = {(long long)(intptr_t)jobs_.p, (long long)(intptr_t)state_.p,
                                 (long long)(intptr_t)tile_job_.p,
                                 (long long)(intptr_t)fold_end_.p, (long long)(intptr_t)user_fn_,
-                                fold_total_, fold_total2_,
+                                fold_total_,
                                 n, ntiles_, (long long)lds_refine_, hist64_[0], hist64_[1],
                                 direct_, dmax_};
   for (int p = 0; p < 2; ++p) {
@@ -461,13 +481,14 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
   return CCUBA_OK;
 }
 
-int VegasEngine::dosample_only(hipStream_t s, bool level2, hipEvent_t between) {
+int VegasEngine::dosample_only(hipStream_t s, hipEvent_t between, double *sums, double *hist) {
   const int rc = launch_tile_groups(ctx_, args_, tgroups_, s, user_fn_);
   if (rc) return rc;
   if (between) CCUBA_HIP(hipEventRecord(between, s));
-  if (direct_ && !level2) return CCUBA_OK;
-  FoldArgs F{jobs_.p, fold_end_.p, njobs(), fold_total_, fold_end_.p + njobs(), fold_total2_};
-  CCUBA_HIP(launch_fold(F, level2, s));
+  if (direct_ && !sums) return CCUBA_OK;
+  const long long dN = (long long)hjobs_[0].ndim * hjobs_[0].nbins;
+  FoldArgs F{jobs_.p, fold_end_.p, njobs(), fold_total_, (dN + 63) / 64, sums, hist};
+  CCUBA_HIP(launch_fold(F, s));
   return CCUBA_OK;
 }
 
@@ -478,7 +499,7 @@ int VegasEngine::launch_iteration(hipStream_t s) {
     hipEvent_t ev[4];
     for (auto &e : ev) CCUBA_HIP(hipEventCreate(&e));
     CCUBA_HIP(hipEventRecord(ev[0], s));
-    int rc = dosample_only(s, false, ev[1]);
+    int rc = dosample_only(s, ev[1]);
     if (rc) return rc;
     CCUBA_HIP(hipEventRecord(ev[2], s));
     CCUBA_HIP(launch_refine(args_, njobs(), dmax_, direct_, s));
@@ -766,11 +787,6 @@ int VegasEngine::load_grid(int job, const double *src, hipMemcpyKind kind, hipSt
   const long long row = (long long)J.ndim * (J.nbins + 1);
   CCUBA_HIP(hipMemcpyAsync(J.grid, src, row * sizeof(double), kind, s));
   if (kind == hipMemcpyHostToDevice) CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
-}
-
-int VegasEngine::collect(double *sums_dev, double *hist_dev, hipStream_t s) {
-  CCUBA_HIP(launch_collect(args_, 1, sums_dev, hist_dev, s));
   return CCUBA_OK;
 }
 

@@ -45,6 +45,11 @@ struct TileGroup {
   int hfx;  // 1: the fixed-point LDS histogram instance
 };
 
+// Dynamic LDS of a DoSample instance (the layouts of vegas_sample.h) for an
+// integral of dimension d with N bins; *hist_off: where its histogram starts
+// when that is not a constant of the instance.
+size_t dosample_lds(int prec, bool fixed, int nb, bool pow2, int d, int N, size_t *hist_off);
+
 // Whether the DoSample launch of a class takes the fixed-point LDS histogram:
 // unless hist64 asks for the FP64 one, or (FP64 evaluation: 16-byte cells and
 // three histogram words per bin) the class's largest d N would not fit the LDS.
@@ -60,10 +65,12 @@ void plan_tile_groups(std::vector<VJob> &jobs, std::vector<int> &tiles,
 // kernel of the one class of a caller's device integrand.
 int launch_tile_groups(ccuba_ctx *ctx, VegasArgs A, const std::vector<TileGroup> &groups,
                        hipStream_t s, hipFunction_t user = nullptr);
-// Inclusive prefixes over jobs of their fold tasks, both levels (see
-// FoldArgs); ends holds level 1 then level 2 (2 * njobs entries).
-void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total,
-                long long *total2);
+// Inclusive prefixes over jobs of their fold tasks (see FoldArgs).
+void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total);
+// Points of a tile of a single integral whose largest iteration has n points,
+// a multiple of bs (its block): about one tile per block, of at most
+// blocks_per_cu blocks on each of ncu compute units.
+long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu);
 
 // Whether the refine launch can sum every job's tile rows itself (no fold).
 bool direct_refine(const std::vector<VJob> &jobs);
@@ -112,15 +119,14 @@ class VegasEngine {
   // The grid and iteration t's estimate and variance of one job, read with
   // one synchronisation (what a checkpoint needs after each iteration).
   int read_step(int job, int t, double *grid, double *I, double *var, hipStream_t s);
-  // Raw pieces: set iteration index of job 0, run DoSample only, and sum the
-  // group partials into caller buffers.
+  // Raw pieces: set iteration index of job 0, run DoSample only.
   int set_iteration(int job, int t, hipStream_t s);
   int load_grid(int job, const double *src, hipMemcpyKind kind, hipStream_t s);
-  // the sampling kernels, then the fold (with level2 both levels, into
-  // hsum; without, only where the refine launch needs it); records `between`
-  // (if given) after the sampling kernels
-  int dosample_only(hipStream_t s, bool level2 = false, hipEvent_t between = nullptr);
-  int collect(double *sums_dev, double *hist_dev, hipStream_t s);
+  // the sampling kernels, then the fold (both levels, into the one job's sums
+  // and hist where they are given; else only where the refine launch needs
+  // it); records `between` (if given) after the sampling kernels
+  int dosample_only(hipStream_t s, hipEvent_t between = nullptr, double *sums = nullptr,
+                    double *hist = nullptr);
   // One refinement of job 0 from a given histogram and grid.
   int refine_only(const double *hist, const double *grid_in, double *grid_out, hipStream_t s);
 
@@ -170,8 +176,7 @@ class VegasEngine {
       iter_var_;
   DevBuf<float> p32_;
   DevBuf<long long> fold_end_;
-  DevBuf<double> hsum_;
-  long long fold_total_ = 0, fold_total2_ = 0;
+  long long fold_total_ = 0;
   VegasArgs args_{};
   bool direct_ = false;  // the refine launch sums the tile rows (direct_refine)
   int ntiles_ = 0, ngroups_ = 0;

@@ -31,12 +31,4 @@ __device__ __forceinline__ double wave_reduce63_sum(double v) {
   return wave_reduce63(v, 0.0, [](double a, double b) { return a + b; });
 }
 
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ double uniform(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readfirstlane((int)b);
-  const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 }  // namespace ccuba
