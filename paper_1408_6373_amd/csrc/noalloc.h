@@ -28,8 +28,8 @@ struct JobSetup {
   long long end;  // the fold tasks of the one job
   VJob *job_dst;        // (null: the descriptor is not wanted)
   VState *st_dst;
-  double *p64_dst;
-  float *p32_dst;
+  double *p64_dst;      // (null: not wanted)
+  float *p32_dst;       // (null: not wanted)
   long long *end_dst;   // (null: not wanted)
   double *grid_dst;     // the uniform starting grid goes here (null: none)
 };

@@ -53,8 +53,8 @@ __global__ void __launch_bounds__(256) job_setup_kernel(JobSetup S) {
   static_assert(sizeof(VJob) % 4 == 0 && sizeof(VState) % 4 == 0, "whole words");
   if (S.job_dst) copy_words(S.job_dst, &S.job, (int)sizeof(VJob), tid);
   copy_words(S.st_dst, &S.st, (int)sizeof(VState), tid);
-  copy_words(S.p64_dst, S.p64, (int)sizeof(S.p64), tid);
-  copy_words(S.p32_dst, S.p32, (int)sizeof(S.p32), tid);
+  if (S.p64_dst) copy_words(S.p64_dst, S.p64, (int)sizeof(S.p64), tid);
+  if (S.p32_dst) copy_words(S.p32_dst, S.p32, (int)sizeof(S.p32), tid);
   if (S.end_dst && tid == 0) *S.end_dst = S.end;
   if (S.grid_dst) {  // E_j[k] = k/N
     const int N = S.job.nbins, row = N + 1, tot = S.job.ndim * row;

@@ -46,7 +46,7 @@ struct PointsArgs {
   uint32_t *words;     // npts * 4 * ceil(ndim/4)
   double *x;           // npts * ndim
   double *w;           // npts
-  int *bin;            // npts * ndim
+  int *bin;            // npts * ndim (null: not wanted; nor are words)
 };
 
 // Caller-evaluated integrands (points in batches; see vegas_batched.cpp).
@@ -58,7 +58,9 @@ struct BatchedArgs {
   int tile_base;        // row of the batch's first tile
   const double *w;      // [npts]
   const double *f;      // [npts][ncomp]
-  const int *bin;       // [npts][ndim]
+  uint32_t key0, key1, sid;  // the points' words, made again for their bins
+  int iteration;
+  long long i0;
   double *rows;         // [tiles][2 ncomp + ndim nbins]: S1, S2 per component, H
   const VState *state;  // [ncomp]: the shift of each component's sums
 };
@@ -73,6 +75,7 @@ struct BatchedFinishArgs {
   int pad;
   long long nstart, nincrease, mineval, maxeval;
   double epsrel, epsabs;
+  VState *out;               // [ncomp], mapped host memory: the states again
 };
 #ifndef CCUBA_RTC  // host launchers (not part of a run-time compiled kernel)
 // One tile row per block of tile_pts points of the batch.

@@ -104,3 +104,49 @@ def test_cuhre_selection_of_tiny_errors_matches_oracle(cc, ctx, d, a0, batch, re
     assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
     assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
     assert abs(g["error"] - o["error"]) <= 1e-10 * o["error"] + 1e-14 * abs(o["integral"])
+
+
+# ---- a device integrand's batches, the next one made ahead ------------------
+
+@pytest.mark.parametrize("nbins,prec,nvec,nstart", [
+    (64, 64, 1000, 1000),    # one batch an iteration
+    (100, 64, 1000, 2001),   # the last batch one point; bins not a power of two
+    (100, 32, 4096, 12288),  # whole batches of whole tiles, odd number of them
+    (128, 32, 4097, 9000),   # ragged tiles
+])
+def test_device_batches_match_host_batches(cc, ctx, nbins, prec, nvec, nstart):
+    # the integrand only multiplies, so that both sides compute the same bits,
+    # and the sums differ only by the LDS histogram's order
+    import torch
+    flags = cc.FP32_EVAL if prec == 32 else cc.FP64
+    kw = dict(ctx=ctx, nvec=nvec, nstart=nstart, nincrease=nvec, maxeval=5 * nstart + 10 * nvec,
+              nbins=nbins, flags=flags, seed=4)
+    seen = []
+
+    def fdev(x, f):
+        seen.append(len(x))
+        f.copy_(torch.stack((x[:, 0] * x[:, 1], x[:, 2] * 0.5 + 0.25), 1))
+
+    host = []
+
+    def fhost(x):
+        host.append(len(x))
+        return np.stack((x[:, 0] * x[:, 1], x[:, 2] * 0.5 + 0.25), 1)
+
+    g = cc.vegas_batched(fdev, 3, 2, where="device", **kw)
+    h = cc.vegas_batched(fhost, 3, 2, **kw)
+    assert seen == host and g["neval"] == h["neval"] and g["fail"] == h["fail"] == 1
+    np.testing.assert_allclose(g["integral"], h["integral"], rtol=1e-12)
+    np.testing.assert_allclose(g["error"], h["error"], rtol=1e-10)
+    # an integrand that stops while the next batch's points are being made
+    seen.clear()
+    full = fdev
+
+    def stop(x, f):
+        full(x, f)
+        return -999 if len(seen) == 2 else 0
+
+    r = cc.vegas_batched(stop, 3, 2, where="device", **kw)
+    assert r["fail"] == -99 and r["neval"] == sum(host[:2])
+    again = cc.vegas_batched(fdev, 3, 2, where="device", **kw)
+    np.testing.assert_allclose(again["integral"], h["integral"], rtol=1e-12)
