@@ -320,9 +320,7 @@ int Server::tick() {
   if (!table.empty()) {
     size_t refb = 0;
     const int h64[2] = {ctx_->tune[0].hist64, ctx_->tune[1].hist64};
-    const long long blocks[2] = {(long long)ctx_->ncu * ctx_->tune[0].blocks_per_cu,
-                                 (long long)ctx_->ncu * ctx_->tune[1].blocks_per_cu};
-    plan_tile_groups(table, tiles, groups, h64, blocks, &refb);
+    plan_tile_groups(table, tiles, groups, h64, &refb);
     if (jobs_.n < table.size() && (rc = jobs_.alloc(ctx_, table.size() * 2))) return rc;
     if (tiles_.n < tiles.size() && (rc = tiles_.alloc(ctx_, tiles.size() * 2))) return rc;
     CCUBA_HIP(hipMemcpyAsync(jobs_.p, table.data(), table.size() * sizeof(VJob),

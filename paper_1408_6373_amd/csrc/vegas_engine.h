@@ -56,11 +56,10 @@ size_t dosample_lds(int prec, bool fixed, int nb, bool pow2, int d, int N, size_
 bool fixed_hist(int prec, int hist64, long long dN);
 
 // Order the tiles of `jobs' by class, set each job's tile0 to the position of
-// its first tile, and describe the classes.  blocks: the persistent blocks of
-// a launch, per precision.  Also returns the refine LDS.
+// its first tile, and describe the classes.  Also returns the refine LDS.
 void plan_tile_groups(std::vector<VJob> &jobs, std::vector<int> &tiles,
                       std::vector<TileGroup> &groups, const int hist64[2],
-                      const long long blocks[2], size_t *refine_lds);
+                      size_t *refine_lds);
 // One DoSample launch per class; `user' (if given) is the run-time compiled
 // kernel of the one class of a caller's device integrand.
 int launch_tile_groups(ccuba_ctx *ctx, VegasArgs A, const std::vector<TileGroup> &groups,
