@@ -98,8 +98,9 @@ constexpr int kTopGroup = 64;   // boundary keys ranked directly
 // differ, until at most 64 keys share the boundary digits (they rank
 // themselves) or all that do are taken; then a bitonic sort of the K winners.
 // One workgroup: latency.  Up to 8192 keys stay in registers over the passes.
-// 1024 of up to 8192 keys: 18.9 us on average, 24.3 with eight passes that
-// read the keys from memory each time; 64 of up to 1000: 10.8 from 14.8.
+// 1024 of up to 8192 keys: 14.7 us on average, 17.6 with every step of the sort
+// through LDS, 24.3 with eight passes that read the keys from memory as well; 64
+// of up to 1000: 9.5, 10.4 and 14.8.
 __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, int K, int *sel) {
   __shared__ unsigned hist[2][256];
   __shared__ unsigned long long wmax[16], wmin[16];
@@ -248,27 +249,37 @@ __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, in
     }
   }
   __syncthreads();
-  // bitonic sort: larger key first, then lower position
+  // bitonic sort, an element a thread: larger key first, then lower position.
+  // Partners of the same wavefront exchange by shuffles; only strides from 64 on go
+  // through LDS and its barriers (10 of the 55 steps for 1024 elements).
+  unsigned long long mk = tid < P ? skey[tid] : 0;
+  int mp = tid < P ? spos[tid] : 0;
   for (int size = 2; size <= P; size <<= 1)
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = tid; i < P; i += 1024) {
-        const int jx = i ^ stride;
-        if (jx > i) {
-          const bool up = (i & size) == 0;
-          const unsigned long long ka = skey[i], kb = skey[jx];
-          const int pa = spos[i], pb = spos[jx];
-          const bool a_first = ka > kb || (ka == kb && pa < pb);
-          if (a_first != up) {
-            skey[i] = kb;
-            skey[jx] = ka;
-            spos[i] = pb;
-            spos[jx] = pa;
-          }
+      unsigned long long ok;
+      int op;
+      if (stride >= 64) {
+        __syncthreads();
+        if (tid < P) {
+          skey[tid] = mk;
+          spos[tid] = mp;
         }
+        __syncthreads();
+        if (tid >= P) continue;
+        ok = skey[tid ^ stride];
+        op = spos[tid ^ stride];
+      } else {
+        if ((tid & ~63) >= P) continue;  // (whole wavefronts)
+        ok = (unsigned long long)__shfl_xor((long long)mk, stride, 64);
+        op = __shfl_xor(mp, stride, 64);
       }
-      __syncthreads();
+      const bool first = mk > ok || (mk == ok && mp < op);
+      if (first != (((tid & stride) == 0) == ((tid & size) == 0))) {
+        mk = ok;
+        mp = op;
+      }
     }
-  for (int i = tid; i < K; i += 1024) sel[i] = spos[i];
+  if (tid < K) sel[tid] = mp;
 }
 
 // Split statistics in two passes over each selected region's sample, both

@@ -117,7 +117,9 @@ def count(asm_text):
                 if best is None or len(v) > len(best):
                     best = v
             if best:
-                fam_slots[FAMILIES[fam]] = sum(_weight(o) for o in best) / int(ilp)
+                # (an instance for several d has a loop for each: the largest)
+                slots = sum(_weight(o) for o in best) / int(ilp)
+                fam_slots[FAMILIES[fam]] = max(slots, fam_slots.get(FAMILIES[fam], 0.0))
         key = "%s%s_ilp%s_nb%s%s%s" % ({"f": "f32", "d": "f64"}[T], {"y": "hfx", "d": "h64"}[H],
                                        ilp, nb, "_pow2" if pow2 == "1" else "",
                                        "_full" if full == "1" else "")
