@@ -150,3 +150,75 @@ def test_device_batches_match_host_batches(cc, ctx, nbins, prec, nvec, nstart):
     assert r["fail"] == -99 and r["neval"] == sum(host[:2])
     again = cc.vegas_batched(fdev, 3, 2, where="device", **kw)
     np.testing.assert_allclose(again["integral"], h["integral"], rtol=1e-12)
+
+
+# ---- DoSample: every dimension, both LDS layouts, what is left of a tile ----
+
+def _rel(a, b):
+    return abs(a - b) / max(abs(b), 1e-300)
+
+
+def _all_dims(flags, nbins):
+    specs = []
+    for d in range(1, 17):
+        a, u = W.genz_params(d % 5, d, 40 + d)
+        n = 40961 + 127 * d
+        specs.append(dict(method=0, ndim=d, family=d % 5, a=a, u=u, seed=d, nstart=n,
+                          maxeval=3 * n, nbins=nbins, flags=flags))
+    return specs
+
+
+def _run_batch(cc, specs, ilp, hist64):
+    c = cc.Context()
+    c.config("ilp", ilp)
+    c.config("hist64", hist64)
+    res = cc.vegas_batch(c, specs)
+    c.close()
+    return res
+
+
+@pytest.mark.parametrize("nbins,ilp,hist64", [
+    (64, 2, 0),   # a fixed-point histogram of two words after the cells
+    (256, 2, 0),
+    (64, 1, 1),   # an FP64 histogram in its region before the cells
+    (256, 1, 1),
+    (2, 1, 0),
+    (100, 2, 0),  # bins not a power of two: cells first
+])
+def test_every_dimension_in_one_batch(cc, nbins, ilp, hist64):
+    # d = 1 to 16 with points that leave odd parts of trips and tiles; integrals of
+    # all dimensions of a block count share a launch
+    specs = _all_dims(cc.FP64, nbins)
+    for s, r in zip(specs, _run_batch(cc, specs, ilp, hist64)):
+        o = O.vegas(O.genz(s["family"], s["a"], s["u"]), s["ndim"], seed=s["seed"],
+                    nstart=s["nstart"], maxeval=s["maxeval"], nbins=nbins)
+        assert r["status"] == 0 and r["neval"] == o["neval"] and r["fail"] == o["fail"]
+        assert _rel(r["integral"], o["integral"]) < 1e-12, s["ndim"]
+        assert _rel(r["error"], o["error"]) < 1e-11, s["ndim"]
+
+
+@pytest.mark.parametrize("nbins", [2, 64, 100, 256])
+def test_fp32_layouts_and_trips_agree(cc, nbins):
+    # FP32 evaluation: the points and their values are the same whatever the
+    # histogram's type and place and the points per trip; only the order of the sums
+    # differs (the bar of the fixed-point histogram's own test)
+    specs = _all_dims(cc.FP32_EVAL, nbins)
+    base = _run_batch(cc, specs, 1, 1)
+    for ilp, hist64 in ((1, 0), (2, 0), (2, 1)):
+        for s, r, b in zip(specs, _run_batch(cc, specs, ilp, hist64), base):
+            assert r["status"] == 0 and r["neval"] == b["neval"] and r["fail"] == b["fail"]
+            assert _rel(r["integral"], b["integral"]) < 1e-12, (ilp, hist64, s["ndim"])
+            assert _rel(r["error"], b["error"]) < 1e-12, (ilp, hist64, s["ndim"])
+
+
+@pytest.mark.parametrize("n", [65536, 65537, 3072 * 256, 3072 * 256 + 1])
+def test_tiles_of_a_single_integral(cc, ctx, n):
+    # the sizes where the tiles of an iteration change: 64 tiles and no fold up to
+    # 65536 points, then one and two tiles per compute unit
+    a, u = W.genz_params(0, 3, 12)
+    kw = dict(nbins=64, nstart=n, maxeval=2 * n, seed=6)
+    g = cc.vegas(0, a, u, ctx=ctx, **kw)
+    o = O.vegas(O.genz(0, a, u), 3, **kw)
+    assert g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert _rel(g["integral"], o["integral"]) < 1e-12
+    assert _rel(g["error"], o["error"]) < 1e-11
