@@ -1147,17 +1147,16 @@ int ccuba_vegas_batch(ccuba_ctx *ctx, int njobs, const ccuba_job jobs[], ccuba_r
   const std::vector<VegasSpec> half0(specs.begin(), specs.begin() + cut),
       half1(specs.begin() + cut, specs.end());
   std::vector<VState> st, st1;
-  int rc = CCUBA_OK;
-  if (!split) {
-    rc = run_batch_engine(ctx, half0, st);
-  } else {
+  auto run_all = [&]() -> int {
+    if (!split) return run_batch_engine(ctx, half0, st);
     // In profile mode the halves' sampling launches are timed against one
     // reference event that both streams start after, and the context's busy
     // time gets the union of their intervals.
     hipEvent_t ref = nullptr;
     std::vector<std::pair<double, double>> iv;
     if (ctx->profile) {
-      if ((rc = second_stream(ctx))) return rc;
+      const int src = second_stream(ctx);
+      if (src) return src;
       CCUBA_HIP(hipEventCreate(&ref));
       if (hipEventRecord(ref, ctx->stream) != hipSuccess ||
           hipStreamWaitEvent(ctx->stream2, ref, 0) != hipSuccess) {
@@ -1165,12 +1164,20 @@ int ccuba_vegas_batch(ccuba_ctx *ctx, int njobs, const ccuba_job jobs[], ccuba_r
         return CCUBA_EHIP;
       }
     }
-    rc = run_halves(ctx, half0, half1, st, st1, ref, iv);
+    const int hrc = run_halves(ctx, half0, half1, st, st1, ref, iv);
     if (ref) {
       std::lock_guard<std::mutex> g(ctx->stats_lock);
       ctx->stats.dosample_busy_ms += union_length(iv);
       (void)hipEventDestroy(ref);
     }
+    return hrc;
+  };
+  int rc = run_all();
+  if (rc == CCUBA_ENOMEM) {  // once more with fewer tile rows
+    const long long keep[2] = {ctx->tune[0].min_tile, ctx->tune[1].min_tile};
+    for (int p = 0; p < 2; ++p) ctx->tune[p].min_tile = std::max(keep[p], kTightTile);
+    rc = run_all();
+    for (int p = 0; p < 2; ++p) ctx->tune[p].min_tile = keep[p];
   }
   if (rc) return rc;
   st.insert(st.end(), st1.begin(), st1.end());

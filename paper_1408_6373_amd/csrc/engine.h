@@ -84,6 +84,10 @@ __host__ __device__ inline int ngroups_of(int ntiles) { return (ntiles + kGroupT
 // Flags understood by the device code.
 enum { FLAG_FREEZE_GRID = 1 << 4 };
 
+// Points of a batch's or a served request's smallest tile where the memory budget
+// refuses the setting's: fewer rows of partial results for longer launches.
+constexpr long long kTightTile = 16384;
+
 // Launch geometry of the DoSample kernel.
 struct VegasTune {
   int block = 256;        // threads per block
@@ -91,7 +95,7 @@ struct VegasTune {
   int hist64 = 0;         // 1 = FP64 LDS histogram, 0 = the exact 64-bit fixed-point one
   int ilp = 1;            // points per lane per trip (1 or 2)
   int tiles_per_job = 0;  // 0 = automatic (one tile per persistent block)
-  long long min_tile = 4096;
+  long long min_tile = 2048;
   int streams = 2;        // a batch of 2+ integrals: 2 = two halves on two streams
 };
 

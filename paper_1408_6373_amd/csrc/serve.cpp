@@ -185,18 +185,25 @@ int Server::activate(Req &r) {
   vegas_budget(sp, &iters, &nmax);
   const int bs = ctx_->tune[sp.prec].block;
   auto round_up = [](long long v, long long m) { return (v + m - 1) / m * m; };
-  const long long P = std::max(round_up(ctx_->tune[sp.prec].min_tile, bs),
-                               round_up((nmax + 63) / 64, bs));
-  const int nt = (int)std::max<long long>(1, (nmax + P - 1) / P), ng = ngroups_of(nt);
   const long long dN = (long long)sp.ndim * sp.nbins, row = (long long)sp.ndim * (sp.nbins + 1);
   const int cap = std::max(1, iters);
-  int rc;
-  if ((rc = r.grid.alloc(ctx_, row)) || (rc = r.tsums.alloc(ctx_, 2 * nt)) ||
-      (rc = r.thist.alloc(ctx_, nt * dN)) || (rc = r.gsums.alloc(ctx_, 2 * ng)) ||
-      (rc = r.ghist.alloc(ctx_, ng * dN)) ||
-      (rc = r.iters.alloc(ctx_, 2 * (size_t)cap)) ||
-      (rc = r.p64.alloc(ctx_, 2 * kParamRow)) || (rc = r.p32.alloc(ctx_, 2 * kParamRow)))
-    return rc;
+  const long long least = ctx_->tune[sp.prec].min_tile;
+  long long P = 0;
+  int nt = 0, rc = CCUBA_ENOMEM;
+  for (long long tile : {least, std::max(least, kTightTile)}) {
+    P = std::max(round_up(tile, bs), round_up((nmax + 63) / 64, bs));
+    nt = (int)std::max<long long>(1, (nmax + P - 1) / P);
+    const int ng = ngroups_of(nt);
+    r.thist.release();
+    if (!(rc = r.grid.alloc(ctx_, row)) && !(rc = r.tsums.alloc(ctx_, 2 * nt)) &&
+        !(rc = r.thist.alloc(ctx_, nt * dN)) && !(rc = r.gsums.alloc(ctx_, 2 * ng)) &&
+        !(rc = r.ghist.alloc(ctx_, ng * dN)) &&
+        !(rc = r.iters.alloc(ctx_, 2 * (size_t)cap)) &&
+        !(rc = r.p64.alloc(ctx_, 2 * kParamRow)) && !(rc = r.p32.alloc(ctx_, 2 * kParamRow)))
+      break;
+    if (rc != CCUBA_ENOMEM) return rc;
+  }
+  if (rc) return rc;
   if (free_slots_.empty()) return CCUBA_ENOMEM;
   r.slot = free_slots_.back();
   free_slots_.pop_back();

@@ -222,3 +222,43 @@ def test_tiles_of_a_single_integral(cc, ctx, n):
     assert g["neval"] == o["neval"] and g["fail"] == o["fail"]
     assert _rel(g["integral"], o["integral"]) < 1e-12
     assert _rel(g["error"], o["error"]) < 1e-11
+
+
+# ---- memory budgets that refuse the rows of the smallest tiles --------------
+
+def _wide(cc, n, jobs):
+    # d = 16 with 256 bins: 32 KiB a tile row
+    specs = []
+    for q in range(jobs):
+        a, u = W.genz_params(0, 16, 60 + q)
+        specs.append(dict(method=0, ndim=16, family=0, a=a, u=u, seed=q + 1, nstart=n,
+                          maxeval=2 * n, nbins=256, flags=cc.FP64))
+    return specs
+
+
+def test_batch_under_a_tight_budget_takes_larger_tiles(cc, ctx):
+    # 8 x 65536 points: 8 MiB of rows of about 2048 points, 1 MiB of 16384
+    specs = _wide(cc, 65536, 8)
+    c = cc.Context(hbm_budget=6 << 20)
+    before = c.config_get("min_tile")
+    got = cc.vegas_batch(c, specs)
+    assert c.config_get("min_tile") == before
+    c.close()
+    for r, w in zip(got, cc.vegas_batch(ctx, specs)):
+        assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
+        assert _rel(r["integral"], w["integral"]) < 1e-12
+        assert _rel(r["error"], w["error"]) < 1e-11
+
+
+def test_served_request_under_a_tight_budget_takes_larger_tiles(cc, ctx):
+    # 131072 points: 2 MiB in rows of 2048 points, 256 KiB of 16384
+    spec = _wide(cc, 131072, 1)[0]
+    c = cc.Context(hbm_budget=1536 << 10)
+    t = cc.submit(c, spec)
+    cc.drain(c)
+    r = cc.poll(c, t)
+    c.close()
+    w = cc.vegas_batch(ctx, [spec])[0]
+    assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
+    assert _rel(r["integral"], w["integral"]) < 1e-12
+    assert _rel(r["error"], w["error"]) < 1e-11
