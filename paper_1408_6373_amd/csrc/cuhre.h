@@ -161,6 +161,16 @@ hipError_t launch_totals(const CRegions &R, long long m, const CScratch &S, doub
 // The root region of [0,1]^d (centre 1/2, half-width 1/2) at position 0, and
 // the run's stop flag cleared (done may be null).
 hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t s);
+// What a run finds before its first launch: the integrand's constants, passed by
+// value, and a cleared histogram and parent list.
+struct CSetup {
+  double params[2][kParamRow];
+  double *params_dst;
+  unsigned *hist;     // [kTopBins]
+  long long *parent;  // [nparent]
+  long long nparent;
+};
+hipError_t launch_cuhre_setup(const CSetup &S, hipStream_t s);
 long long scratch_blocks(long long n);
 
 }  // namespace ccuba

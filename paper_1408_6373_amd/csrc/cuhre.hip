@@ -1630,6 +1630,26 @@ hipError_t launch_grow(const GrowArgs &A, int family, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One launch in place of two fills and an upload: a run of some 200 us otherwise
+// starts with 15 us of them.
+constexpr int kSetupPer = 2048;  // parent entries of a block
+
+static __global__ void __launch_bounds__(256) cuhre_setup_kernel(CSetup S) {
+  const int tid = threadIdx.x;
+  const long long p0 = (long long)blockIdx.x * kSetupPer;
+  const long long p1 = min(p0 + kSetupPer, S.nparent);
+  for (long long p = p0 + tid; p < p1; p += 256) S.parent[p] = 0;
+  if (blockIdx.x > 0) return;
+  for (int k = tid; k < kTopBins; k += 256) S.hist[k] = 0;
+  if (tid < 2 * kParamRow) S.params_dst[tid] = S.params[tid / kParamRow][tid % kParamRow];
+}
+
+hipError_t launch_cuhre_setup(const CSetup &S, hipStream_t s) {
+  const long long blocks = S.nparent > kSetupPer ? (S.nparent + kSetupPer - 1) / kSetupPer : 1;
+  hipLaunchKernelGGL(cuhre_setup_kernel, dim3((unsigned)blocks), dim3(256), 0, s, S);
+  return hipGetLastError();
+}
+
 hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t s) {
   hipLaunchKernelGGL(cuhre_root_kernel, dim3(1), dim3(64), 0, s, R, ndim, done);
   return hipGetLastError();

@@ -59,8 +59,9 @@ int CuhreRun::alloc_store(CRegions &R, DevBuf<double> &cb, DevBuf<double> &hb,
   return CCUBA_OK;
 }
 
-// Scratch sized for a store of cap regions.
-int CuhreRun::alloc_scratch(long long cap, hipStream_t s) {
+// Scratch sized for a store of cap regions.  (The parents are cleared by the
+// caller: positions read by a rule launch are always in the store.)
+int CuhreRun::alloc_scratch(long long cap) {
   int rc;
   const long long nb = scratch_blocks(cap);
   rows_stride_ = step_rows(cap);
@@ -69,8 +70,6 @@ int CuhreRun::alloc_scratch(long long cap, hipStream_t s) {
       (rc = parent_.alloc(ctx_, cap / 2 + 1)) || (rc = cand_key_.alloc(ctx_, cap)) ||
       (rc = cand_pos_.alloc(ctx_, cap)))
     return rc;
-  // (positions read by a rule launch are always in the store)
-  CCUBA_HIP(hipMemsetAsync(parent_.p, 0, parent_.n * sizeof(long long), s));
   S_.cand_key = cand_key_.p;
   S_.cand_pos = cand_pos_.p;
   S_.parent = parent_.p;
@@ -112,7 +111,9 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
         CCUBA_HIP(hipMemcpyAsync(R.axis, O.axis, m * 4, hipMemcpyDeviceToDevice, s));
       }
       CCUBA_HIP(hipStreamSynchronize(s));
-      rc = alloc_scratch(cap, s);
+      rc = alloc_scratch(cap);
+      if (rc == CCUBA_OK)
+        CCUBA_HIP(hipMemsetAsync(parent_.p, 0, parent_.n * sizeof(long long), s));
     }
     if (rc == CCUBA_OK) break;
     if (rc != CCUBA_ENOMEM || cap <= need) return rc;
@@ -158,8 +159,6 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   S_.window = stop_.p + 1;
   S_.hist = hist_.p;
   S_.cand_cnt = cand_cnt_.p;
-  // (a split leaves the histogram cleared after every selection)
-  CCUBA_HIP(hipMemsetAsync(hist_.p, 0, kTopBins * sizeof(unsigned), s));
   S_.prefix = prefix_.p;
   S_.krem = krem_.p;
   // room for the first few batches, so that the store rarely grows (growing
@@ -172,7 +171,7 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
   long long cap0 = first_cap;
   for (;;) {
     rc = alloc_store(R_, c_, h_, vals_, axis_, cap0);
-    if (rc == CCUBA_OK) rc = alloc_scratch(cap0, s);
+    if (rc == CCUBA_OK) rc = alloc_scratch(cap0);
     if (rc != CCUBA_ENOMEM) break;
     const long long small = std::max<long long>(
         16, std::min<long long>(2 * spec.batch + 1, spec.maxeval / np_ + 2));
@@ -190,9 +189,13 @@ int CuhreRun::start(const CuhreSpec &spec, hipStream_t s, bool root) {
     vs.u[j] = spec.u[j];
   }
   float p32[2][kParamRow];
-  genz_constants(vs, hp64_, p32);
-  // (the host source is a member, alive while the copy runs)
-  CCUBA_HIP(hipMemcpyAsync(params_.p, hp64_, sizeof(hp64_), hipMemcpyHostToDevice, s));
+  CSetup setup{};
+  genz_constants(vs, setup.params, p32);
+  setup.params_dst = params_.p;
+  setup.hist = hist_.p;  // (a split leaves it cleared after every selection)
+  setup.parent = parent_.p;
+  setup.nparent = (long long)parent_.n;
+  CCUBA_HIP(launch_cuhre_setup(setup, s));
   rooted_ = false;
   return root ? launch_root(s) : CCUBA_OK;
 }

@@ -71,7 +71,7 @@ class CuhreRun {
   int ensure(long long need, hipStream_t s);
   int alloc_store(CRegions &R, DevBuf<double> &cb, DevBuf<double> &hb, DevBuf<double> &vals,
                   DevBuf<int> &ax, long long cap);
-  int alloc_scratch(long long cap, hipStream_t s);
+  int alloc_scratch(long long cap);
   // The segment of the 2K children of step with K splits: formed from the
   // live regions [next_id_ - n_, next_id_) when all split and they are
   // contiguous, else from the positions launch_split wrote.
@@ -106,7 +106,6 @@ class CuhreRun {
   DevBuf<CSeg> seg_;
   DevBuf<long long> seg_end_;
   CScratch S_{};
-  double hp64_[2][kParamRow];  // host source of the parameter upload
   double *mapped_host_ = nullptr, *mapped_dev_ = nullptr;
 };
 
