@@ -62,13 +62,14 @@ __device__ inline double gamma_p(double a, double x) {
 // prefix-sum interval holds its share, by the lane that owns that bin (the
 // bin a binary search of the prefix sums would find).  h, dd and Eo are LDS
 // rows (h is overwritten with the prefix sums); En receives the N + 1 new
-// edges.
+// edges: the old ones where the row's sum is not above zero (a NaN in it
+// included) or gives no shares to place edges by (it overflows).
 __device__ __forceinline__ void rebin_dimension(double *h, double *dd, const double *Eo,
                                                 double *En, int N, int lane) {
   const int per = (N + 63) >> 6;  // contiguous bins per lane
   const int k0 = lane * per, k1 = min(k0 + per, N);
   // smoothing and the row's sum
-  bool any = false;
+  bool any = false, odd = false;  // (odd: a negative bin or a NaN)
   double ds = 0.0;
   for (int k = k0; k < k1; ++k) {
     double v;
@@ -79,11 +80,19 @@ __device__ __forceinline__ void rebin_dimension(double *h, double *dd, const dou
     else
       v = (h[k - 1] + h[k] + h[k + 1]) / 3.0;
     any = any || h[k] > 0.0;
+    odd = odd || !(h[k] >= 0.0);
     ds += v;
     dd[k] = v;
   }
   ds = wave_sum(ds);
-  if (!__any(any)) {  // nothing sampled in this dimension: the edges are kept
+  // Among bins from zero up the sum is above zero if any bin is.
+  bool sampled = __any(any);
+  if (__any(odd)) {
+    double hs = 0.0;
+    for (int k = k0; k < k1; ++k) hs += h[k];
+    sampled = wave_sum(hs) > 0.0;
+  }
+  if (!sampled) {  // nothing sampled in this dimension
     for (int i = lane; i <= N; i += 64) En[i] = Eo[i];
     return;
   }
@@ -112,6 +121,10 @@ __device__ __forceinline__ void rebin_dimension(double *h, double *dd, const dou
   }
   wave_sync_lds();
   const double share = h[N - 1] / N;
+  if (!(share > 0.0 && share < INFINITY)) {
+    for (int i = lane; i <= N; i += 64) En[i] = Eo[i];
+    return;
+  }
   // new edge i (0 < i < N) lies in the smallest old bin k with C_k >= i *
   // share (the last bin if there is none): each lane places the edges of its
   // own bins, those with C_{k-1} < i * share <= C_k, a contiguous run of i
