@@ -722,9 +722,7 @@ int ccuba_vegas_dosample_raw(ccuba_ctx *ctx, int ndim, int nbins, const ccuba_in
   if ((rc = eng.set_iteration(0, iteration, s))) return rc;
   if ((rc = eng.load_grid(0, grid_dev, hipMemcpyDeviceToDevice, s))) return rc;
   if ((rc = eng.dosample_only(s, nullptr, sums_dev, hist_dev))) return rc;
-  // the engine's buffers are released on return: finish before that
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return eng.drain(s);
 }
 
 int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,

@@ -255,6 +255,9 @@ bool direct_refine(const std::vector<VJob> &jobs) {
 }
 
 VegasEngine::~VegasEngine() {
+  // (after an error too: the pool that takes the buffers back knows no streams,
+  // and may hand them to another one while a launch still writes them)
+  if (busy_) (void)hipStreamSynchronize(busy_);
   for (auto &g : graphs_) (void)hipGraphExecDestroy(g.exec);
 }
 
@@ -416,6 +419,7 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
       st[j].fail = 1;
     }
   }
+  busy_ = s;
   if (n == 1) {
     // one launch instead of six uploads and the grid's (each upload is staged
     // and waited for); with one job the kernels look no tile up
@@ -470,11 +474,17 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     graph_sig_ = sig;
   }
   // host copies of the tables must outlive the async uploads
-  if (n > 1) CCUBA_HIP(hipStreamSynchronize(s));
+  return n > 1 ? drain(s) : CCUBA_OK;
+}
+
+int VegasEngine::drain(hipStream_t s) {
+  CCUBA_HIP(hipStreamSynchronize(s));
+  busy_ = nullptr;
   return CCUBA_OK;
 }
 
 int VegasEngine::dosample_only(hipStream_t s, hipEvent_t between, double *sums, double *hist) {
+  busy_ = s;
   const int rc = launch_tile_groups(ctx_, args_, tgroups_, s, user_fn_);
   if (rc) return rc;
   if (between) CCUBA_HIP(hipEventRecord(between, s));
@@ -632,6 +642,7 @@ int VegasEngine::launch_run(hipStream_t s) {
       hipGraphExec_t exec = nullptr;
       const int rc = graph_for(k, s, &exec);
       if (rc) return rc;
+      busy_ = s;
       CCUBA_HIP(hipGraphLaunch(exec, s));
     } else {
       for (int q = 0; q < k; ++q) {
@@ -654,11 +665,12 @@ int VegasEngine::launch_run(hipStream_t s) {
 
 int VegasEngine::finish_run(hipStream_t s) {
   if (max_iters_ == 0) return CCUBA_OK;
-  CCUBA_HIP(hipStreamSynchronize(s));
+  int rc = drain(s);
+  if (rc) return rc;
   std::vector<VState> st;
   if (ctx_->profile) {
     // every point a timed DoSample launch sampled is in some job's neval
-    int rc = read_states(st, s);
+    rc = read_states(st, s);
     if (rc) return rc;
     std::lock_guard<std::mutex> g(ctx_->stats_lock);
     for (const auto &x : st) ctx_->stats.evals += x.neval;
@@ -676,7 +688,7 @@ int VegasEngine::run_each(hipStream_t s, const std::function<int(const VState &)
     if ((rc = read_states(st, s))) return rc;
     if ((rc = after(st[0]))) return rc;
   }
-  CCUBA_HIP(hipStreamSynchronize(s));
+  if ((rc = drain(s))) return rc;
   return flush_timing();
 }
 
@@ -691,16 +703,14 @@ int VegasEngine::load_checkpoint(const VState &st, const double *grid, const dou
     CCUBA_HIP(hipMemcpyAsync(J.iter_var, var, st.T * sizeof(double), hipMemcpyHostToDevice, s));
   }
   CCUBA_HIP(hipMemcpyAsync(state_.p, &st, sizeof(VState), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipStreamSynchronize(s));  // the host copies are the caller's
-  return CCUBA_OK;
+  return drain(s);  // the host copies are the caller's
 }
 
 int VegasEngine::read_states(std::vector<VState> &out, hipStream_t s) {
   out.resize(njobs());
   CCUBA_HIP(hipMemcpyAsync(out.data(), state_.p, njobs() * sizeof(VState),
                            hipMemcpyDeviceToHost, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return drain(s);
 }
 
 int VegasEngine::read_results(VState &st, double *I, double *var, int max_iter, double *grid,
@@ -715,13 +725,13 @@ int VegasEngine::read_results(VState &st, double *I, double *var, int max_iter, 
                     ccuba_ctx::kPinnedBytes,
                 "every run's results fit the pinned block");
   double *host = nullptr, *dev = nullptr;
-  const int rc = pinned_block(ctx_, &host, &dev);
+  int rc = pinned_block(ctx_, &host, &dev);
   if (rc) return rc;
   // (the launch comes after every launch that writes the block's first word)
   CCUBA_HIP(launch_publish(jobs_.p, dev, (int)n, I ? dev + kState : nullptr,
                            var ? dev + kState + n : nullptr,
                            grid ? dev + kState + 2 * n : nullptr, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
+  if ((rc = drain(s))) return rc;
   std::memcpy(&st, host, sizeof(VState));
   const size_t done = (size_t)std::min<long long>(n, st.T);
   if (I && done) std::memcpy(I, host + kState, done * sizeof(double));
@@ -740,8 +750,7 @@ int VegasEngine::read_history(int job, int n, double *I, double *var, hipStream_
   if (var)
     CCUBA_HIP(hipMemcpyAsync(var, hjobs_[job].iter_var, n * sizeof(double),
                              hipMemcpyDeviceToHost, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return drain(s);
 }
 
 int VegasEngine::read_grid(int job, double *grid, hipStream_t s) {
@@ -749,8 +758,7 @@ int VegasEngine::read_grid(int job, double *grid, hipStream_t s) {
   const VJob &J = hjobs_[job];
   const long long row = (long long)J.ndim * (J.nbins + 1);
   CCUBA_HIP(hipMemcpyAsync(grid, J.grid, row * sizeof(double), hipMemcpyDeviceToHost, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return drain(s);
 }
 
 int VegasEngine::read_step(int job, int t, double *grid, double *I, double *var,
@@ -761,8 +769,7 @@ int VegasEngine::read_step(int job, int t, double *grid, double *I, double *var,
   CCUBA_HIP(hipMemcpyAsync(grid, J.grid, row * sizeof(double), hipMemcpyDeviceToHost, s));
   CCUBA_HIP(hipMemcpyAsync(I, J.iter_I + t, sizeof(double), hipMemcpyDeviceToHost, s));
   CCUBA_HIP(hipMemcpyAsync(var, J.iter_var + t, sizeof(double), hipMemcpyDeviceToHost, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return drain(s);
 }
 
 int VegasEngine::set_iteration(int job, int t, hipStream_t s) {
@@ -771,8 +778,7 @@ int VegasEngine::set_iteration(int job, int t, hipStream_t s) {
   st.T = t;
   // the state is a pinned-free host value; copy synchronously to keep it alive
   CCUBA_HIP(hipMemcpyAsync(state_.p + job, &st, sizeof(VState), hipMemcpyHostToDevice, s));
-  CCUBA_HIP(hipStreamSynchronize(s));
-  return CCUBA_OK;
+  return drain(s);
 }
 
 int VegasEngine::load_grid(int job, const double *src, hipMemcpyKind kind, hipStream_t s) {

@@ -93,6 +93,8 @@ class VegasEngine {
   // (one integral, set_alone) one at a time, one ahead of the last whose
   // outcome the host has polled.
   int launch_run(hipStream_t s);
+  // Wait for everything queued on the engine's stream.
+  int drain(hipStream_t s);
   // Wait for what launch_run queued; the profile-mode timings.
   int finish_run(hipStream_t s);
   // No job can stop before its budget (no epsrel or epsabs).
@@ -164,6 +166,7 @@ class VegasEngine {
   hipEvent_t ref_ = nullptr;
   std::vector<std::pair<double, double>> ds_iv_;
   bool capturing_ = false, alone_ = false;
+  hipStream_t busy_ = nullptr;  // the stream that may still hold the engine's work
   int iter_launched_ = 0;
   ccuba_ctx *ctx_;
   std::vector<VegasSpec> specs_;

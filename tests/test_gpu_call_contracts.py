@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,48 @@ def test_refine_keeps_the_edges_of_rows_without_a_sum(cc, ctx, nbins):
         assert np.array_equal(got[j], grid[j]), j
     for j in (0, 8):
         np.testing.assert_allclose(got[j], O.refine_dim(H[j], grid[j]), rtol=0, atol=1e-12)
+
+
+# ---- batches whose second half does not fit the budget at first ---------------
+
+def _jobs(cc, dims, npts, nbins, iters=2):
+    specs = []
+    for q, (d, n) in enumerate(zip(dims, npts)):
+        a, u = W.genz_params(q % 5, d, 70 + q)
+        specs.append(dict(method=0, ndim=d, family=q % 5, a=a, u=u, seed=q + 1, nstart=n,
+                          maxeval=iters * n, nbins=nbins, flags=cc.FP64))
+    return specs
+
+
+@pytest.mark.parametrize("budget_mib", [12, 14, 16])
+def test_batch_retried_after_one_half_is_queued(cc, ctx, budget_mib):
+    # the first half is one integral (8 MiB of tile rows), whose setup launch is
+    # queued when the second half's 11 MiB of rows are refused; the retry gives
+    # that integral's buffers to other engines (1.4 MiB of rows for the second half)
+    specs = _jobs(cc, [16] * 12, [700000] + [1 << 16] * 11, 256)
+    want = cc.vegas_batch(ctx, specs)
+    for _ in range(3):
+        c = cc.Context(hbm_budget=budget_mib << 20)
+        got = cc.vegas_batch(c, specs)
+        c.close()
+        for r, w in zip(got, want):
+            assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
+            for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+                assert abs(r[k] - w[k]) <= tol * abs(w[k]), k
+
+
+def test_state_file_of_more_iterations_is_refused(cc, ctx, tmp_path):
+    # a call refused once its engine is set up leaves the context as it was
+    a, u = W.genz_params(W.GAUSSIAN, 4, 1)
+    path = str(tmp_path / "vegas.state")
+    kw = dict(ctx=ctx, nbins=64, nstart=2000, seed=3)
+    cc.vegas(W.GAUSSIAN, a, u, statefile=path, maxeval=12000, **kw)
+    want = cc.vegas(W.GAUSSIAN, a, u, maxeval=6000, **kw)
+    for _ in range(3):
+        with pytest.raises(cc.CcubaError):
+            cc.vegas(W.GAUSSIAN, a, u, statefile=path, maxeval=6000, **kw)
+        specs = _jobs(cc, [4, 4], [2000, 2000], 64)
+        again = cc.vegas_batch(ctx, specs)
+        assert [r["status"] for r in again] == [0, 0]
+        got = cc.vegas(W.GAUSSIAN, a, u, maxeval=6000, **kw)
+        assert abs(got["integral"] - want["integral"]) <= 1e-12 * abs(want["integral"])
