@@ -162,10 +162,23 @@ void plan_tile_groups(std::vector<VJob> &jobs, std::vector<int> &tiles,
   // tiles would leave compute units idle.
   // 256 integrals of 10^4 to 10^6 points, d = 2 to 12, FP32: 4.21 ms, 4.63 with a
   // test of d per coordinate there and the d = 4 nb jobs in launches of their own.
+  // (Not where the larger d would take the fixed-point histogram from the others,
+  // whose results it makes independent of the order of the adds.)
   bool seen[32] = {false};
-  for (const VJob &J : jobs) seen[class_of(J)] = true;
+  long long most[32] = {0};  // d N
+  for (const VJob &J : jobs) {
+    const int c = class_of(J);
+    seen[c] = true;
+    most[c] = std::max(most[c], (long long)J.ndim * J.nbins);
+  }
   int to[32];
-  for (int c = 0; c < 32; ++c) to[c] = seen[c & ~1] ? c & ~1 : c;
+  for (int c = 0; c < 32; ++c) {
+    const int p = c >> 4, o = c & ~1;
+    to[c] = seen[o] && fixed_hist(p, hist64[p], most[o]) ==
+                           fixed_hist(p, hist64[p], std::max(most[o], most[c]))
+                ? o
+                : c;
+  }
   for (int cls = 0; cls < 32; ++cls) {
     const int p = cls >> 4, nb = ((cls >> 2) & 3) + 1, pw = (cls >> 1) & 1, full = cls & 1;
     TileGroup g{p, nb, pw, full, (int)tiles.size(), 0, 0, 0, 0};

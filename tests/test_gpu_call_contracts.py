@@ -89,3 +89,28 @@ def test_state_file_of_more_iterations_is_refused(cc, ctx, tmp_path):
         assert [r["status"] for r in again] == [0, 0]
         got = cc.vegas(W.GAUSSIAN, a, u, maxeval=6000, **kw)
         assert abs(got["integral"] - want["integral"]) <= 1e-12 * abs(want["integral"])
+
+
+# ---- an integral's bits do not depend on the batch's other integrals ----------
+
+def _run_fixed_point(cc, specs):
+    # tiles of 256 points whatever the batch, one engine, and the histogram whose
+    # sums do not depend on the order of their adds
+    c = cc.Context()
+    for key, value in (("min_tile", 256), ("hist64", 0), ("batch_streams", 1)):
+        c.config(key, value)
+    res = cc.vegas_batch(c, specs)
+    c.close()
+    return res
+
+
+@pytest.mark.parametrize("nbins", [255, 256])
+def test_fixed_point_histogram_beside_a_larger_integral(cc, nbins):
+    # d = 16 with so many bins leaves no room for the fixed-point histogram; the
+    # others, of the same number of Philox blocks, keep theirs
+    dims, npts = [15, 14, 13, 16], [16384, 9999, 12000, 16000]
+    few = _run_fixed_point(cc, _jobs(cc, dims[:3], npts[:3], nbins, iters=6))
+    many = _run_fixed_point(cc, _jobs(cc, dims, npts, nbins, iters=6))
+    for a, b in zip(few, many):
+        assert a["status"] == b["status"] == 0
+        assert a["integral"] == b["integral"] and a["error"] == b["error"]
