@@ -222,9 +222,9 @@ __device__ __forceinline__ void finish_state(VState &st, bool bad, bool conv, bo
 // is to refine.
 //
 // With DIRECT there was no fold: every integral has at most kDirectTiles tiles
-// (two groups), whose rows this kernel reads itself and adds in the order the
-// fold and the group sums take, so that an iteration is two launches and not
-// three.  Above that the rows a thread adds in turn cost more than the fold's
+// (two groups), whose rows and sums this kernel reads itself and adds in the order
+// the fold and the group sums take (an integral's results are the same to the last
+// bit either way), so that an iteration is two launches and not three.  Above that the rows a thread adds in turn cost more than the fold's
 // launch.  40 tiles, d = 4, 50 bins: 7.0 us, against 5.3 + 6.3 for the fold and
 // the refine launch.
 constexpr int kRefineThreads = 256;  // the refine kernel's block (launch_refine)
@@ -254,12 +254,14 @@ __global__ void __launch_bounds__(kRefineThreads) vegas_refine_kernel(VegasArgs 
   double *grow = JOB_FIELD(jw, grid) + (long long)dim * row;
   const double *gsums = DIRECT ? JOB_FIELD(jw, tsums) : JOB_FIELD(jw, gsums);
   // One round trip to memory for all of: the state (a word per lane of the
-  // first wavefront), the first 32 rows' sums (a value per lane), this
+  // first wavefront), the first rows' sums (a value per lane of the last), this
   // dimension's edges and its bins' rows.  (The edges are staged in
   // LDS before any of them is rewritten.)
   const uint32_t stw = wv == 0 ? load_words<kStateWords>(JOB_FIELD(jw, snap), lane) : 0u;
-  const double gsv = (tid < 2 * min(ng, 32)) ? gload(gsums)[tid] : 0.0;
-  const double gsv2 = DIRECT && tid < 2 * (ng - 32) ? gload(gsums)[64 + tid] : 0.0;
+  // (the sums are the last wavefront's: it has a bin of its own from N = 193 on only)
+  const bool sums = wv == kRefineThreads / 64 - 1;
+  const double gsv = sums && lane < 2 * min(ng, 32) ? gload(gsums)[lane] : 0.0;
+  const double gsv2 = DIRECT && sums && lane < 2 * (ng - 32) ? gload(gsums)[64 + lane] : 0.0;
   const double e0 = tid < row ? gload(grow)[tid] : 0.0;
   const double e1 = (tid == 0 && row > bs) ? gload(grow)[bs] : 0.0;
   // the last fold level: the group rows in group order (the order of the
@@ -294,16 +296,21 @@ __global__ void __launch_bounds__(kRefineThreads) vegas_refine_kernel(VegasArgs 
     }
     H[tid] = h;
   }
-  if (wv == 0) {
-    if (lane < kStateWords) s_stw[lane] = stw;
+  if (wv == 0 && lane < kStateWords) s_stw[lane] = stw;
+  if (sums) {
     double h1 = 0.0, h2 = 0.0;
-    if (DIRECT) {
-      // lane 2q + k holds sum k of tiles q and 32 + q: even and odd lanes apart
-      double t = gsv + gsv2;
+    if constexpr (DIRECT) {
+      // lane 2q + k holds sum k of tiles q and 32 + q; lane 2g + k adds those of
+      // group g in tile order (what is past the last tile is 0)
+      __shared__ double ts[2 * kDirectTiles];
+      ts[lane] = gsv;
+      ts[64 + lane] = gsv2;
+      wave_sync_lds();
+      double t = 0.0;
 #pragma unroll
-      for (int o = 32; o > 1; o >>= 1) t += __shfl_xor(t, o, 64);
-      h1 = lane_value(t, 0);
-      h2 = lane_value(t, 1);
+      for (int q = 0; q < kGroupTiles; ++q) t += ts[64 * ((lane >> 1) & 1) + 2 * q + (lane & 1)];
+      h1 = lane_value(t, 0) + lane_value(t, 2);
+      h2 = lane_value(t, 1) + lane_value(t, 3);
     } else {
       // the group sums in group order: the first 32 read across the lanes
       for (int q = 0; q < min(ng, 32); ++q) {

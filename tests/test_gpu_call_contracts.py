@@ -93,9 +93,14 @@ def test_state_file_of_more_iterations_is_refused(cc, ctx, tmp_path):
 
 # ---- an integral's bits do not depend on the batch's other integrals ----------
 
-def _run_fixed_point(cc, specs):
+def _run_fixed_point(cc, dims, npts, nbins):
     # tiles of 256 points whatever the batch, one engine, and the histogram whose
-    # sums do not depend on the order of their adds
+    # sums do not depend on the order of their adds: the values are all within
+    # the window that its integers hold (v^2 down to 2^-37 of the cap), so that
+    # none goes to the FP64 histogram beside it
+    specs = _jobs(cc, dims, npts, nbins, iters=6)
+    for s in specs:
+        s["family"], s["a"] = W.C0, np.full(s["ndim"], 0.2)
     c = cc.Context()
     for key, value in (("min_tile", 256), ("hist64", 0), ("batch_streams", 1)):
         c.config(key, value)
@@ -109,8 +114,19 @@ def test_fixed_point_histogram_beside_a_larger_integral(cc, nbins):
     # d = 16 with so many bins leaves no room for the fixed-point histogram; the
     # others, of the same number of Philox blocks, keep theirs
     dims, npts = [15, 14, 13, 16], [16384, 9999, 12000, 16000]
-    few = _run_fixed_point(cc, _jobs(cc, dims[:3], npts[:3], nbins, iters=6))
-    many = _run_fixed_point(cc, _jobs(cc, dims, npts, nbins, iters=6))
+    few = _run_fixed_point(cc, dims[:3], npts[:3], nbins)
+    many = _run_fixed_point(cc, dims, npts, nbins)
+    for a, b in zip(few, many):
+        assert a["status"] == b["status"] == 0
+        assert a["integral"] == b["integral"] and a["error"] == b["error"]
+
+
+@pytest.mark.parametrize("npts", [256, 8192, 8193, 16384])
+def test_tile_sums_with_and_without_the_fold(cc, npts):
+    # 1, 32, 33 and 64 tiles: summed by the refine launch alone, or through the fold
+    # where another integral of the batch has more
+    few = _run_fixed_point(cc, [3, 4, 2], [npts] * 3, 64)
+    many = _run_fixed_point(cc, [3, 4, 2, 5], [npts] * 3 + [40000], 64)
     for a, b in zip(few, many):
         assert a["status"] == b["status"] == 0
         assert a["integral"] == b["integral"] and a["error"] == b["error"]
