@@ -296,6 +296,10 @@ __global__ void __launch_bounds__(1024) topk_kernel(const double *key, int R, in
 // LDS; a workgroup's dimension groups read the same points at about the same
 // time.  The half of a point enters as a bit mask: factors 0.0 and 1.0 of
 // fused multiply-adds, and quiet NaNs, which minimum and maximum pass over.
+// Every factor's partner is finite, or a point would reach the other half as 0.0
+// times infinity: a square that overflows enters as the largest finite number, and
+// a deviation below the smallest normal, whose reciprocal overflows, is scaled by
+// the smallest normal instead (F_h is the same for every scale).
 // 64 regions of 2^17 points, d = 8, p = 25: 30 and 45 us a launch, against 59 and
 // 66 (and 7 for a reduction launch between them) with the chunks staged in LDS
 // and a thread per (dimension, point).
@@ -388,7 +392,7 @@ __global__ void __launch_bounds__(kFlThreads *kFlGroups) suave_fluct1_kernel(Sua
 #pragma unroll
     for (int p = 0; p < U; ++p) {
       if (p >= m) break;
-      const double xx = x[p] * x[p];
+      const double xx = min_num(x[p] * x[p], 0x1.fffffffffffffp1023);
       const unsigned long long xb = (unsigned long long)__double_as_longlong(x[p]);
       const uint32_t xh = (uint32_t)(xb >> 32);
 #pragma unroll
@@ -471,7 +475,8 @@ __global__ void __launch_bounds__(kFlThreads *kFlGroups) suave_fluct2_kernel(Sua
     for (int k = 0; k < 2; ++k) {
       const double S1 = x[1 + 2 * k], mn = x[5 + 2 * k], mx = x[6 + 2 * k];
       const double m = cnt[k] > 0.0 ? S1 / cnt[k] : 0.0;
-      const double M = cnt[k] > 0.0 ? fmax(mx - m, m - mn) : 0.0;
+      double M = cnt[k] > 0.0 ? fmax(mx - m, m - mn) : 0.0;
+      if (M > 0.0) M = fmax(M, 0x1p-1022);
       sm[j][k] = m;
       sinv[j][k] = M > 0.0 ? 1.0 / M : 0.0;
       if (ch == 0) {

@@ -130,3 +130,21 @@ def test_tile_sums_with_and_without_the_fold(cc, npts):
     for a, b in zip(few, many):
         assert a["status"] == b["status"] == 0
         assert a["integral"] == b["integral"] and a["error"] == b["error"]
+
+
+# ---- Suave: regions whose values leave the normal range ------------------------
+
+@pytest.mark.parametrize("a,nsplit,flatness", [((36.0, 3.0), 64, 25.0), ((3.0, 36.0), 64, 25.0),
+                                               ((35.7, 20.0), 64, 25.0),
+                                               ((36.0, 1.0, 36.0), 8, 2.5)])
+def test_suave_halves_of_subnormal_values(cc, ctx, a, nsplit, flatness):
+    # a Gaussian's tail from e^-324 to e^-729: halves whose deviations from their
+    # mean are subnormal, or all zero, beside others in the normal range
+    d, u = len(a), np.zeros(len(a))
+    kw = dict(seed=1, nnew=1000, nbins=32, nsplit=nsplit, flatness=flatness, maxeval=15000)
+    g = cc.suave(W.GAUSSIAN, np.array(a), u, ctx=ctx, trace=True, **kw)
+    o = O.suave(O.genz(W.GAUSSIAN, np.array(a), u), d, **kw)
+    assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert np.array_equal(g["cut"], o["cut"]) and np.array_equal(g["lo"], o["lo"])
+    assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
+    assert abs(g["error"] - o["error"]) <= 1e-10 * abs(o["error"])
