@@ -93,9 +93,16 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
   CRegions R{};
   DevBuf<double> cb, hb, vals;
   DevBuf<int> ax;
+  auto release = [&] {
+    cb.release();
+    hb.release();
+    vals.release();
+    ax.release();
+  };
   for (;; cap = need) {
     int rc = alloc_store(R, cb, hb, vals, ax, cap);
-    if (rc == CCUBA_OK) {
+    const bool copied = rc == CCUBA_OK;
+    if (copied) {
       const CRegions &O = R_;
       const long long m = next_id_;
       if (m > 0) {
@@ -112,26 +119,25 @@ int CuhreRun::ensure(long long need, hipStream_t s) {
       }
       CCUBA_HIP(hipStreamSynchronize(s));
       rc = alloc_scratch(cap);
-      if (rc == CCUBA_OK)
-        CCUBA_HIP(hipMemsetAsync(parent_.p, 0, parent_.n * sizeof(long long), s));
     }
-    if (rc == CCUBA_OK) break;
-    if (rc != CCUBA_ENOMEM || cap <= need) return rc;
-    cb.release();  // the larger store does not fit after all
-    hb.release();
-    vals.release();
-    ax.release();
+    if (rc == CCUBA_ENOMEM && cap > need) {
+      release();  // the larger store does not fit after all
+      continue;
+    }
+    if (rc && !copied) return rc;
+    c_.swap(cb);
+    h_.swap(hb);
+    vals_.swap(vals);
+    axis_.swap(ax);
+    R_ = R;
+    cap_ = cap;
+    release();  // (the old store)
+    // the scratch may fit only now
+    if (rc == CCUBA_ENOMEM) rc = alloc_scratch(cap);
+    if (rc) return rc;
+    break;
   }
-  c_.swap(cb);
-  h_.swap(hb);
-  vals_.swap(vals);
-  axis_.swap(ax);
-  R_ = R;
-  cb.release();
-  hb.release();
-  vals.release();
-  ax.release();
-  cap_ = cap;
+  CCUBA_HIP(hipMemsetAsync(parent_.p, 0, parent_.n * sizeof(long long), s));
   return CCUBA_OK;
 }
 

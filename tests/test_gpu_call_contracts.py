@@ -148,3 +148,19 @@ def test_suave_halves_of_subnormal_values(cc, ctx, a, nsplit, flatness):
     assert np.array_equal(g["cut"], o["cut"]) and np.array_equal(g["lo"], o["lo"])
     assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
     assert abs(g["error"] - o["error"]) <= 1e-10 * abs(o["error"])
+
+
+# ---- a Cuhre store that grows under a tight budget ------------------------------
+
+def test_cuhre_store_grows_beside_no_more_than_it_needs(cc, ctx):
+    # 36600 KiB hold the old store and the new one, and then the new one's scratch,
+    # but not all three at once
+    a, u = W.genz_params(W.GAUSSIAN, 3, 3)
+    kw = dict(epsrel=1e-30, maxeval=33 * 200000, max_regions_per_batch=20000)
+    c = cc.Context(hbm_budget=36600 << 10)
+    g = cc.cuhre(W.CORNER_PEAK, a, u, ctx=c, **kw)
+    c.close()
+    w = cc.cuhre(W.CORNER_PEAK, a, u, ctx=ctx, **kw)
+    assert g["nregions"] == w["nregions"] and g["neval"] == w["neval"] and g["fail"] == w["fail"]
+    assert abs(g["integral"] - w["integral"]) <= 1e-12 * abs(w["integral"])
+    assert abs(g["error"] - w["error"]) <= 1e-10 * abs(w["error"])
