@@ -252,9 +252,8 @@ enum { CCUBA_POINTS_HOST = 0, CCUBA_POINTS_DEVICE = 1 };
  * CCUBA_POINTS_HOST x and f are host arrays the library owns; with
  * CCUBA_POINTS_DEVICE they are device arrays on the context's GPU, and the
  * integrand's writes to f must be complete when it returns (for work it
- * launches itself, it synchronises first).  x and f are valid during the call
- * and may be other arrays in the next one: with CCUBA_POINTS_DEVICE the next
- * batch is made while the integrand runs.  The integrand runs while the
+ * launches itself, it synchronises first).  x and f are the same arrays for
+ * every batch of a call.  The integrand runs while the
  * context is held and must not call back into the same context.
  * Components: every one has its own sums, estimate, combination, chi^2 and
  * prob over the same points; the grid adapts to component 0's histogram;

@@ -12,12 +12,13 @@
 // statistics, the stop rule and the grid, which also writes the states to the
 // pinned block.
 //
-// While the integrand has a batch in device memory, the next one's points are
-// made beside it, in a second set of buffers, and the last one's values are
-// accumulated; between two integrand calls the device then only waits for the
-// host.  3 iterations of 4 batches of 10^6 points at d = 8, a Gaussian in five
-// library kernels: 1.93 ms, 1.39 ms of it the integrand's own; 2.19 ms when
-// every batch waited for the one before.
+// The integrand gets the same arrays for every batch, so that a program may keep
+// their addresses (in a graph it replays, say); a batch's points are therefore
+// made when the one before it has been evaluated, except that an iteration's first
+// are queued behind the last one's statistics.  3 iterations of 4 batches of 10^6
+// points at d = 8, a Gaussian in five library kernels: 2.02 ms, 1.39 ms of it the
+// integrand's own; 1.92 ms with the next batch made meanwhile in a second set of
+// arrays, which such a program would not see.
 #include "vegas_batched.h"
 
 #include <algorithm>
@@ -32,10 +33,10 @@ namespace {
 
 constexpr int kBatchedTile = 4096;  // points per tile row
 
-// Batches up to this size are made ahead (the second set of buffers, and an
-// iteration's first points before it is known that the last one was not
-// enough).  Larger ones run long enough to hide the waits: 256 MiB are about
-// 3.5 x 10^6 points at d = 8, whose kernels take 0.4 ms, the waits 0.05 ms.
+// An iteration's first points are made before it is known that the last one was
+// not enough, for batches up to this size.  Larger ones run long enough to hide
+// the wait: 256 MiB are about 3.5 x 10^6 points at d = 8, whose kernels take
+// 0.1 ms, the wait 0.01 ms.
 constexpr long long kAheadBytes = 256ll << 20;
 
 // Nothing of the call is left on the stream when its buffers go back.
@@ -78,8 +79,7 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
   const long long mmax = std::min<long long>(sp.nvec, nmax);
   const long long tiles_max = ceil_div(nmax, sp.nvec) * ceil_div(mmax, kBatchedTile);
   const long long groups_max = ngroups_of((int)tiles_max);
-  // two sets of batch buffers where the points are made ahead
-  DevBuf<double> grid, x[2], f[2], w[2], rows, ghist, gsums, hist;
+  DevBuf<double> grid, x, f, w, rows, ghist, gsums, hist;
   // all zero: the components' states before the first iteration, and what the
   // fold's view of the tile rows reads, a state that is never done and tile
   // sums of zero
@@ -90,8 +90,8 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
   const long long stw = sizeof(VState) / sizeof(double);
   const long long nzero = (nc + 1) * stw + 2 * tiles_max;
   int rc;
-  if ((rc = grid.alloc(ctx, (size_t)d * row)) || (rc = x[0].alloc(ctx, mmax * d)) ||
-      (rc = f[0].alloc(ctx, mmax * nc)) || (rc = w[0].alloc(ctx, mmax)) ||
+  if ((rc = grid.alloc(ctx, (size_t)d * row)) || (rc = x.alloc(ctx, mmax * d)) ||
+      (rc = f.alloc(ctx, mmax * nc)) || (rc = w.alloc(ctx, mmax)) ||
       (rc = rows.alloc(ctx, tiles_max * R)) || (rc = ghist.alloc(ctx, groups_max * R)) ||
       (rc = gsums.alloc(ctx, 2 * groups_max)) || (rc = hist.alloc(ctx, 2ll * nc * cap)) ||
       (rc = zeros.alloc(ctx, nzero)) || (rc = view.alloc(ctx, 1)) ||
@@ -105,21 +105,7 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
     CCUBA_HIP(hipHostMalloc(&xh.p, mmax * d * sizeof(double), hipHostMallocDefault));
     CCUBA_HIP(hipHostMalloc(&fh.p, mmax * nc * sizeof(double), hipHostMallocDefault));
   }
-  const long long set_bytes = mmax * (d + nc + 1) * (long long)sizeof(double);
-  const bool ahead = set_bytes <= kAheadBytes;
-  // (the second set is left out where it would take the context past half of
-  // its budget, or where the device has no room)
-  int sets = 1;
-  if (ahead && !host && nmax > mmax && ctx->used.load() + set_bytes <= ctx->budget / 2) {
-    if (x[1].alloc(ctx, mmax * d) || f[1].alloc(ctx, mmax * nc) || w[1].alloc(ctx, mmax)) {
-      x[1].release();
-      f[1].release();
-      w[1].release();
-      (void)hipGetLastError();
-    } else {
-      sets = 2;
-    }
-  }
+  const bool ahead = mmax * (d + nc + 1) * (long long)sizeof(double) <= kAheadBytes;
   double *pin_host = nullptr, *pin_dev = nullptr;
   if ((rc = pinned_block(ctx, &pin_host, &pin_dev))) return rc;
   static_assert(kMaxComp * sizeof(VState) <= ccuba_ctx::kPinnedBytes, "the states fit");
@@ -136,39 +122,37 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
   pa.key1 = (uint32_t)(sp.seed >> 32);
   pa.sid = sp.sid;
   pa.grid = grid.p;
+  pa.x = x.p;
+  pa.w = w.p;
   // the points of the batch of iteration t (of n points) that starts at i0
-  auto make_points = [&](int t, long long n, long long i0, int set) {
+  auto make_points = [&](int t, long long n, long long i0) {
     pa.iteration = t;
     pa.i0 = i0;
     pa.npts = std::min<long long>(sp.nvec, n - i0);
-    pa.x = x[set].p;
-    pa.w = w[set].p;
     return launch_points(pa, s);
   };
   VJob jv{};
   long long tend = 0;
   long long handed = 0;  // points given to the integrand
   const int core = -1;   // an accelerator (Sect. 3.2.4)
-  long long batch = 0;   // batches so far: the next one's buffers are set batch % sets
-  bool made = true;      // its points are launched
-  bool ready = false;    // and there
-  CCUBA_HIP(make_points(0, sp.nstart, 0, 0));
+  bool made = true;   // the next batch's points are launched
+  bool ready = false; // and there
+  CCUBA_HIP(make_points(0, sp.nstart, 0));
   for (int t = 0; t < iters; ++t) {
     const long long n = sp.nstart + (long long)t * sp.nincrease;
     int tiles = 0;
-    for (long long i0 = 0; i0 < n; i0 += sp.nvec, ++batch) {
-      const int set = (int)(batch % sets);
+    for (long long i0 = 0; i0 < n; i0 += sp.nvec) {
       const long long m = std::min<long long>(sp.nvec, n - i0);
-      if (!made) CCUBA_HIP(make_points(t, n, i0, set));
+      if (!made) CCUBA_HIP(make_points(t, n, i0));
       if (host)
-        CCUBA_HIP(hipMemcpyAsync(xh.p, x[0].p, m * d * sizeof(double), hipMemcpyDeviceToHost, s));
+        CCUBA_HIP(hipMemcpyAsync(xh.p, x.p, m * d * sizeof(double), hipMemcpyDeviceToHost, s));
+      // (the last batch's values, which f holds, have been read then, too)
       if (host || !ready) CCUBA_HIP(hipStreamSynchronize(s));
-      const bool next = sets == 2 && i0 + sp.nvec < n;
-      if (next) CCUBA_HIP(make_points(t, n, i0 + sp.nvec, set ^ 1));
+      made = ready = false;
       const int mi = (int)m, nd = d, ncomp = nc;
       const int urc = host ? fn(&nd, (const double *)xh.p, &ncomp, (double *)fh.p, userdata, &mi,
                                 &core)
-                           : fn(&nd, x[set].p, &ncomp, f[set].p, userdata, &mi, &core);
+                           : fn(&nd, x.p, &ncomp, f.p, userdata, &mi, &core);
       handed += m;
       if (urc == -999) {
         for (int c = 0; c < nc; ++c) integral[c] = error[c] = prob[c] = 0.0;
@@ -177,12 +161,8 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
         return CCUBA_OK;
       }
       if (host)
-        CCUBA_HIP(hipMemcpyAsync(f[0].p, fh.p, m * nc * sizeof(double), hipMemcpyHostToDevice, s));
-      // Before this batch's values are queued: the next one's points are there
-      // and the last one's values, which its f holds, have been read.
-      if (next) CCUBA_HIP(hipStreamSynchronize(s));
-      made = ready = next;
-      BatchedArgs ba{d, N, nc, sp.prec, m, kBatchedTile, tiles, w[set].p, f[set].p,
+        CCUBA_HIP(hipMemcpyAsync(f.p, fh.p, m * nc * sizeof(double), hipMemcpyHostToDevice, s));
+      BatchedArgs ba{d, N, nc, sp.prec, m, kBatchedTile, tiles, w.p, f.p,
                      pa.key0, pa.key1, pa.sid, t, i0, rows.p, states};
       CCUBA_HIP(launch_batched_accumulate(ba, s));
       tiles += (int)ceil_div(m, kBatchedTile);
@@ -232,7 +212,7 @@ int vegas_batched(ccuba_ctx *ctx, const BatchedSpec &sp, ccuba_batch_integrand f
     CCUBA_HIP(launch_batched_finish(fa, s));
     // the next iteration's first points, on the grid as refined
     made = ahead && t + 1 < iters;
-    if (made) CCUBA_HIP(make_points(t + 1, n + sp.nincrease, 0, (int)(batch % sets)));
+    if (made) CCUBA_HIP(make_points(t + 1, n + sp.nincrease, 0));
     CCUBA_HIP(hipStreamSynchronize(s));
     ready = made;
     if (out[0].done) break;

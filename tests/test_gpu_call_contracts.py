@@ -164,3 +164,27 @@ def test_cuhre_store_grows_beside_no_more_than_it_needs(cc, ctx):
     assert g["nregions"] == w["nregions"] and g["neval"] == w["neval"] and g["fail"] == w["fail"]
     assert abs(g["integral"] - w["integral"]) <= 1e-12 * abs(w["integral"])
     assert abs(g["error"] - w["error"]) <= 1e-10 * abs(w["error"])
+
+
+# ---- a device integrand's arrays --------------------------------------------------
+
+@pytest.mark.parametrize("nvec,npts", [(1000, 1000), (1000, 3500), (4096, 12288)])
+def test_device_integrand_may_keep_its_first_arrays(cc, ctx, nvec, npts):
+    # as one does that replays a graph recorded over them; a shorter last batch is
+    # their first part.  It only multiplies, so that both sides compute the same bits
+    kw = dict(ctx=ctx, nvec=nvec, nstart=npts, maxeval=4 * npts, nbins=64, seed=4)
+    kept, sizes = [], []
+
+    def fdev(x, f):
+        if not kept:
+            kept.extend((x, f))
+        m = len(x)
+        sizes.append(m)
+        xk, fk = kept
+        fk[:m, 0] = xk[:m, 0] * xk[:m, 1]
+
+    g = cc.vegas_batched(fdev, 3, 1, where="device", **kw)
+    h = cc.vegas_batched(lambda x: x[:, 0] * x[:, 1], 3, 1, **kw)
+    assert max(sizes) == sizes[0] and g["neval"] == h["neval"] == 4 * npts
+    assert abs(g["integral"] - h["integral"]) <= 1e-12 * abs(h["integral"])
+    assert abs(g["error"] - h["error"]) <= 1e-10 * abs(h["error"])
