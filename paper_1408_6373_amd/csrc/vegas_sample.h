@@ -341,7 +341,8 @@ __device__ __forceinline__ uint32_t lds_addr(V *p) {
 // of the last block.
 // Each lane carries ILP independent points per trip (q, q + blockDim, ...),
 // so that several Philox chains are in flight; what is left at the tile's end goes
-// one point at a time.  A trip's
+// one point at a time (a caller's function, of any size, is compiled once: its last
+// trip computes past the end).  A trip's
 // histogram updates are issued at its end, so that the LDS works through
 // them while the next trip's Philox rounds run; the next trip's wait for its
 // grid reads then finds them done.  (Updates deferred to after the next
@@ -368,9 +369,11 @@ __device__ __forceinline__ void sample_tile(const VJob &J, int t, long long i0, 
   // an assembly comment naming the family, so that the per-point loop that
   // follows can be found in the assembly listing (it emits no instruction)
   asm volatile("; ccuba sample_tile family %0" ::"n"(FAM));
-  // one trip: P points per lane from q0 on
-  auto trip = [&](int q0, auto points) {
+  // one trip: P points per lane from q0 on (with MASK, those past the tile's end
+  // are computed too, with LDS reads in range, and contribute nothing)
+  auto trip = [&](int q0, auto points, auto mask) {
     constexpr int P = decltype(points)::value;
+    constexpr bool MASK = decltype(mask)::value;
     T fr[P][ND], lo[P][ND], sp[P][ND];
     int idx[P][ND];
     // words, bins and the grid cells they select
@@ -451,6 +454,7 @@ __device__ __forceinline__ void sample_tile(const VJob &J, int t, long long i0, 
         return CL ? lds_at<double>((uint32_t)idx[e][j] + (lds_addr(sHx) - lds0))
                   : sHx + idx[e][j];
       };
+      if (MASK && q0 + e * bs >= cnt) continue;
       const double dv = (double)v - shift;
       S1 += dv;
       S2 = fma(dv, dv, S2);
@@ -500,9 +504,14 @@ __device__ __forceinline__ void sample_tile(const VJob &J, int t, long long i0, 
     }
   };
   int q0 = threadIdx.x;
+#ifdef CCUBA_RTC
+  for (; q0 < cnt; q0 += ILP * bs) trip(q0, Int<ILP>{}, Int<(ILP > 1)>{});
+#else
   if constexpr (ILP > 1)
-    for (int end = ILP * bs; end <= cnt; end += ILP * bs, q0 += ILP * bs) trip(q0, Int<ILP>{});
-  for (; q0 < cnt; q0 += bs) trip(q0, Int<1>{});
+    for (int end = ILP * bs; end <= cnt; end += ILP * bs, q0 += ILP * bs)
+      trip(q0, Int<ILP>{}, Int<0>{});
+  for (; q0 < cnt; q0 += bs) trip(q0, Int<1>{}, Int<0>{});
+#endif
 }
 
 // One kernel per (precision, histogram type, ILP, NB, power-of-two bins,
@@ -514,9 +523,17 @@ __device__ __forceinline__ void sample_tile(const VJob &J, int t, long long i0, 
 // (three above 12 dimensions), so that blocks of a batch's two halves run beside
 // each other: 256 integrals of 10^4 to 10^6 points, d = 2 to 12, in 4.06 ms instead
 // of 4.22 with 139 registers at d = 9 to 12.  (A few values used outside the loops
-// are spilled.)
+// are spilled.)  A caller's function takes the registers that it needs: what it
+// holds of a point is not known here.  Three arrays of 16 words, 10 x 8 x 10^6
+// points: 3.1 ms at d = 12, 7.0 with 68 registers spilled under the bound.
+#ifdef CCUBA_RTC
+constexpr int sample_waves(bool, int) { return 1; }
+#else
+constexpr int sample_waves(bool f32_pow2, int nb) { return !f32_pow2 ? 1 : nb == 4 ? 3 : 4; }
+#endif
+
 template <typename T, typename HT, int ILP, int NB, bool POW2, bool FULL>
-__global__ void __launch_bounds__(256, sizeof(T) == 8 || !POW2 ? 1 : NB == 4 ? 3 : 4)
+__global__ void __launch_bounds__(256, sample_waves(sizeof(T) == 4 && POW2, NB))
     vegas_dosample_kernel(VegasArgs A) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[2][4];
@@ -563,7 +580,10 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 || !POW2 ? 1 : NB == 4 ? 3
     if (st.done) continue;  // the same for the whole block: nothing read the cells yet
     // (only now: their loads have been in flight beside the cells').  FP32 at up
     // to 8 dimensions keeps them in vector registers: it has those to spare,
-    // and an instruction reads one scalar operand.
+    // and an instruction reads one scalar operand.  So does a caller's function,
+    // whose loops may index them: 10 x 2 x 10^7 points of a Gaussian's loop at d = 11,
+    // FP32, 2.3 ms, 2.9 with scalar ones.
+#ifndef CCUBA_RTC
     if constexpr (sizeof(T) == 8 || NB > 2) {
 #pragma unroll
       for (int j = 0; j < ND; ++j) {
@@ -571,6 +591,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 8 || !POW2 ? 1 : NB == 4 ? 3
         pp1[j] = uniform(pp1[j]);
       }
     }
+#endif
     const long long n_t = J.nstart + (long long)st.T * J.nincrease;
     // The tiles are sized for the run's largest iteration; a smaller one is
     // spread over all of them (whole trips of the block), so that its launch

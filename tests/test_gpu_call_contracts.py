@@ -188,3 +188,34 @@ def test_device_integrand_may_keep_its_first_arrays(cc, ctx, nvec, npts):
     assert max(sizes) == sizes[0] and g["neval"] == h["neval"] == 4 * npts
     assert abs(g["integral"] - h["integral"]) <= 1e-12 * abs(h["integral"])
     assert abs(g["error"] - h["error"]) <= 1e-10 * abs(h["error"])
+
+
+# ---- device sources: the last trip of a tile ---------------------------------------
+
+LOOP_SRC = r"""
+__device__ double ccuba_user(const double *x, int d, const double *a, const double *u) {
+  double s = 0.0;
+  for (int j = 0; j < d; ++j) {
+    const double t = x[j] - u[j];
+    s = fma(a[j] * a[j], t * t, s);
+  }
+  return exp(-s);
+}
+"""
+
+
+@pytest.mark.parametrize("d,nbins,npts,ilp", [
+    (3, 64, 255, 2), (3, 64, 257, 2), (8, 128, 511, 2), (11, 128, 513, 2), (11, 100, 40961, 2),
+    (16, 256, 2049, 2), (13, 64, 1025, 1)])
+def test_source_with_points_left_over(cc, d, nbins, npts, ilp):
+    # (the bars of the integrator's parity tests)
+    a, u = W.genz_params(W.GAUSSIAN, d, 21)
+    kw = dict(nbins=nbins, nstart=npts, maxeval=5 * npts, seed=9)
+    c = cc.Context()
+    c.config("ilp", ilp)
+    s = cc.vegas_source(LOOP_SRC, d, a, u, ctx=c, **kw)
+    b = cc.vegas(W.GAUSSIAN, a, u, ctx=c, **kw)
+    c.close()
+    assert s["neval"] == b["neval"] == 5 * npts and s["fail"] == b["fail"]
+    for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+        assert abs(s[k] - b[k]) <= tol * abs(b[k]), k
