@@ -488,6 +488,7 @@ int ccuba_vegas_source(ccuba_ctx **ctxp, int ndim, const char *source, const dou
   // an engine of its own: the cached one's graphs hold the built-in kernels
   VegasEngine eng(ctx);
   eng.set_user_kernel(fn);
+  eng.set_once();
   if ((rc = eng.setup({sp}, true, ctx->stream))) return rc;
   return vegas_finish(ctx, eng, neval, fail, integral, error, prob, nullptr);
 }
@@ -566,6 +567,7 @@ int ccuba_vegas_ex(ccuba_ctx **ctxp, int ndim, int ncomp, const ccuba_integrand 
     ep = ctx->vcache;
   } else {
     own.reset(new VegasEngine(ctx));
+    own->set_once();
     ep = own.get();
   }
   VegasEngine &eng = *ep;
@@ -574,6 +576,7 @@ int ccuba_vegas_ex(ccuba_ctx **ctxp, int ndim, int ncomp, const ccuba_integrand 
     // the cached buffers may be what exceeds the budget: start afresh
     drop_engine_cache(ctx);
     own.reset(new VegasEngine(ctx));
+    own->set_once();
     rc = own->setup({sp}, true, ctx->stream);
     if (rc) return rc;
     return vegas_finish(ctx, *own, neval, fail, integral, error, prob, trace);

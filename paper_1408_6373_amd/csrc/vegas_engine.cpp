@@ -644,9 +644,9 @@ int VegasEngine::launch_run(hipStream_t s) {
   // Iterations are launched in chunks between host checks of the states:
   // all of them at once when no job can stop early, else 2, 4, 8, ... (a
   // finished job's state makes the remaining launches of its chunk skip it).
-  // With graphs on, a chunk of k iterations is one graph of 3k kernels, so
+  // With graphs on, a chunk of k iterations is one graph of their kernels, so
   // that consecutive iterations are not separated by graph launches.
-  const bool graph = ctx_->use_graph != 0 && !ctx_->profile;
+  const bool graph = ctx_->use_graph != 0 && !ctx_->profile && !once_;
   int chunk = fixed ? std::min(remaining, kMaxGraphIters) : 2;
   std::vector<VState> st;
   while (remaining > 0) {

@@ -219,3 +219,19 @@ def test_source_with_points_left_over(cc, d, nbins, npts, ilp):
     assert s["neval"] == b["neval"] == 5 * npts and s["fail"] == b["fail"]
     for k, tol in (("integral", 1e-12), ("error", 1e-11)):
         assert abs(s[k] - b[k]) <= tol * abs(b[k]), k
+
+
+@pytest.mark.parametrize("epsrel", [0.0, 2e-3])
+def test_engines_that_are_not_kept_match_the_kept_one(cc, epsrel):
+    # their iterations are queued one by one, a kept engine's as graphs
+    a, u = W.genz_params(W.GAUSSIAN, 3, 21)
+    kw = dict(nbins=64, nstart=5000, maxeval=60 * 5000, epsrel=epsrel, seed=9)
+    c = cc.Context()
+    kept = cc.vegas(W.GAUSSIAN, a, u, ctx=c, **kw)
+    c.config("engine_cache", 0)
+    runs = [cc.vegas(W.GAUSSIAN, a, u, ctx=c, **kw), cc.vegas_source(LOOP_SRC, 3, a, u, ctx=c, **kw)]
+    c.close()
+    for r in runs:
+        assert r["neval"] == kept["neval"] and r["fail"] == kept["fail"]
+        for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+            assert abs(r[k] - kept[k]) <= tol * abs(kept[k]), k
