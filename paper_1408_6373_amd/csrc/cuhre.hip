@@ -66,6 +66,13 @@ __constant__ GMWeights kWeights = gm_weights();
 constexpr int kLaneRuleMaxDim = 8;          // lane-per-region rule up to this d
 constexpr long long kLaneRuleMinRegions = 512;  // and from this many regions on
 constexpr long long kOneLaneRuleMinRegions = 49152;  // one lane per region from here
+// Whether it may: a lane holds the unrolled pairs and the corners' tree, and around
+// a cosine, whose own registers come on top, they spill from d = 4 on (a lane of
+// four wavefronts holds a quarter of them).  4 x 10^5 regions, oscillatory, us:
+//   d       4    5    6    7     8
+//   one   112  213  475  755  1039
+//   four   95  156  235  411   613
+constexpr bool one_lane_rule(int family, int d) { return family != OSCILLATORY || d < 4; }
 constexpr long long kWaveRuleBlocks = 2048;       // most blocks of a wave-per-region launch
 // Up to this many regions a launch over several integrals or above 8
 // dimensions gives each a whole workgroup (its four wavefronts share the rule
@@ -1582,9 +1589,12 @@ enum RuleSplit { LANE, LANE4, WAVE };  // a lane, a lane of four wavefronts, a w
 
 template <int FAM, int D>
 static void launch_rule_lane_dd(const RuleArgs &A, unsigned grid, RuleSplit split, hipStream_t s) {
-  if (split == LANE)
-    hipLaunchKernelGGL((gm_rule_lane1_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
-  else if (split == WAVE)
+  if constexpr (one_lane_rule(FAM, D))
+    if (split == LANE) {
+      hipLaunchKernelGGL((gm_rule_lane1_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
+      return;
+    }
+  if (split == WAVE)
     hipLaunchKernelGGL((gm_rule_wave_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
   else
     hipLaunchKernelGGL((gm_rule_lane_kernel<FAM, D>), dim3(grid), dim3(256), 0, s, A);
@@ -1657,7 +1667,7 @@ hipError_t launch_root_clear(const CRegions &R, int ndim, int *done, hipStream_t
 
 // One integral of at most 8 dimensions: a lane per region from
 // kOneLaneRuleMinRegions on, where a wavefront per SIMD and more fill the
-// device, a lane of each of four wavefronts from kLaneRuleMinRegions, a
+// device (and one_lane_rule allows it), a lane of each of four wavefronts from kLaneRuleMinRegions, a
 // wavefront per region below.  Above 8 dimensions (the registers a lane holds
 // grow with d, and the 2^d corners with it) and for launches over several
 // integrals, a workgroup or a wavefront per region.
@@ -1666,9 +1676,9 @@ static bool dim_rule(const RuleArgs &A) {
 }
 
 static RuleSplit rule_split(const RuleArgs &A) {
-  return A.total >= kOneLaneRuleMinRegions ? LANE
-         : A.total >= kLaneRuleMinRegions  ? LANE4
-                                           : WAVE;
+  if (A.total < kLaneRuleMinRegions) return WAVE;
+  return A.total >= kOneLaneRuleMinRegions && one_lane_rule(A.one.family, A.one.ndim) ? LANE
+                                                                                      : LANE4;
 }
 
 long long rule_blocks(const RuleArgs &A) {

@@ -235,3 +235,26 @@ def test_engines_that_are_not_kept_match_the_kept_one(cc, epsrel):
         assert r["neval"] == kept["neval"] and r["fail"] == kept["fail"]
         for k, tol in (("integral", 1e-12), ("error", 1e-11)):
             assert abs(r[k] - kept[k]) <= tol * abs(kept[k]), k
+
+
+# ---- Cuhre's rule: every split, at the edges of the sizes that choose it ------------
+
+@pytest.mark.parametrize("d", [3, 4, 8])
+@pytest.mark.parametrize("nreg", [511, 512, 49151, 49152, 49217])
+def test_oscillatory_rule_at_the_edges_of_its_splits(cc, ctx, d, nreg):
+    # regions repeated in blocks of 61, so that the oracle evaluates 61 of them (the
+    # bars of the rule's own parity test)
+    rng = np.random.default_rng(d)
+    a, u = W.genz_params(W.OSCILLATORY, d, 5)
+    c0, h0 = rng.uniform(0.2, 0.8, (61, d)), rng.uniform(0.01, 0.2, (61, d))
+    pick = np.arange(nreg) % 61
+    g = cc.cuhre_rule(ctx, W.OSCILLATORY, a, u, c0[pick], h0[pick])
+    for q in range(61):
+        o = O.gm_rule(O.genz(W.OSCILLATORY, a, u), c0[q], h0[q])
+        same = pick == q
+        vol = np.prod(2.0 * h0[q])
+        for k, m in (("I7", 20), ("I5", 60)):
+            assert np.all(np.abs(g[k][same] - o[k]) <= 1e-12 * abs(o[k]) + 1e-15 * vol * m), k
+        D = np.sort(o["dfour"])[::-1]
+        if D[0] - D[1] > 1e-9 * D[0]:
+            assert np.all(g["axis"][same] == o["axis"])
