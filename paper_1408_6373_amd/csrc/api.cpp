@@ -765,7 +765,11 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   auto bytes_for = [&](long long nt) {
     return a256(nt * 16) + a256(nt * dN * 8) + a256((long long)ngroups_of((int)nt) * row);
   };
-  long long P = single_tile(npts, bs, ctx->ncu, t.blocks_per_cu);
+  const int nb = (ndim + 3) / 4;
+  const bool pow2 = (nbins & (nbins - 1)) == 0, fixed = fixed_hist(p, t.hist64, dN);
+  size_t hist_off = 0;
+  const size_t lds = dosample_lds(p, fixed, nb, pow2, ndim, nbins, &hist_off);
+  long long P = single_tile(npts, bs, ctx->ncu, t.blocks_per_cu, p, dN, lds_blocks(lds));
   long long nt = (npts + P - 1) / P;
   for (long long fit = avail / (row + row / kGroupTiles + 64); bytes_for(nt) > avail;
        fit -= std::max(1ll, fit / 64)) {
@@ -820,11 +824,7 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   A.tile_count = (int)nt;
   A.njobs = 1;
   A.ilp = t.ilp;
-  A.hist64 = fixed_hist(p, t.hist64, dN) ? 0 : 1;
-  const int nb = (ndim + 3) / 4;
-  const bool pow2 = (nbins & (nbins - 1)) == 0;
-  size_t hist_off = 0;
-  const size_t lds = dosample_lds(p, !A.hist64, nb, pow2, ndim, nbins, &hist_off);
+  A.hist64 = fixed ? 0 : 1;
   A.lds_hist_byte_off = (long long)hist_off;
   CCUBA_HIP(launch_dosample(A, p, nb, pow2, ndim == 4 * nb, (int)std::min<long long>(B, nt),
                             (int)bs, lds, s));

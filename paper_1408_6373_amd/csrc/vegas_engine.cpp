@@ -244,19 +244,29 @@ void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, lon
   *total = t;
 }
 
-// Every tile costs its block's setup and a row of d N results that the folds
-// read again, so a small iteration takes fewer and larger tiles: at most 64 (the
-// refine launch then needs no fold) up to 2^16 points, a tile per compute unit
-// up to 3072 points each, two up to 12288, the setting's from there on.
-// 10 iterations at d = 8, FP32 / FP64, us: 3 x 10^4 points in 64 tiles 193 / 189,
-// in one per compute unit 226 / 223; with 1, 2 and 3 tiles per compute unit
-//   10^5      238 / 237   261 / 254   258 / 254
-//   10^6      328 / 328   329 / 341   340 / 358
-//   2 x 10^6  427 / 419   402 / 432   412 / 442
-//   4 x 10^6  614 / 607   544 / 596   541 / 604
-long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu) {
-  const long long per_cu = n <= 3072ll * ncu ? 1 : n <= 12288ll * ncu ? 2 : blocks_per_cu;
-  long long tiles = (long long)ncu * std::min<long long>(per_cu, blocks_per_cu);
+int lds_blocks(size_t lds) {
+  return (int)std::max<long long>(1, 160 * 1024 / (long long)(lds + 512));  // (static LDS: 144 B)
+}
+
+// Every tile costs its block's setup and a row of d N results that the folds read
+// again, so a small iteration takes fewer and larger tiles: at most 64 (the refine
+// launch then needs no fold) up to 2^16 points; then one per compute unit, the
+// longer the more a row holds and the slower a point is; two up to 24576 points
+// each; the setting's from there on; and never more than a compute unit holds at
+// once, as the rest would run behind them.  10 iterations, us, with 1, 2 and 3 tiles
+// per compute unit (3 x 10^4 points at d = 8 in 64 tiles 193, in 256 226):
+//                          FP64                                  FP32
+//   d, N      10^6         3 x 10^6       10^7          10^6         3 x 10^6     10^7
+//   2, 128    237 242 241  309 300 300  560  515  507   236 234 233  305 284 285  556  461  445
+//   8, 128    307 317 325  491 480 487  1136 1063 1070  305 304 311  475 438 449  1063 928  888
+//   12, 128   370 387 387  620 632 628  1508 1497 1501  376 381 378  628 587 587  1505 1326 1275
+//   16, 256 (one block per compute unit)
+//             536 647 647  890 1013 1012 2172 2294 2383 525 644 637  833 957 963  1991 2111 2209
+long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int prec,
+                      long long dN, int resident) {
+  const long long one = (prec == FP64 ? 8 : 3) * std::max<long long>(1024, dN);
+  const long long per_cu = n <= one * ncu ? 1 : n <= 24576ll * ncu ? 2 : blocks_per_cu;
+  long long tiles = (long long)ncu * std::min<long long>({per_cu, blocks_per_cu, resident});
   if (n <= 1 << 16) tiles = std::min<long long>(tiles, kDirectTiles);
   return std::max(round_up((n + tiles - 1) / tiles, bs), bs);
 }
@@ -346,8 +356,20 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     const VegasSpec &sp = specs[j];
     const int p = sp.prec;
     const int bs = block_[p];
-    const long long P =
-        single ? single_tile(nmax[j], bs, ctx_->ncu, ctx_->tune[p].blocks_per_cu) : batch_P[p];
+    long long P = batch_P[p];
+    if (single) {
+      const long long dN = (long long)sp.ndim * sp.nbins;
+      size_t off = 0;
+      const size_t lds = dosample_lds(p, fixed_hist(p, hist64_[p], dN), (sp.ndim + 3) / 4,
+                                      (sp.nbins & (sp.nbins - 1)) == 0, sp.ndim, sp.nbins, &off);
+      int resident = lds_blocks(lds);
+      // (a caller's function may hold more registers than the built-in families)
+      int held = 0;
+      if (user_fn_ && hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&held, user_fn_, bs,
+                                                                         lds) == hipSuccess)
+        resident = std::max(1, std::min(resident, held));
+      P = single_tile(nmax[j], bs, ctx_->ncu, ctx_->tune[p].blocks_per_cu, p, dN, resident);
+    }
     const int nt = (int)std::max<long long>(1, (nmax[j] + P - 1) / P);
     VJob &J = hjobs_[j];
     J.ndim = sp.ndim;

@@ -66,10 +66,14 @@ int launch_tile_groups(ccuba_ctx *ctx, VegasArgs A, const std::vector<TileGroup>
                        hipStream_t s, hipFunction_t user = nullptr);
 // Inclusive prefixes over jobs of their fold tasks (see FoldArgs).
 void fold_tasks(const std::vector<VJob> &jobs, std::vector<long long> &ends, long long *total);
-// Points of a tile of a single integral whose largest iteration has n points,
-// a multiple of bs (its block): about one tile per block, of at most
-// blocks_per_cu blocks on each of ncu compute units.
-long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu);
+// Blocks of a DoSample instance that a compute unit's LDS holds at once.
+int lds_blocks(size_t lds);
+
+// Points of a tile of a single integral (dN = ndim nbins) whose largest iteration
+// has n points, a multiple of bs (its block): about one tile per block, of at most
+// blocks_per_cu blocks on each of ncu compute units, which hold `resident' at once.
+long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int prec,
+                      long long dN, int resident);
 
 // Whether the refine launch can sum every job's tile rows itself (no fold).
 bool direct_refine(const std::vector<VJob> &jobs);

@@ -258,3 +258,20 @@ def test_oscillatory_rule_at_the_edges_of_its_splits(cc, ctx, d, nreg):
         D = np.sort(o["dfour"])[::-1]
         if D[0] - D[1] > 1e-9 * D[0]:
             assert np.all(g["axis"][same] == o["axis"])
+
+
+# ---- the sizes where a single integral's tiles change ---------------------------------
+
+@pytest.mark.parametrize("d,nbins,npts", [(3, 64, 2 << 20), (3, 64, (2 << 20) + 1),
+                                          (2, 64, 24576 * 256 + 1), (16, 256, 65537),
+                                          (16, 256, 3072 * 256 + 1)])
+def test_tiles_of_a_single_integral_at_its_edges(cc, ctx, d, nbins, npts):
+    # one and two tiles per compute unit, the setting's three, and the one block that
+    # a compute unit holds at d = 16 (the bars of the integrator's parity tests)
+    a, u = W.genz_params(W.GAUSSIAN, d, 12)
+    kw = dict(nbins=nbins, nstart=npts, maxeval=2 * npts, seed=6)
+    g = cc.vegas(W.GAUSSIAN, a, u, ctx=ctx, **kw)
+    o = O.vegas(O.genz(W.GAUSSIAN, a, u), d, **kw)
+    assert g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+        assert abs(g[k] - o[k]) <= tol * abs(o[k]), k

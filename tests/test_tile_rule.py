@@ -1,0 +1,36 @@
+"""The tiles of a single integral, by the rule that the library plans them with."""
+import ctypes as C
+
+import pytest
+
+import paper_1408_6373_amd as cc
+
+FP64, FP32 = 0, 1
+
+
+def _tiles(n, prec, dN, resident=8, bs=256, ncu=256, per_cu=3):
+    rule = cc._lib["_ZN5ccuba11single_tileExxiiixi"]
+    rule.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int, C.c_int, C.c_longlong, C.c_int]
+    rule.restype = C.c_longlong
+    P = rule(n, bs, ncu, per_cu, prec, dN, resident)
+    assert P > 0 and P % bs == 0
+    return -(-n // P)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("dN", [2, 1024, 4096])
+def test_no_more_tiles_than_blocks(prec, dN):
+    for n in (2, 255, 65536, 65537, 10**6, 10**7, 2**32 - 1):
+        for per_cu in (1, 2, 3, 16):
+            assert _tiles(n, prec, dN, per_cu=per_cu) <= 256 * per_cu
+            assert _tiles(n, prec, dN, per_cu=per_cu, resident=1) <= 256
+        assert n > 65536 or _tiles(n, prec, dN) <= 64
+
+
+@pytest.mark.parametrize("n,prec,dN,resident,per_cu", [
+    (10**6, FP64, 1024, 3, 1), (2 * 10**6, FP64, 1024, 3, 1), (4 * 10**6, FP64, 1024, 3, 2),
+    (10**6, FP32, 1024, 3, 2), (4 * 10**6, FP32, 1024, 3, 2), (10**7, FP32, 1024, 3, 3),
+    (3 * 10**6, FP64, 1536, 3, 1), (10**7, FP64, 4096, 1, 1), (10**6, FP32, 4096, 1, 1)])
+def test_tiles_follow_the_measured_best(n, prec, dN, resident, per_cu):
+    # the fastest of 1, 2 and 3 tiles per compute unit, or within 2% of it, as measured
+    assert 256 * (per_cu - 1) < _tiles(n, prec, dN, resident) <= 256 * per_cu
