@@ -242,6 +242,13 @@ double time_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs, bool spli
 
 }  // namespace
 
+int batch_tile_sizes(long long setting, long long out[4]) {
+  int n = 0;
+  for (long long v : {setting, 4096ll, 16384ll, 65536ll})
+    if (std::find(out, out + n, v) == out + n) out[n++] = v;
+  return n;
+}
+
 void autotune_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs) {
   for (int prec = 0; prec < 2; ++prec) {
     if (ctx->tuned_batch[prec]) continue;
@@ -263,7 +270,8 @@ void autotune_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs) {
     const int profile = ctx->profile;  // (the tuning runs are not profiled)
     ctx->profile = 0;
     const int bpcs[] = {2, 3, 4, 6};
-    const long long tiles[] = {4096, 16384, 65536};
+    long long tiles[4];
+    const int nsizes = batch_tile_sizes(saved.min_tile, tiles);
     // one engine, or two halves (2+ integrals); a tile plan that holds one
     // integral is the single-integral one, which does not use the minimum
     // tile size
@@ -271,7 +279,7 @@ void autotune_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs) {
       const bool split = streams == 2;
       const size_t cut = split ? batch_cut(mine) : mine.size();
       const bool single = split ? (cut == 1 && mine.size() == 2) : mine.size() == 1;
-      const int ntiles = single ? 1 : 3;
+      const int ntiles = single ? 1 : nsizes;
       for (int bpc : bpcs)
         for (int ilp = 1; ilp <= 2; ++ilp)
           for (int ti = 0; ti < ntiles; ++ti)

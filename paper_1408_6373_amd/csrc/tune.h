@@ -18,6 +18,9 @@ void maybe_autotune(ccuba_ctx *ctx, int prec);
 // once per context and precision; the choice is cached in the file named by
 // CCUBA_TUNE_CACHE under a signature of the jobs' shapes.
 struct VegasSpec;
+// The smallest-tile sizes it tries, each once: the setting's, so that tuning is
+// never slower than not tuning, and three larger steps.  Returns their number.
+int batch_tile_sizes(long long setting, long long out[4]);
 void autotune_batch(ccuba_ctx *ctx, const std::vector<VegasSpec> &specs);
 
 }  // namespace ccuba

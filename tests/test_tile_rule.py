@@ -1,4 +1,4 @@
-"""The tiles of a single integral, by the rule that the library plans them with."""
+"""The tiles of an integral, by the rules that the library plans them with."""
 import ctypes as C
 
 import pytest
@@ -34,3 +34,16 @@ def test_no_more_tiles_than_blocks(prec, dN):
 def test_tiles_follow_the_measured_best(n, prec, dN, resident, per_cu):
     # the fastest of 1, 2 and 3 tiles per compute unit, or within 2% of it, as measured
     assert 256 * (per_cu - 1) < _tiles(n, prec, dN, resident) <= 256 * per_cu
+
+
+@pytest.mark.parametrize("setting,sizes", [(2048, {2048, 4096, 16384, 65536}),
+                                           (4096, {4096, 16384, 65536}),
+                                           (65536, {4096, 16384, 65536}),
+                                           (100, {100, 4096, 16384, 65536})])
+def test_autotuner_tries_the_setting_it_replaces(setting, sizes):
+    f = cc._lib["_ZN5ccuba16batch_tile_sizesExPx"]
+    f.argtypes = [C.c_longlong, C.POINTER(C.c_longlong)]
+    f.restype = C.c_int
+    out = (C.c_longlong * 4)()
+    n = f(setting, out)
+    assert n == len(sizes) and set(out[:n]) == sizes
