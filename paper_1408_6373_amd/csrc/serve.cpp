@@ -21,7 +21,7 @@ struct Server::Req {
   VegasSpec vs;
   VJob hj{};
   bool vdone = false;
-  DevBuf<double> grid, tsums, thist, gsums, ghist, iters, p64;
+  DevBuf<double> grid, tsums, thist, iters, p64;
   DevBuf<float> p32;
   // Cuhre
   std::unique_ptr<CuhreRun> cuhre;
@@ -118,8 +118,6 @@ void Server::release(Req &r) {
   r.grid.release();
   r.tsums.release();
   r.thist.release();
-  r.gsums.release();
-  r.ghist.release();
   r.iters.release();
   r.p64.release();
   r.p32.release();
@@ -191,13 +189,12 @@ int Server::activate(Req &r) {
   long long P = 0;
   int nt = 0, rc = CCUBA_ENOMEM;
   for (long long tile : {least, std::max(least, kTightTile)}) {
-    P = std::max(round_up(tile, bs), round_up((nmax + 63) / 64, bs));
+    // (at most kDirectTiles tiles: the refine launch sums their rows, without a fold)
+    P = std::max(round_up(tile, bs), round_up((nmax + kDirectTiles - 1) / kDirectTiles, bs));
     nt = (int)std::max<long long>(1, (nmax + P - 1) / P);
-    const int ng = ngroups_of(nt);
     r.thist.release();
     if (!(rc = r.grid.alloc(ctx_, row)) && !(rc = r.tsums.alloc(ctx_, 2 * nt)) &&
-        !(rc = r.thist.alloc(ctx_, nt * dN)) && !(rc = r.gsums.alloc(ctx_, 2 * ng)) &&
-        !(rc = r.ghist.alloc(ctx_, ng * dN)) &&
+        !(rc = r.thist.alloc(ctx_, nt * dN)) &&
         !(rc = r.iters.alloc(ctx_, 2 * (size_t)cap)) &&
         !(rc = r.p64.alloc(ctx_, 2 * kParamRow)) && !(rc = r.p32.alloc(ctx_, 2 * kParamRow)))
       break;
@@ -231,8 +228,6 @@ int Server::activate(Req &r) {
   J.grid = r.grid.p;
   J.tsums = r.tsums.p;
   J.thist = r.thist.p;
-  J.gsums = r.gsums.p;
-  J.ghist = r.ghist.p;
   J.iter_I = r.iters.p;
   J.iter_var = r.iters.p + cap;
   J.p64 = r.p64.p;
@@ -319,8 +314,7 @@ int Server::tick() {
   // Vegas: one DoSample per (precision, dimension class) over every running
   // request, one refine over all of them
   std::vector<VJob> table;
-  std::vector<long long> ends;  // host tables live until the tick's sync
-  std::vector<int> tiles;
+  std::vector<int> tiles;  // host tables live until the tick's sync
   std::vector<TileGroup> groups;
   for (auto &r : active_)
     if (r->job.method == 0 && !r->vdone) table.push_back(r->hj);
@@ -341,19 +335,9 @@ int Server::tick() {
     A.tile_job = tiles_.p;
     A.njobs = (int)table.size();
     if ((rc = launch_tile_groups(ctx_, A, groups, s))) return rc;
-    long long ftot = 0;
-    fold_tasks(table, ends, &ftot);
-    const bool direct = direct_refine(table);
-    if (!direct) {
-      if (fold_end_.n < ends.size() && (rc = fold_end_.alloc(ctx_, ends.size() * 2))) return rc;
-      CCUBA_HIP(hipMemcpyAsync(fold_end_.p, ends.data(), ends.size() * sizeof(long long),
-                               hipMemcpyHostToDevice, s));
-      FoldArgs F{jobs_.p, fold_end_.p, (int)table.size(), ftot, 0, nullptr, nullptr};
-      CCUBA_HIP(launch_fold(F, s));
-    }
     int dmax = 1;
     for (const VJob &J : table) dmax = std::max(dmax, J.ndim);
-    CCUBA_HIP(launch_refine(A, (int)table.size(), dmax, direct, s));
+    CCUBA_HIP(launch_refine(A, (int)table.size(), dmax, true, s));
   }
   // Cuhre: one rule launch over the children of every stepping request
   if (!segs.empty()) {

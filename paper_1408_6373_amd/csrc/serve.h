@@ -65,7 +65,6 @@ class Server {
   std::vector<int> free_slots_;
   DevBuf<VJob> jobs_;
   DevBuf<int> tiles_;
-  DevBuf<long long> fold_end_;
   DevBuf<CSeg> segs_;
   DevBuf<long long> seg_end_;
   // per slot, the Cuhre totals in pinned host memory the device writes to

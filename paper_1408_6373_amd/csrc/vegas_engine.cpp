@@ -775,19 +775,6 @@ int VegasEngine::read_results(VState &st, double *I, double *var, int max_iter, 
   return CCUBA_OK;
 }
 
-int VegasEngine::read_history(int job, int n, double *I, double *var, hipStream_t s) {
-  if (job < 0 || job >= njobs()) return CCUBA_EINVAL;
-  n = std::min(n, hjobs_[job].hist_cap);
-  if (n <= 0) return CCUBA_OK;
-  if (I)
-    CCUBA_HIP(hipMemcpyAsync(I, hjobs_[job].iter_I, n * sizeof(double),
-                             hipMemcpyDeviceToHost, s));
-  if (var)
-    CCUBA_HIP(hipMemcpyAsync(var, hjobs_[job].iter_var, n * sizeof(double),
-                             hipMemcpyDeviceToHost, s));
-  return drain(s);
-}
-
 int VegasEngine::read_grid(int job, double *grid, hipStream_t s) {
   if (job < 0 || job >= njobs()) return CCUBA_EINVAL;
   const VJob &J = hjobs_[job];

@@ -119,7 +119,6 @@ class VegasEngine {
   int read_results(VState &st, double *I, double *var, int max_iter, double *grid,
                    hipStream_t s);
   int read_states(std::vector<VState> &out, hipStream_t s);
-  int read_history(int job, int n, double *I, double *var, hipStream_t s);
   int read_grid(int job, double *grid, hipStream_t s);
   // The grid and iteration t's estimate and variance of one job, read with
   // one synchronisation (what a checkpoint needs after each iteration).

@@ -275,3 +275,22 @@ def test_tiles_of_a_single_integral_at_its_edges(cc, ctx, d, nbins, npts):
     assert g["neval"] == o["neval"] and g["fail"] == o["fail"]
     for k, tol in (("integral", 1e-12), ("error", 1e-11)):
         assert abs(g[k] - o[k]) <= tol * abs(o[k]), k
+
+
+# ---- a served request holds what its launches read ------------------------------------
+
+def test_served_request_in_a_small_budget(cc, ctx):
+    # eight tile rows of 32 KiB, the grid, the history and the server's tables: 404 KiB,
+    # and 32 KiB more with rows for a fold that a request of at most 64 tiles never has
+    a, u = W.genz_params(W.GAUSSIAN, 16, 60)
+    spec = dict(method=0, ndim=16, family=W.GAUSSIAN, a=a, u=u, seed=1, nstart=131072,
+                maxeval=2 * 131072, nbins=256, flags=cc.FP64)
+    c = cc.Context(hbm_budget=416 << 10)
+    t = cc.submit(c, spec)
+    cc.drain(c)
+    r = cc.poll(c, t)
+    c.close()
+    w = cc.vegas_batch(ctx, [spec])[0]
+    assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
+    for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+        assert abs(r[k] - w[k]) <= tol * abs(w[k]), k
