@@ -412,12 +412,15 @@ int CuhreRun::run(hipStream_t s) {
   auto outcome = [&](int t) {
     return poll_outcome(host_slots + slot(t) + 2, (unsigned long long)t, s);
   };
+  const long long evals_before = ctx_->stats.rule_evals;
   // finish with the state of plan p, whose totals are in slot q's place and
   // whose outcome (code) ended the run
   auto finish = [&](const Plan &p, int q, int code) -> int {
     CCUBA_HIP(hipStreamSynchronize(s));  // queued launches run empty; the last ones end
     n_ = p.n;
     neval_ = p.neval;
+    // (what was queued after that state evaluated nothing)
+    if (ctx_->profile) ctx_->stats.rule_evals = evals_before + neval_;
     next_id_ = p.next_id;
     batches_ = p.batches;
     done_ = true;
@@ -482,7 +485,6 @@ int CuhreRun::run(hipStream_t s) {
       CCUBA_HIP(hipEventElapsedTime(&ms, e0, e1));
       ctx_->stats.rule_launches += 1;
       ctx_->stats.rule_ms += ms;
-      ctx_->stats.rule_evals += np_ * ((2ll << t0) - 1);
       (void)hipEventDestroy(e0);
       (void)hipEventDestroy(e1);
     }

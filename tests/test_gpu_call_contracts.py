@@ -294,3 +294,22 @@ def test_served_request_in_a_small_budget(cc, ctx):
     assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
     for k, tol in (("integral", 1e-12), ("error", 1e-11)):
         assert abs(r[k] - w[k]) <= tol * abs(w[k]), k
+
+
+# ---- profile mode: the rule's evaluations ----------------------------------------------
+
+@pytest.mark.parametrize("fam,d,kw", [
+    (W.GAUSSIAN, 2, dict(epsrel=1e-3, maxeval=10**6)),           # ends among the first states
+    (W.GAUSSIAN, 3, dict(epsrel=1e-9, maxeval=10**6, max_regions_per_batch=100)),  # converges later
+    (W.CORNER_PEAK, 3, dict(epsrel=1e-30, maxeval=33 * 20)),     # runs out of budget
+    (W.GAUSSIAN, 10, dict(epsrel=1e-2, maxeval=10**6))])         # no shared first launch
+def test_profiled_rule_evaluations_are_the_runs(cc, fam, d, kw):
+    import bench
+    a, u = W.genz_params(fam, d, 60 + d)
+    c = cc.Context()
+    c.config("profile", 1)
+    bench._stats(cc, c)
+    r = cc.cuhre(fam, a, u, ctx=c, **kw)
+    st = bench._stats(cc, c)
+    c.close()
+    assert st.rule_evals == r["neval"] and st.rule_launches > 0 and st.rule_ms > 0.0
