@@ -1396,7 +1396,7 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
   unsigned long long mask = shared_digit ? 0ull : 0xFFFFull << 48;
   int dig;
   // up to kExactReg keys per thread, and their positions (below 2^32: a store
-  // of 2^32 regions would need over 500 GB), stay in registers
+  // of 2^32 regions would need over 340 GB), stay in registers
   constexpr int kExactReg = 16;
   constexpr long long kDirect = kTopThreads;  // candidates ranked directly
   const bool inreg = mc <= (long long)kExactReg * kTopThreads;

@@ -16,7 +16,7 @@ struct CuhreSpec {
 int validate_cuhre(const CuhreSpec &s);
 long long gm_npoints(int ndim);
 
-// Rule weights (w7, w5: [17][5]) and generators, from Genz & Malik (1980).
+// The rule's generators, from Genz & Malik (1980).
 RuleLambdas gm_lambdas();
 
 class CuhreRun {

@@ -13,10 +13,10 @@
 //              then a fixed-order block sum -> one FP64 partial per tile
 //   a6 hist    H_j[k_j] += v^2 with LDS atomics, written per tile as FP64
 // A fold kernel sums the tile rows 32 at a time in tile order, and those group
-// rows are summed in group order (so the sums are deterministic);
-// the refine kernel (one workgroup per integral) then does a7: iteration
-// statistics, the inverse-variance combination with chi^2 and its
-// probability, the convergence test and Lepage's grid refinement, all in FP64.
+// rows are summed in group order (so the sums are deterministic); the refine kernel
+// (one workgroup per dimension of an integral) then does a7: iteration statistics,
+// the inverse-variance combination with chi^2 and its probability, the convergence
+// test and Lepage's grid refinement, all in FP64.
 // Iteration t and its point count are read from device state, so a captured
 // iteration replays unchanged.
 #include "engine.h"

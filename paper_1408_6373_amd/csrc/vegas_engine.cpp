@@ -829,7 +829,8 @@ int VegasEngine::refine_only(const double *hist, const double *grid_in, double *
   CCUBA_HIP(hipStreamSynchronize(s));
   rc = set_iteration(0, 0, s);
   if (rc) return rc;
-  // (the refine kernel reads the state through the snapshot the fold takes)
+  // (the refine kernel reads the state through the snapshot, which a DoSample launch
+  // takes otherwise)
   CCUBA_HIP(hipMemcpyAsync(hjobs_[0].snap, hjobs_[0].state, sizeof(VState),
                            hipMemcpyDeviceToDevice, s));
   CCUBA_HIP(launch_refine(args_, 1, dmax_, false, s));

@@ -15,7 +15,7 @@ __device__ __forceinline__ double dpp_or(double v, double identity) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// A reduction over the wavefront, its result in lane 63 the row shifts leave
+// A reduction over the wavefront, its result in lane 63: the row shifts leave
 // each row's result in its lane 15, the row broadcasts carry it on.
 template <typename OP>
 __device__ __forceinline__ double wave_reduce63(double v, double identity, OP op) {
