@@ -84,9 +84,11 @@ __host__ __device__ inline int ngroups_of(int ntiles) { return (ntiles + kGroupT
 // Flags understood by the device code.
 enum { FLAG_FREEZE_GRID = 1 << 4 };
 
+// Points from which on a tile's row of partial results costs little beside them.
+constexpr long long kFullTile = 16384;
 // Points of a batch's or a served request's smallest tile where the memory budget
 // refuses the setting's: fewer rows of partial results for longer launches.
-constexpr long long kTightTile = 16384;
+constexpr long long kTightTile = kFullTile;
 
 // Launch geometry of the DoSample kernel.
 struct VegasTune {

@@ -271,6 +271,21 @@ long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int
   return std::max(round_up((n + tiles - 1) / tiles, bs), bs);
 }
 
+// The setting's smallest tile; or larger while each compute unit still gets two
+// tiles (three where a row is short) up to 16384 points, from which on a row costs
+// little beside its points; or what gives every block 8 tiles.
+// Points an iteration, us by the smallest tile: 1.6 x 10^7 at d = 9 to 10, 256 bins,
+// FP64 (9 iterations) 2048 2882, 8192 2346, 16384 2214; 8.6 x 10^6 at d = 9 to 12,
+// 200 bins, FP32 (5) 2048 903, 8192 756, 16384 763; 10^7 at d = 2 to 5, 50 bins, FP32
+// (5) 2048 765, 6144 709, 16384 826; 2 x 10^6 at d = 8 (5) 2048 350, 6144 360, 16384 448.
+long long batch_tile(long long total, double rows, long long min_tile, long long bs, int ncu,
+                     int blocks_per_cu) {
+  const long long B = (long long)ncu * blocks_per_cu;
+  const long long per_cu = rows >= 1024.0 * (double)total ? 2 : 3;
+  const long long fill = std::min(kFullTile, round_up(total / (ncu * per_cu), bs));
+  return std::max({round_up(min_tile, bs), fill, round_up((total + B * 8 - 1) / (B * 8), bs), bs});
+}
+
 bool direct_refine(const std::vector<VJob> &jobs) {
   for (const VJob &J : jobs)
     if (J.ntiles > kDirectTiles) return false;
@@ -312,22 +327,21 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
     has_prec_[specs[j].prec] = 1;
     if (iters[j] > 0) evals_iter_ += specs[j].nstart;
   }
-  // Tile size of a batch, per precision: the tuned minimum, or larger when
-  // that would give more than 8 tiles per block; then, within 3/4 to 5/4 of
-  // that size, the one that makes the most tiles a compute unit gets
-  // smallest.  The blocks take the tiles in turn, so a compute unit works
-  // through about ceil(tiles / CUs) of them and the launch takes as long as
-  // the busiest one: 1222 tiles of 16384 points leave some units 5 tiles
-  // (81920 points) where 4.8 is the mean, 1262 of 15872 leave at most 5 of
-  // the smaller tiles (79360).
+  // Tile size of a batch, per precision: within 3/4 to 5/4 of batch_tile's, the one
+  // that makes the most tiles a compute unit gets smallest.  The blocks take the
+  // tiles in turn, so a compute unit works through about ceil(tiles / CUs) of them
+  // and the launch takes as long as the busiest one: 1222 tiles of 16384 points
+  // leave some units 5 tiles (81920 points) where 4.8 is the mean, 1262 of 15872
+  // leave at most 5 of the smaller tiles (79360).
   long long batch_P[2] = {0, 0};
   for (int p = 0; p < 2 && !single; ++p) {
     if (!has_prec_[p]) continue;
     const int bs = block_[p];
-    const long long B = (long long)ctx_->ncu * ctx_->tune[p].blocks_per_cu;
-    const long long target = round_up((total[p] + B * 8 - 1) / (B * 8), bs);
-    const long long P0 = std::max<long long>(
-        std::max(round_up(ctx_->tune[p].min_tile, bs), target), bs);
+    double rows = 0.0;
+    for (int j = 0; j < n; ++j)
+      if (specs[j].prec == p) rows += (double)nmax[j] * specs[j].ndim * specs[j].nbins;
+    const long long P0 = batch_tile(total[p], rows, ctx_->tune[p].min_tile, bs, ctx_->ncu,
+                                    ctx_->tune[p].blocks_per_cu);
     long long best = P0, best_load = -1;
     for (long long P = std::max<long long>(bs, round_up(3 * P0 / 4, bs)); P <= 5 * P0 / 4;
          P += bs) {

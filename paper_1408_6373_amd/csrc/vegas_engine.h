@@ -75,6 +75,12 @@ int lds_blocks(size_t lds);
 long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int prec,
                       long long dN, int resident);
 
+// The same for the integrals of one precision of a batch (of an engine: one or both
+// halves), which take total points in their largest iterations, rows the sum of
+// their points times d N.
+long long batch_tile(long long total, double rows, long long min_tile, long long bs, int ncu,
+                     int blocks_per_cu);
+
 // Whether the refine launch can sum every job's tile rows itself (no fold).
 bool direct_refine(const std::vector<VJob> &jobs);
 

@@ -313,3 +313,15 @@ def test_profiled_rule_evaluations_are_the_runs(cc, fam, d, kw):
     st = bench._stats(cc, c)
     c.close()
     assert st.rule_evals == r["neval"] and st.rule_launches > 0 and st.rule_ms > 0.0
+
+
+def test_batch_of_middle_sized_tiles_matches_the_integrals_alone(cc, ctx):
+    # some 4 x 10^6 points an iteration at d N of about 2000: tiles between the
+    # setting's smallest and a full one
+    specs = _jobs(cc, [9, 10, 11, 12] * 8, [100003 + 1777 * q for q in range(32)], 200)
+    for s, r in zip(specs, cc.vegas_batch(ctx, specs)):
+        w = cc.vegas(s["family"], s["a"], s["u"], ctx=ctx, seed=s["seed"], nbins=200,
+                     nstart=s["nstart"], maxeval=s["maxeval"])
+        assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
+        for k, tol in (("integral", 1e-12), ("error", 1e-11)):
+            assert abs(r[k] - w[k]) <= tol * abs(w[k]), k

@@ -47,3 +47,20 @@ def test_autotuner_tries_the_setting_it_replaces(setting, sizes):
     out = (C.c_longlong * 4)()
     n = f(setting, out)
     assert n == len(sizes) and set(out[:n]) == sizes
+
+
+@pytest.mark.parametrize("total,dN,lo,hi", [
+    (8 * 10**6, 2432, 12288, 16384),    # long rows: two tiles per compute unit
+    (6.8 * 10**6, 1408, 12288, 16384),
+    (4.3 * 10**6, 2100, 6144, 10240),
+    (5 * 10**6, 175, 5120, 8192),       # short rows: three
+    (10**6, 1024, 2048, 2048),          # the setting's smallest
+    (2.7 * 10**7, 2700, 16384, 16384),  # no more than a full tile
+    (3 * 10**8, 1024, 40000, 65536)])   # or eight tiles a block
+def test_batch_tiles_follow_the_measured_best(total, dN, lo, hi):
+    f = cc._lib["_ZN5ccuba10batch_tileExdxxii"]
+    f.argtypes = [C.c_longlong, C.c_double, C.c_longlong, C.c_longlong, C.c_int, C.c_int]
+    f.restype = C.c_longlong
+    P = f(int(total), float(total) * dN, 2048, 256, 256, 3)
+    assert P % 256 == 0 and lo <= P <= hi
+    assert f(int(total), float(total) * dN, 131072, 256, 256, 3) == 131072  # a larger setting
