@@ -1373,14 +1373,14 @@ __global__ void __launch_bounds__(kTopThreads) topk_gather_kernel(const double *
 // are not all taken (a tie across the threshold), passes of 8 bits over the
 // positions (ascending), else the largest of their positions.  Its key to
 // prefix[0], its position to krem[0]; the selected candidates are added to
-// their tiles' counts.
+// the counts of their tiles (of nb).
 __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned long long *ckey,
                                                                  const long long *cpos,
                                                                  const unsigned long long *cnt,
                                                                  const int *window,
                                                                  unsigned long long *prefix,
                                                                  long long *krem,
-                                                                 long long *bsum,
+                                                                 long long *bsum, long long nb,
                                                                  const int *done) {
   if (stopped(done)) return;
   __shared__ unsigned h[4096];
@@ -1515,19 +1515,31 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     prefix[0] = pre;
     krem[0] = (long long)tpos;
   }
-  auto count = [&](unsigned long long k, long long p) {
-    if (k > pre || (k == pre && p <= (long long)tpos))
-      atomicAdd((unsigned long long *)&bsum[p / kScanTile], 1ull);
-  };
-  if (inreg) {
+  // the selected candidates join the gather's counts, summed in LDS 4096 tiles
+  // at a time (one by one in memory, 16384 candidates of one digit took 60 us)
+  for (long long w0 = 0; w0 < nb; w0 += 4096) {
+    const int n = (int)min(nb - w0, 4096ll);
+    __syncthreads();  // (h's last readers)
+    for (int q = t; q < n; q += kTopThreads) h[q] = 0u;
+    __syncthreads();
+    auto count = [&](unsigned long long k, long long p) {
+      const long long tile = p / kScanTile - w0;
+      if ((k > pre || (k == pre && p <= (long long)tpos)) && tile >= 0 && tile < n)
+        atomicAdd(&h[tile], 1u);
+    };
+    if (inreg) {
 #pragma unroll
-    for (int q = 0; q < kExactReg; ++q)
-      if (kr[q]) count(kr[q], pr[q]);
-  } else {
-    for (long long i = t; i < mc; i += kTopThreads) {
-      const unsigned long long k = ckey[i];
-      if (k >= pre) count(k, cpos[i]);
+      for (int q = 0; q < kExactReg; ++q)
+        if (kr[q]) count(kr[q], pr[q]);
+    } else {
+      for (long long i = t; i < mc; i += kTopThreads) {
+        const unsigned long long k = ckey[i];
+        if (k >= pre) count(k, cpos[i]);
+      }
     }
+    __syncthreads();
+    for (int q = t; q < n; q += kTopThreads)
+      if (const unsigned c = h[q]) bsum[w0 + q] += c;
   }
 }
 
@@ -1725,7 +1737,7 @@ hipError_t launch_select(const CRegions &R, long long m, long long K, const CScr
                      S.cand_cnt, S.bsum, (const int *)S.done);
   hipLaunchKernelGGL(topk_exact_kernel, dim3(1), dim3(kTopThreads), 0, s, S.cand_key, S.cand_pos,
                      S.cand_cnt, (const int *)S.window, S.prefix, S.krem, S.bsum,
-                     (const int *)S.done);
+                     scratch_blocks(m), (const int *)S.done);
   return hipGetLastError();
 }
 

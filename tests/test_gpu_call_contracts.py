@@ -325,3 +325,30 @@ def test_batch_of_middle_sized_tiles_matches_the_integrals_alone(cc, ctx):
         assert r["status"] == 0 and r["neval"] == w["neval"] and r["fail"] == w["fail"]
         for k, tol in (("integral", 1e-12), ("error", 1e-11)):
             assert abs(r[k] - w[k]) <= tol * abs(w[k]), k
+
+
+# ---- Cuhre's selection: many candidates of one digit, and many tiles ---------------------
+
+def _cuhre_as_the_oracle(cc, ctx, fam, d, regions, batch):
+    a, u = W.genz_params(fam, d, 3)
+    kw = dict(epsrel=1e-30, maxeval=(2**d + 2 * d * d + 2 * d + 1) * (2 * regions - 1),
+              max_regions_per_batch=batch)
+    g = cc.cuhre(fam, a, u, ctx=ctx, **kw)
+    o = O.cuhre(O.genz(fam, a, u), d, **kw)
+    assert g["nregions"] == o["nregions"] and g["neval"] == o["neval"] and g["fail"] == o["fail"]
+    assert abs(g["integral"] - o["integral"]) <= 1e-12 * abs(o["integral"])
+    assert abs(g["error"] - o["error"]) <= 1e-10 * o["error"] + 1e-14 * abs(o["integral"])
+
+
+@pytest.mark.parametrize("fam,d,regions,batch", [(W.OSCILLATORY, 5, 60000, 9000),
+                                                 (W.OSCILLATORY, 3, 200000, 30000),
+                                                 (W.GAUSSIAN, 2, 300000, 90000)])
+def test_cuhre_with_many_candidates_matches_oracle(cc, ctx, fam, d, regions, batch):
+    # the errors of a smooth integrand share few digits: thousands of candidates for
+    # the last places, beyond what the ranking holds in registers too
+    _cuhre_as_the_oracle(cc, ctx, fam, d, regions, batch)
+
+
+def test_cuhre_with_many_tiles_matches_oracle(cc, ctx):
+    # the last step selects among 4.5 x 10^6 positions: 4392 tiles, counted 4096 at a time
+    _cuhre_as_the_oracle(cc, ctx, W.OSCILLATORY, 2, 2848576, 1200000)
