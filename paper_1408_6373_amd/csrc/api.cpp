@@ -721,6 +721,7 @@ int ccuba_vegas_dosample_raw(ccuba_ctx *ctx, int ndim, int nbins, const ccuba_in
   CCUBA_HIP(hipSetDevice(ctx->device));
   hipStream_t s = (hipStream_t)hip_stream;
   VegasEngine eng(ctx);
+  eng.set_raw();
   if ((rc = eng.setup({sp}, true, s))) return rc;
   if ((rc = eng.set_iteration(0, iteration, s))) return rc;
   if ((rc = eng.load_grid(0, grid_dev, hipMemcpyDeviceToDevice, s))) return rc;
@@ -769,7 +770,8 @@ int ccuba_vegas_dosample_raw_noalloc(ccuba_ctx *ctx, int ndim, int nbins,
   const bool pow2 = (nbins & (nbins - 1)) == 0, fixed = fixed_hist(p, t.hist64, dN);
   size_t hist_off = 0;
   const size_t lds = dosample_lds(p, fixed, nb, pow2, ndim, nbins, &hist_off);
-  long long P = single_tile(npts, bs, ctx->ncu, t.blocks_per_cu, p, dN, lds_blocks(lds));
+  long long P = single_tile(npts, bs, ctx->ncu, t.blocks_per_cu, p, dN, lds_blocks(lds),
+                            false);
   long long nt = (npts + P - 1) / P;
   for (long long fit = avail / (row + row / kGroupTiles + 64); bytes_for(nt) > avail;
        fit -= std::max(1ll, fit / 64)) {

@@ -249,8 +249,10 @@ int lds_blocks(size_t lds) {
 }
 
 // Every tile costs its block's setup and a row of d N results that the folds read
-// again, so a small iteration takes fewer and larger tiles: at most 64 (the refine
-// launch then needs no fold) up to 2^16 points; then one per compute unit, the
+// again, so a small iteration takes fewer and larger tiles: at most 64 up to 2^16
+// points where a refine launch follows (it then needs no fold; a pass alone takes
+// its fold anyhow: 65536 points at d = 12, FP64, 35.5 us in 256 tiles, 37.0 in 64);
+// then one per compute unit, the
 // longer the more a row holds and the slower a point is; two up to 24576 points
 // each; the setting's from there on; and never more than a compute unit holds at
 // once, as the rest would run behind them.  10 iterations, us, with 1, 2 and 3 tiles
@@ -263,11 +265,11 @@ int lds_blocks(size_t lds) {
 //   16, 256 (one block per compute unit)
 //             536 647 647  890 1013 1012 2172 2294 2383 525 644 637  833 957 963  1991 2111 2209
 long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int prec,
-                      long long dN, int resident) {
+                      long long dN, int resident, bool refined) {
   const long long one = (prec == FP64 ? 8 : 3) * std::max<long long>(1024, dN);
   const long long per_cu = n <= one * ncu ? 1 : n <= 24576ll * ncu ? 2 : blocks_per_cu;
   long long tiles = (long long)ncu * std::min<long long>({per_cu, blocks_per_cu, resident});
-  if (n <= 1 << 16) tiles = std::min<long long>(tiles, kDirectTiles);
+  if (refined && n <= 1 << 16) tiles = std::min<long long>(tiles, kDirectTiles);
   return std::max(round_up((n + tiles - 1) / tiles, bs), bs);
 }
 
@@ -382,7 +384,8 @@ int VegasEngine::setup(const std::vector<VegasSpec> &specs, bool single, hipStre
       if (user_fn_ && hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&held, user_fn_, bs,
                                                                          lds) == hipSuccess)
         resident = std::max(1, std::min(resident, held));
-      P = single_tile(nmax[j], bs, ctx_->ncu, ctx_->tune[p].blocks_per_cu, p, dN, resident);
+      P = single_tile(nmax[j], bs, ctx_->ncu, ctx_->tune[p].blocks_per_cu, p, dN, resident,
+                      !raw_);
     }
     const int nt = (int)std::max<long long>(1, (nmax[j] + P - 1) / P);
     VJob &J = hjobs_[j];

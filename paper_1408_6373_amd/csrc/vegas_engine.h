@@ -71,9 +71,10 @@ int lds_blocks(size_t lds);
 
 // Points of a tile of a single integral (dN = ndim nbins) whose largest iteration
 // has n points, a multiple of bs (its block): about one tile per block, of at most
-// blocks_per_cu blocks on each of ncu compute units, which hold `resident' at once.
+// blocks_per_cu blocks on each of ncu compute units, which hold `resident' at once;
+// refined: a refine launch follows.
 long long single_tile(long long n, long long bs, int ncu, int blocks_per_cu, int prec,
-                      long long dN, int resident);
+                      long long dN, int resident, bool refined);
 
 // The same for the integrals of one precision of a batch (of an engine: one or both
 // halves), which take total points in their largest iterations, rows the sum of
@@ -148,6 +149,8 @@ class VegasEngine {
   // iterations of 10^5 points at d = 8: 212 us; 271 with a graph, and 406 in half
   // of the processes.
   void set_once() { once_ = true; }
+  // The engine makes sampling passes only (dosample_only with sums); before setup.
+  void set_raw() { raw_ = true; }
   // A caller's device integrand (family USER): its compiled DoSample kernel,
   // set before setup.
   void set_user_kernel(hipFunction_t f) { user_fn_ = f; }
@@ -179,7 +182,7 @@ class VegasEngine {
   std::vector<Timed> pending_;
   hipEvent_t ref_ = nullptr;
   std::vector<std::pair<double, double>> ds_iv_;
-  bool capturing_ = false, alone_ = false, once_ = false;
+  bool capturing_ = false, alone_ = false, once_ = false, raw_ = false;
   hipStream_t busy_ = nullptr;  // the stream that may still hold the engine's work
   int iter_launched_ = 0;
   ccuba_ctx *ctx_;

@@ -8,11 +8,12 @@ import paper_1408_6373_amd as cc
 FP64, FP32 = 0, 1
 
 
-def _tiles(n, prec, dN, resident=8, bs=256, ncu=256, per_cu=3):
-    rule = cc._lib["_ZN5ccuba11single_tileExxiiixi"]
-    rule.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int, C.c_int, C.c_longlong, C.c_int]
+def _tiles(n, prec, dN, resident=8, bs=256, ncu=256, per_cu=3, refined=True):
+    rule = cc._lib["_ZN5ccuba11single_tileExxiiixib"]
+    rule.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int, C.c_int, C.c_longlong, C.c_int,
+                     C.c_bool]
     rule.restype = C.c_longlong
-    P = rule(n, bs, ncu, per_cu, prec, dN, resident)
+    P = rule(n, bs, ncu, per_cu, prec, dN, resident, refined)
     assert P > 0 and P % bs == 0
     return -(-n // P)
 
@@ -24,6 +25,8 @@ def test_no_more_tiles_than_blocks(prec, dN):
         for per_cu in (1, 2, 3, 16):
             assert _tiles(n, prec, dN, per_cu=per_cu) <= 256 * per_cu
             assert _tiles(n, prec, dN, per_cu=per_cu, resident=1) <= 256
+        # a pass alone: a tile per block of points; up to 64 for a refine launch
+        assert n > 65536 or _tiles(n, prec, dN, refined=False) == -(-n // 256)
         assert n > 65536 or _tiles(n, prec, dN) <= 64
 
 
