@@ -1126,6 +1126,13 @@ __device__ __forceinline__ bool selected(double e, long long i, unsigned long lo
 }
 
 constexpr int kTopThreads = 1024;
+// Stores up to this many positions have their selected regions counted per tile by
+// the gather and the exact ranking, one workgroup over the boundary digit's
+// candidates; above, where these can be 10^5 and more, by a launch of its own (4 to
+// 9 us).  3 x 10^5 regions a batch at d = 4, oscillatory, to 5 x 10^8 evaluations: 9.88 ms
+// with the ranking's count, 9.64 ms with the launch; 10^5 at d = 2, continuous, to 10^8:
+// 36.2 and 34.5 ms; below 10^6 regions the two are within 2%.
+constexpr long long kCountApart = 1 << 18;
 static_assert(kTopThreads == kScanTile, "the gather's passes are the split's tiles");
 
 // Each selected region is retired and its position written to parent[j],
@@ -1364,6 +1371,21 @@ __global__ void __launch_bounds__(kTopThreads) topk_gather_kernel(const double *
   }
 }
 
+// h[d] += 1 for the lanes with sel, in one add where they share d: adds to one
+// address follow one another, and so would those of equal keys, of positions that
+// differ in other bits, or of one tile's candidates, which the gather wrote together.
+__device__ __forceinline__ void count_digit(unsigned *h, int d, bool sel) {
+  const unsigned long long any = __ballot(sel);
+  if (!any) return;
+  const int l = __ffsll((long long)any) - 1;
+  const int first = __builtin_amdgcn_readlane(d, l);
+  if (__ballot(sel && d != first)) {
+    if (sel) atomicAdd(&h[d], 1u);
+  } else if ((int)(threadIdx.x & 63) == l) {
+    atomicAdd(&h[first], (unsigned)__popcll(any));
+  }
+}
+
 // One workgroup: among the gathered regions, the one of rank krem[0] (from
 // 1) in the order key descending, position ascending: radix passes of 12
 // bits over the key's low 48 bits (descending; for the window's digit 0, whose
@@ -1373,14 +1395,14 @@ __global__ void __launch_bounds__(kTopThreads) topk_gather_kernel(const double *
 // are not all taken (a tie across the threshold), passes of 8 bits over the
 // positions (ascending), else the largest of their positions.  Its key to
 // prefix[0], its position to krem[0]; the selected candidates are added to
-// the counts of their tiles (of nb).
+// the counts of their tiles (of nb; 0: not counted).
 __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned long long *ckey,
                                                                  const long long *cpos,
                                                                  const unsigned long long *cnt,
                                                                  const int *window,
                                                                  unsigned long long *prefix,
                                                                  long long *krem,
-                                                                 long long *bsum, long long nb,
+                                                                 long long *bsum, int nb,
                                                                  const int *done) {
   if (stopped(done)) return;
   __shared__ unsigned h[4096];
@@ -1408,20 +1430,44 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     kr[q] = inreg && i < mc ? ckey[i] : 0ull;  // (a live key is not 0)
     pr[q] = inreg && i < mc ? (unsigned)cpos[i] : 0u;
   }
+  // f(key, position) over the thread's candidates; more than the registers hold are
+  // read again in batches (a load at a time would cost each its way to memory),
+  // their positions only if asked for, f getting the candidate's index otherwise
+  auto each = [&](auto with_positions, auto f) {
+    constexpr bool POS = decltype(with_positions)::value != 0;
+    constexpr int kBatch = 4;
+    if (inreg) {
+#pragma unroll
+      for (int q = 0; q < kExactReg; ++q)
+        if (kr[q]) f(kr[q], (long long)pr[q]);
+    } else {
+      for (long long i0 = t; i0 < mc; i0 += kBatch * kTopThreads) {
+        unsigned long long kk[kBatch];
+        long long pp[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const long long i = i0 + (long long)q * kTopThreads;
+          kk[q] = i < mc ? ckey[i] : 0ull;
+          pp[q] = !POS ? i : i < mc ? cpos[i] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (kk[q]) f(kk[q], pp[q]);
+      }
+    }
+  };
   for (int shift = shared_digit ? 56 : 36; shift >= 0; shift -= shift > 48 ? 8 : 12) {
     const unsigned long long bits = shift >= 48 ? 255ull : 4095ull;
     for (int q = t; q < 4096; q += kTopThreads) h[q] = 0u;
     __syncthreads();
-    if (inreg) {
-#pragma unroll
-      for (int q = 0; q < kExactReg; ++q)
-        if (kr[q] && (kr[q] & mask) == pre) atomicAdd(&h[(kr[q] >> shift) & bits], 1u);
-    } else {
-      for (long long i = t; i < mc; i += kTopThreads) {
-        const unsigned long long k = ckey[i];
-        if ((k & mask) == pre) atomicAdd(&h[(k >> shift) & bits], 1u);
-      }
-    }
+    each(Int<0>{}, [&](unsigned long long k, long long) {
+      const int d = (int)((k >> shift) & bits);
+      const bool sel = (k & mask) == pre;
+      if (!inreg)
+        count_digit(h, d, sel);
+      else if (sel)
+        atomicAdd(&h[d], 1u);
+    });
     __syncthreads();
     long long c4[4];
 #pragma unroll
@@ -1443,24 +1489,13 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     __shared__ long long s_pos;
     if (t == 0) gcnt = 0;
     __syncthreads();
-    if (inreg) {
-#pragma unroll
-      for (int q = 0; q < kExactReg; ++q)
-        if (kr[q] && (kr[q] & mask) == pre) {
-          const int o = atomicAdd(&gcnt, 1);
-          gk[o] = kr[q];
-          gp[o] = pr[q];
-        }
-    } else {
-      for (long long i = t; i < mc; i += kTopThreads) {
-        const unsigned long long k = ckey[i];
-        if ((k & mask) == pre) {
-          const int o = atomicAdd(&gcnt, 1);
-          gk[o] = k;
-          gp[o] = cpos[i];
-        }
+    each(Int<0>{}, [&](unsigned long long k, long long p) {
+      if ((k & mask) == pre) {
+        const int o = atomicAdd(&gcnt, 1);
+        gk[o] = k;
+        gp[o] = inreg ? p : cpos[p];
       }
-    }
+    });
     __syncthreads();
     const int c = gcnt;
     if (t < c) {
@@ -1480,14 +1515,9 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     if (t == 0) s_max = 0ull;
     __syncthreads();
     unsigned long long mx = 0ull;
-    if (inreg) {
-#pragma unroll
-      for (int q = 0; q < kExactReg; ++q)
-        if (kr[q] == pre) mx = max(mx, (unsigned long long)pr[q]);
-    } else {
-      for (long long i = t; i < mc; i += kTopThreads)
-        if (ckey[i] == pre) mx = max(mx, (unsigned long long)cpos[i]);
-    }
+    each(Int<1>{}, [&](unsigned long long k, long long p) {
+      if (k == pre) mx = max(mx, (unsigned long long)p);
+    });
     atomicMax(&s_max, mx);
     __syncthreads();
     tpos = s_max;
@@ -1499,10 +1529,10 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     for (int shift = 24; shift >= 0; shift -= 8) {
       if (t < 256) h[t] = 0u;
       __syncthreads();
-      for (long long i = t; i < mc; i += kTopThreads) {
-        const unsigned long long p = (unsigned long long)cpos[i];
-        if (ckey[i] == pre && (p & pmask) == ppre) atomicAdd(&h[(p >> shift) & 255ull], 1u);
-      }
+      each(Int<1>{}, [&](unsigned long long k, long long p) {
+        count_digit(h, (int)((p >> shift) & 255),
+                    k == pre && ((unsigned long long)p & pmask) == ppre);
+      });
       __syncthreads();
       const long long c1[1] = {t < 256 ? (long long)h[t] : 0};
       pick_digit<1>(c1, need, 256, &dig, &need, &gc);
@@ -1515,32 +1545,37 @@ __global__ void __launch_bounds__(kTopThreads) topk_exact_kernel(const unsigned 
     prefix[0] = pre;
     krem[0] = (long long)tpos;
   }
-  // the selected candidates join the gather's counts, summed in LDS 4096 tiles
-  // at a time (one by one in memory, 16384 candidates of one digit took 60 us)
-  for (long long w0 = 0; w0 < nb; w0 += 4096) {
-    const int n = (int)min(nb - w0, 4096ll);
-    __syncthreads();  // (h's last readers)
-    for (int q = t; q < n; q += kTopThreads) h[q] = 0u;
-    __syncthreads();
-    auto count = [&](unsigned long long k, long long p) {
-      const long long tile = p / kScanTile - w0;
-      if ((k > pre || (k == pre && p <= (long long)tpos)) && tile >= 0 && tile < n)
-        atomicAdd(&h[tile], 1u);
-    };
-    if (inreg) {
+  // the selected candidates join the gather's counts, summed in LDS (one by one in
+  // memory, 16384 candidates of one digit took 60 us)
+  if (nb == 0) return;
+  __syncthreads();  // (h's last readers)
+  for (int q = t; q < nb; q += kTopThreads) h[q] = 0u;
+  __syncthreads();
+  each(Int<1>{}, [&](unsigned long long k, long long p) {
+    count_digit(h, (int)(p / kScanTile), k > pre || (k == pre && p <= (long long)tpos));
+  });
+  __syncthreads();
+  for (int q = t; q < nb; q += kTopThreads)
+    if (const unsigned c = h[q]) bsum[q] += c;
+}
+
+// The selected regions per tile, for the stores whose exact ranking leaves them out.
+__global__ void __launch_bounds__(kScanBlock) sel_count_kernel(const double *err, long long m,
+                                                               const unsigned long long *prefix,
+                                                               const long long *krem,
+                                                               long long *bsum, const int *done) {
+  if (stopped(done)) return;
+  const unsigned long long thr = prefix[0];
+  const long long tpos = krem[0];
+  long long n = 0;
 #pragma unroll
-      for (int q = 0; q < kExactReg; ++q)
-        if (kr[q]) count(kr[q], pr[q]);
-    } else {
-      for (long long i = t; i < mc; i += kTopThreads) {
-        const unsigned long long k = ckey[i];
-        if (k >= pre) count(k, cpos[i]);
-      }
-    }
-    __syncthreads();
-    for (int q = t; q < n; q += kTopThreads)
-      if (const unsigned c = h[q]) bsum[w0 + q] += c;
+  for (int q = 0; q < kScanItems; ++q) {
+    const long long i = (long long)blockIdx.x * kScanTile + q * kScanBlock + threadIdx.x;
+    n += i < m && selected(err[i], i, thr, tpos);
   }
+  long long total;
+  (void)block_excl_scan(n, &total);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
 // totals ---------------------------------------------------------------------
@@ -1732,12 +1767,16 @@ hipError_t launch_select(const CRegions &R, long long m, long long K, const CScr
   hipLaunchKernelGGL(topk_hist_kernel, dim3(hgrid), dim3(kTopThreads), 0, s, R.err, m, S.hist,
                      S.cand_cnt, S.window, E ? key_window(*E) : -1, open ? *open : none, S.done);
   const int ggrid = (int)std::min<long long>(256, (m + kTopThreads - 1) / kTopThreads);
+  const bool apart = m > kCountApart;
   hipLaunchKernelGGL(topk_gather_kernel, dim3(ggrid), dim3(kTopThreads), 0, s, R.err, m, K,
                      S.hist, (const int *)S.window, S.prefix, S.krem, S.cand_key, S.cand_pos,
                      S.cand_cnt, S.bsum, (const int *)S.done);
   hipLaunchKernelGGL(topk_exact_kernel, dim3(1), dim3(kTopThreads), 0, s, S.cand_key, S.cand_pos,
                      S.cand_cnt, (const int *)S.window, S.prefix, S.krem, S.bsum,
-                     scratch_blocks(m), (const int *)S.done);
+                     apart ? 0 : (int)scratch_blocks(m), (const int *)S.done);
+  if (apart)
+    hipLaunchKernelGGL(sel_count_kernel, dim3((unsigned)scratch_blocks(m)), dim3(kScanBlock), 0,
+                       s, R.err, m, S.prefix, S.krem, S.bsum, (const int *)S.done);
   return hipGetLastError();
 }
 

@@ -342,7 +342,8 @@ def _cuhre_as_the_oracle(cc, ctx, fam, d, regions, batch):
 
 @pytest.mark.parametrize("fam,d,regions,batch", [(W.OSCILLATORY, 5, 60000, 9000),
                                                  (W.OSCILLATORY, 3, 200000, 30000),
-                                                 (W.GAUSSIAN, 2, 300000, 90000)])
+                                                 (W.GAUSSIAN, 2, 300000, 90000),
+                                                 (W.C0, 2, 300000, 90000)])
 def test_cuhre_with_many_candidates_matches_oracle(cc, ctx, fam, d, regions, batch):
     # the errors of a smooth integrand share few digits: thousands of candidates for
     # the last places, beyond what the ranking holds in registers too
@@ -350,5 +351,5 @@ def test_cuhre_with_many_candidates_matches_oracle(cc, ctx, fam, d, regions, bat
 
 
 def test_cuhre_with_many_tiles_matches_oracle(cc, ctx):
-    # the last step selects among 4.5 x 10^6 positions: 4392 tiles, counted 4096 at a time
+    # the last step selects among 4.5 x 10^6 positions: 4392 tiles, counted by a launch of their own
     _cuhre_as_the_oracle(cc, ctx, W.OSCILLATORY, 2, 2848576, 1200000)
