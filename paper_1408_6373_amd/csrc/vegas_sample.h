@@ -580,11 +580,19 @@ __global__ void __launch_bounds__(256, sample_waves(sizeof(T) == 4 && POW2, NB))
     if (st.done) continue;  // the same for the whole block: nothing read the cells yet
     // (only now: their loads have been in flight beside the cells').  FP32 at up
     // to 8 dimensions keeps them in vector registers: it has those to spare,
-    // and an instruction reads one scalar operand.  So does a caller's function,
-    // whose loops may index them: 10 x 2 x 10^7 points of a Gaussian's loop at d = 11,
-    // FP32, 2.3 ms, 2.9 with scalar ones.
+    // and an instruction reads one scalar operand.  So do FP64 above 12 dimensions,
+    // where the scalar registers hold a part of them only, and above 8 with
+    // power-of-two bins (other bin counts would pass the 256 registers of two
+    // wavefronts a SIMD), but for the fixed-point histogram: 3 iterations of
+    // 3 x 10^7 points of the continuous family at d = 16, 256 bins, 1818 us with
+    // scalar ones, 1659 now; at d = 12, 6 x 10^6 points, 398 and 336; a Gaussian at
+    // d = 12, 100 bins, 3 x 10^7 points, 1222 and 1319 (so scalar there).  And so does a
+    // caller's function, whose loops may index them: 10 x 2 x 10^7 points of a Gaussian's
+    // loop at d = 11, FP32, 2.3 ms, 2.9 with scalar ones.
 #ifndef CCUBA_RTC
-    if constexpr (sizeof(T) == 8 || NB > 2) {
+    constexpr bool kVector = sizeof(T) == 4 ? NB <= 2
+                                            : !Layout::kFixed && (NB == 4 || (NB == 3 && POW2));
+    if constexpr (!kVector) {
 #pragma unroll
       for (int j = 0; j < ND; ++j) {
         pp0[j] = uniform(pp0[j]);
